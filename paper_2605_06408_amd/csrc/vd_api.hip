@@ -37,7 +37,7 @@ struct vd_context {
     // pint: parent links of the internal nodes; pleaf: leaf record of each site
     DevBuf pts, spts, keys[2], vals[2], inv, mark, child, pint, pleaf, range, counters, nodes, hist, stmp, bbox,
         bpart, misc, loc, cnt_v, cnt_f, cnt_n, vol, cen, flags, offv, offf, offn, scan_tmp, stats, ctr;
-    DevBuf lists[vd::kTiers];  // lists[t]: cells handed on to tier t (t >= 1)
+    DevBuf lists[vd::kTiers];  // lists[t]: cells handed on to tier t (t >= 1); lists[0]: the retry list of the first pass
     DevBuf st_vert[vd::kTiers], st_tri64[vd::kTiers], st_code[vd::kTiers], st_fsize[vd::kTiers], st_fv[vd::kTiers];
     DevBuf arena;  // per-worker cell arrays of the last (16384-vertex) pass
     DevBuf hand[vd::kTiers - 1];  // hand[t]: states of the cells the pass of tier t hands to the next
@@ -67,7 +67,7 @@ struct vd_context {
 namespace {
 
 using vd::kTierCap;
-constexpr int kMiscWords = 16 + vd::kWorkRanges * vd::kTiers;
+constexpr int kMiscWords = 16 + vd::kWorkRanges * (vd::kTiers + 1);
 static_assert(vd::kTiers <= 4 && vd::kWorkRanges == 8, "misc layout");
 
 vd_status ensure(DevBuf& b, size_t bytes) {
@@ -265,14 +265,15 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     VD_TRY(ensure(c->offf, (N + 1) * sizeof(int64_t)));
     VD_TRY(ensure(c->offn, (N + 1) * sizeof(int64_t)));
     VD_TRY(ensure(c->scan_tmp, vd::scan_tmp_size(n) * sizeof(int64_t)));
-    for (int t = 1; t < vd::kTiers; ++t) VD_TRY(ensure(c->lists[t], N * sizeof(uint32_t)));
+    // lists[0] is the retry list of the 64-vertex pass
+    for (int t = 0; t < vd::kTiers; ++t) VD_TRY(ensure(c->lists[t], N * sizeof(uint32_t)));
     VD_TRY(ensure(c->stats, vd::kStatCount * sizeof(unsigned long long)));
     VD_TRY(ensure(c->ctr, vd::kTiers * vd::kCtrCount * sizeof(unsigned long long)));
     VD_TRY(ensure_stage(c, 0, n));
 
-    // misc: [0] error bits, [1] cells left undone for want of slots, [4 + t]
-    // list count of tier t >= 1, [16 + 8 t ..] the kWorkRanges work counters
-    // of tier t
+    // misc: [0] error bits, [1] cells left undone for want of slots, [4] count
+    // of the retry list, [4 + t] list count of tier t >= 1, [16 + 8 t ..] the
+    // kWorkRanges work counters of tier t, those of the retry list last
     uint32_t* misc = as<uint32_t>(c->misc);
     if (prof) VD_HIP(hipEventRecord(c->ev[0], s));
     VD_HIP(hipMemsetAsync(misc, 0, kMiscWords * sizeof(uint32_t), s));
@@ -333,6 +334,11 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     a.stats = as<unsigned long long>(c->stats);
     a.ctr = o.counters ? as<unsigned long long>(c->ctr) : nullptr;
     a.err = misc;
+    a.retry_list = as<uint32_t>(c->lists[0]);
+    a.retry_count = misc + 4;
+    // the options the 64-vertex pass of vd_clip64.hip is written for
+    const bool fast64 = o.precision == 1 && !o.perturb && !o.counters && o.culling == 3 && o.traversal == 1 &&
+                        o.warm_start == 0;
 
     // The clipping passes run back to back with no host synchronisation: the
     // larger passes are launched with persistent grids that read their cell
@@ -397,7 +403,17 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
             a.hand_out_cap = last ? 0u : hand_cap[tier];
             const int workers = last ? arena_workers : vd::clip_grid_workers(tier, c->num_cu);
             if (prof && tier == 0) VD_HIP(hipEventRecord(c->ev[1], s));
+            if (tier == 0 && fast64) {
+                a.retry = 0;
+                VD_HIP(vd::launch_clip64(a, c->num_cu, s));
+                // what it left, built by the general pass
+                a.list = a.retry_list;
+                a.list_count = a.retry_count;
+                a.work_counter = misc + 16 + vd::kWorkRanges * vd::kTiers;
+                a.retry = 1;
+            }
             VD_HIP(vd::launch_clip(a, workers, last ? c->arena.p : nullptr, s));
+            a.retry = 0;
             if (prof && tier == 0) VD_HIP(hipEventRecord(c->ev[2], s));
             if (prof && tier == 1) VD_HIP(hipEventRecord(c->ev[6], s));
         }

@@ -37,9 +37,7 @@
 // and the cell's final record belong to the first wave.  A cell that
 // outgrows a tier is handed to the next.  The paper's own kernel keeps one cell per thread in
 // global memory; that layout was made for its GPUs and is not used.
-#include <type_traits>
-
-#include "vd_internal.h"
+#include "vd_wave.h"
 
 // The slot loops are written once for every tier and marked for unrolling,
 // which the register tiers need (their vertex state is indexed by slot); in
@@ -48,123 +46,6 @@
 
 namespace vd {
 namespace {
-
-// node queue of the 64-vertex pass: kQueue0 entries, the first 64 in
-// registers (one per lane), the rest in LDS and touched only when the queue
-// is that long.  With one entry per vertex slot (64), cells of far-reaching
-// power cells and of sparse regions next to dense ones filled the queue long
-// before their vertex slots and went to the slower second pass.
-constexpr int kQueue0 = 256;
-
-constexpr float kU = 5.9604645e-08f;  // FP32 unit roundoff 2^-24
-constexpr double kU64 = 1.1102230246251565e-16;
-
-// The launch arguments seen through a pointer the compiler cannot keep
-// constant: the fields used once per cell (outputs, lists, counters) are then
-// loaded where they are used instead of being held in scalar registers
-// across the hot loops, which otherwise run out of them and spill.  Every
-// clip kernel takes its ClipArgs as the first kernel argument.
-using KArgs = const __attribute__((address_space(4))) ClipArgs;
-__device__ __forceinline__ KArgs* cold_args() {
-    KArgs* p = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
-enum ClipResult { kNone = 0, kChanged = 1, kEmptied = 2, kOverflow = 3, kRestart = 4 };
-
-__device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
-__device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-__device__ __forceinline__ int popc(uint64_t m) { return __popcll(m); }
-__device__ __forceinline__ int lowest(uint64_t m) { return __builtin_ctzll(m); }
-__device__ __forceinline__ float rdl(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ uint32_t rdl(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
-__device__ __forceinline__ int rdl(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ __forceinline__ float uni(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-// Wave reductions by DPP lane moves (no LDS round trip): within quads
-// (quad_perm [1,0,3,2] and [2,3,0,1]), across half-rows and rows
-// (row_half_mirror, row_mirror), then row 0 into 1 and 2 into 3
-// (row_bcast:15) and rows 0-1 into 2-3 (row_bcast:31); lane 63 holds the
-// result, which is returned to every lane.  All 64 lanes must be active.
-// dpp: lanes of rows the move does not write get `keep` (the identity of
-// the sum it feeds).
-template <int kCtrl, int kRows>
-__device__ __forceinline__ int dpp(int keep, int v) {
-    return __builtin_amdgcn_update_dpp(keep, v, kCtrl, kRows, 0xF, false);
-}
-// A move within rows (every lane reads a lane of its own row, so all reads
-// are valid): the compiler can fold it into the operation that uses it.
-template <int kCtrl>
-__device__ __forceinline__ int dpp_row(int v) {
-    return __builtin_amdgcn_mov_dpp(v, kCtrl, 0xF, 0xF, true);
-}
-// The two row broadcasts write only rows 1, 3 and then 2, 3; what the
-// other rows then hold never reaches lane 63, so they need no defined value.
-template <int kCtrl, int kRows>
-__device__ __forceinline__ int dpp_bcast(int v) {
-    return __builtin_amdgcn_mov_dpp(v, kCtrl, kRows, 0xF, false);
-}
-template <typename Op>
-__device__ __forceinline__ int wave_reduce_i(int v, Op op) {
-    v = op(v, dpp_row<0xB1>(v));
-    v = op(v, dpp_row<0x4E>(v));
-    v = op(v, dpp_row<0x141>(v));
-    v = op(v, dpp_row<0x140>(v));
-    v = op(v, dpp_bcast<0x142, 0xA>(v));
-    v = op(v, dpp_bcast<0x143, 0xC>(v));
-    return __builtin_amdgcn_readlane(v, 63);
-}
-// Float min and max reduce as integers: the bits of a float with the
-// magnitude bits of negative values flipped order like the values (NaN is
-// never reduced), so each step is one integer min or max on a lane move,
-// with no float canonicalisation between the steps.
-__device__ __forceinline__ int ford(float f) {
-    const int i = __float_as_int(f);
-    return i ^ ((i >> 31) & 0x7FFFFFFF);
-}
-__device__ __forceinline__ float unford(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF)); }
-// Maximum of two non-negative floats (their bits order like integers).
-__device__ __forceinline__ float pmax(float a, float b) {
-    return __int_as_float(max(__float_as_int(a), __float_as_int(b)));
-}
-__device__ __forceinline__ float wmin(float v) {
-    return unford(wave_reduce_i(ford(v), [](int a, int b) { return min(a, b); }));
-}
-__device__ __forceinline__ float wmax(float v) {
-    return unford(wave_reduce_i(ford(v), [](int a, int b) { return max(a, b); }));
-}
-__device__ __forceinline__ uint64_t wor64(uint64_t v) {
-    auto op = [](int a, int b) { return a | b; };
-    const uint32_t lo = (uint32_t)wave_reduce_i((int)(uint32_t)v, op);
-    const uint32_t hi = (uint32_t)wave_reduce_i((int)(uint32_t)(v >> 32), op);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-__device__ __forceinline__ uint32_t wsum_u(uint32_t v) {
-    return (uint32_t)wave_reduce_i((int)v, [](int a, int b) { return (int)((uint32_t)a + (uint32_t)b); });
-}
-template <int kCtrl, int kRows>
-__device__ __forceinline__ double dpp64(double v) {
-    const int lo = dpp<kCtrl, kRows>(0, __double2loint(v));
-    const int hi = dpp<kCtrl, kRows>(0, __double2hiint(v));
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wsum64(double v) {
-    v += dpp64<0xB1, 0xF>(v);
-    v += dpp64<0x4E, 0xF>(v);
-    v += dpp64<0x141, 0xF>(v);
-    v += dpp64<0x140, 0xF>(v);
-    v += dpp64<0x142, 0xA>(v);
-    v += dpp64<0x143, 0xC>(v);
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
-}
 
 // Sizes and index packings of a tier.  Three vertex or plane indices are
 // packed into one word: 10 bits each in 32-bit words up to 1024 vertices,
@@ -188,23 +69,6 @@ struct Tier {
         return W(a) | (W(b) << kB) | (W(c) << (2 * kB));
     }
 };
-
-// Orders this wave's accesses to its per-cell arrays, so that what one lane
-// wrote before is seen by every lane after: LDS (one wave, no workgroup
-// barrier needed) or, for the arena tier, global memory (one wave per
-// workgroup).
-template <bool kLds>
-__device__ __forceinline__ void wave_sync() {
-    if constexpr (kLds) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-}
 
 // Per-slot values of one lane: a register array in the register tiers, a
 // column of an arena array otherwise (element s at m[s * kStride]; stride 64
@@ -251,8 +115,6 @@ struct QueueExt<2> {
     uint32_t qxe[kQueue0 - 128];
     float qxk[kQueue0 - 128];
 };
-// queue capacity of the pass of vertex capacity cap
-constexpr int queue_cap(int cap) { return cap < kQueue0 ? kQueue0 : cap; }
 
 template <int VPL>
 struct WaveMem : ArenaState<VPL>, QueueExt<VPL> {
@@ -2419,8 +2281,13 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
             if (C.ln == 0 && C.lead()) atomicAdd(kc->deferred, 1u);
             continue;
         }
-        const uint32_t k = kc->list ? kc->list[c] : c;
-        const uint32_t slot = kc->list ? c : k;
+        uint32_t k = kc->list ? kc->list[c] : c;
+        bool checked = false;  // begin with checked signs
+        if constexpr (VPL == 1) {
+            checked = (k & kRetryChecked) != 0u;
+            k &= ~kRetryChecked;
+        }
+        const uint32_t slot = kc->list && !(VPL == 1 && kc->retry) ? c : k;
         const uint32_t orig = kc->order[k];
         // a cell the previous pass handed over goes on from where it stopped
         using CellT = Cell<VPL, kLds, kCount, G, kSoS, kW, kOpt>;
@@ -2435,9 +2302,9 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
         // re-evaluation of doubtful ones); if that meets an inconsistent
         // configuration it is rebuilt with the FP64 re-evaluation, then with
         // every sign in FP64
-        C.robust = A.precision == 2 ? 1 : 0;
+        C.robust = A.precision == 2 || checked ? 1 : 0;
         bool done = false, escalated = false, loser = false;
-        for (int attempt = 0; attempt < 3 && !done; ++attempt) {
+        for (int attempt = checked ? 1 : 0; attempt < 3 && !done; ++attempt) {
             const bool res = attempt == 0 && hin != nullptr;
             if (res) {
                 C.resume(k, *hin);

@@ -113,6 +113,10 @@ struct HandoffT {
 // Bytes of the hand-over record that the pass of tier t writes (t < kTiers - 1).
 size_t handoff_bytes(int tier);
 
+// Entry of the retry list: the cell's signs were inconsistent in FP32, it is
+// built with checked signs from the start.
+constexpr uint32_t kRetryChecked = 0x80000000u;
+
 struct ClipArgs {
     const float4* pts;        // sites in Morton order: x, y, z, w (w = -inf: coincident loser)
     const uint32_t* order;    // Morton position -> original index
@@ -149,6 +153,12 @@ struct ClipArgs {
     uint32_t hand_out_cap;
     const void* hand_in;
     uint32_t hand_in_cap;
+    // cells the 64-vertex pass of vd_clip64.hip leaves to the general one:
+    // it writes the list (retry 0), the general pass builds it, each cell in
+    // its own slot (retry 1)
+    uint32_t* retry_list;
+    uint32_t* retry_count;
+    int retry;
     Stage stage;
     uint32_t* loc;            // [n] by Morton position
     uint32_t* cnt_v;          // [n] by original index
@@ -262,6 +272,8 @@ hipError_t scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* tmp,
 int clip_grid_workers(int tier, int num_cu);
 size_t arena_bytes_per_worker();
 hipError_t launch_clip(const ClipArgs& a, int workers, void* arena, hipStream_t s);
+// The 64-vertex pass of FP32 builds with the default search options.
+hipError_t launch_clip64(const ClipArgs& a, int num_cu, hipStream_t s);
 hipError_t launch_set_i64(int64_t* dst, int64_t value, hipStream_t s);
 hipError_t launch_write(const WriteArgs& a, hipStream_t s);
 
