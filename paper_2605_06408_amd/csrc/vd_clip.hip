@@ -1680,8 +1680,8 @@ struct Cell {
     // them (a sibling culled here would be culled when popped: the cell only
     // shrinks), top of the path first so that the nearest is queued last.
     // Returns kNone, or what the leaf returned (kEmptied, kOverflow,
-    // kRestart); *deep if the path has more than 64 siblings (the walk then
-    // starts at the root and passes over the own leaf).
+    // kRestart); *deep if the path has more than 64 siblings (nothing is
+    // clipped then, and the walk starts at the root).
     __device__ int own_leaf_start(uint32_t* own, bool* deep) {
         KArgs* ka = cold_args();
         const uint32_t rec = uni(ka->leaf_of[self]);
@@ -1766,8 +1766,7 @@ struct Cell {
                 bool deep;
                 const int r = own_leaf_start(&done_leaf, &deep);
                 if (r != kNone) return r;
-                have = deep;
-                skip_done = deep;
+                have = deep;  // then from the root, the own leaf like any other
             }
         }
         // every node is visited at most once in a valid tree; the bound only

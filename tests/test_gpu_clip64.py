@@ -60,3 +60,36 @@ def test_equals_the_general_pass(kind, n, leaf):
         assert d.sizes["n_large"] >= 1
     if kind == "clustered":
         assert d.sizes["n_fp64"] > 0  # cells of the retry list (tight clusters: inconsistent FP32 signs)
+
+
+def test_path_of_more_than_64_siblings():
+    """A chain of 63 sites, one for each bit of the Morton code, over a group
+    of sites of one code: the tree is deeper than the lanes of a wave.  Certified
+    cells have the oracle's neighbours (those of the chain see the group as one
+    point and are beyond FP32)."""
+    import torch
+    import oracle
+    import paper_2605_06408_amd as vd
+    rng = np.random.default_rng(3)
+    chain = np.zeros((63, 3))
+    for b in range(63):
+        chain[b, b % 3] = 1.25 * 2.0 ** (20 - b // 3)
+    group = rng.random((200, 3)) * 0.5
+    xyz = np.concatenate([chain, group]).astype(np.float32)
+    box = np.array([0.0, 0, 0] + [2.0 ** 22] * 3)
+    ctx = vd.Context(0)
+    d = ctx.build(torch.from_numpy(xyz).cuda(), None, [float(v) for v in box], leaf_size=2)
+    bvh = ctx.inspect_bvh()
+    deepest, todo = 0, [(bvh["root"], 1)]
+    while todo:
+        node, depth = todo.pop()
+        deepest = max(deepest, depth)
+        refs = [int(bvh["nodes"][node, s, 7]) & 0xFFFFFFFF for s in range(2)]
+        todo += [(r, depth + 1) for r in refs if not r & 0x80000000]
+    assert deepest > 64
+    ref = oracle.cells(xyz, None, box)
+    off, nbr = d.nbr_off.cpu().numpy(), d.nbr.cpu().numpy()
+    cert = np.nonzero(ref["margin"] >= 1e-5)[0]
+    assert len(cert) >= 150
+    for i in cert:
+        assert nbr[off[i]:off[i + 1]].tolist() == ref["nbr"][ref["nbr_off"][i]:ref["nbr_off"][i + 1]].tolist(), i
