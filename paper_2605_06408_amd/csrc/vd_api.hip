@@ -35,8 +35,8 @@ struct vd_context {
     int num_cu = 0;
     // grow-only device scratch
     // pint: parent links of the internal nodes; pleaf: leaf record of each site
-    DevBuf pts, spts, keys[2], vals[2], inv, mark, child, pint, pleaf, range, counters, nodes, hist, stmp, bbox,
-        bpart, misc, loc, cnt_v, cnt_f, cnt_n, vol, cen, flags, offv, offf, offn, scan_tmp, stats, ctr;
+    DevBuf pts, spts, keys[2], vals[2], inv, split, pint, pleaf, range, boxes, nodes, sort_tmp, bbox, bpart, misc, loc,
+        cnt_v, cnt_f, cnt_n, vol, cen, flags, offv, offf, offn, scan_tmp, ctr;
     DevBuf lists[vd::kTiers];  // lists[t]: cells handed on to tier t (t >= 1); lists[0]: the retry list of the first pass
     DevBuf st_vert[vd::kTiers], st_tri64[vd::kTiers], st_code[vd::kTiers], st_fsize[vd::kTiers], st_fv[vd::kTiers];
     DevBuf arena;  // per-worker cell arrays of the last (16384-vertex) pass
@@ -45,6 +45,7 @@ struct vd_context {
     DevBuf tet_cnt, tet_off;  // dual tetrahedra per cell and their offsets
     DevBuf bwd_facet, bwd_self, bwd_orphan, bwd_box;  // backward scratch
     DevBuf inspect;  // scratch of vd_inspect_bvh
+    vd::BuildResult* result = nullptr;  // pinned host memory the build's last kernel writes
     void* fixed_scratch = nullptr;  // this device's fixed scratch of vd_backward_noalloc
     // last build
     bool valid = false;
@@ -67,7 +68,11 @@ struct vd_context {
 namespace {
 
 using vd::kTierCap;
-constexpr int kMiscWords = 16 + vd::kWorkRanges * (vd::kTiers + 1);
+constexpr int kCounterWords = vd::kWorkRanges;  // work counters of one pass
+constexpr int kCounterWord = 16;
+constexpr int kStatWord = kCounterWord + kCounterWords * (vd::kTiers + 1);
+constexpr int kMiscWords = kStatWord + 2 * vd::kStatCount;
+static_assert(kStatWord % 2 == 0, "the statistics are 64-bit words");
 static_assert(vd::kTiers <= 4 && vd::kWorkRanges == 8, "misc layout");
 
 vd_status ensure(DevBuf& b, size_t bytes) {
@@ -169,13 +174,14 @@ VD_API void vd_destroy(vd_context* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    DevBuf* all[] = {&c->pts, &c->spts, &c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->inv, &c->mark,
-                     &c->child, &c->pint, &c->pleaf, &c->range, &c->counters, &c->nodes, &c->hist, &c->stmp,
+    DevBuf* all[] = {&c->pts, &c->spts, &c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->inv, &c->split,
+                     &c->pint, &c->pleaf, &c->range, &c->boxes, &c->nodes, &c->sort_tmp,
                      &c->bbox, &c->bpart, &c->misc, &c->loc, &c->cnt_v, &c->cnt_f, &c->cnt_n, &c->vol, &c->cen,
-                     &c->flags, &c->offv, &c->offf, &c->offn, &c->scan_tmp, &c->stats,
+                     &c->flags, &c->offv, &c->offf, &c->offn, &c->scan_tmp,
                      &c->ctr, &c->arena, &c->tet_cnt, &c->tet_off, &c->bwd_facet, &c->bwd_self,
                      &c->bwd_orphan, &c->bwd_box, &c->inspect};
     for (DevBuf* b : all) release(*b);
+    if (c->result) (void)hipHostFree(c->result);
     if (c->ev_ready)
         for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     for (int t = 0; t + 1 < vd::kTiers; ++t) release(c->hand[t]);
@@ -242,17 +248,16 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
         VD_TRY(ensure(c->vals[k], N * sizeof(uint32_t)));
     }
     VD_TRY(ensure(c->inv, N * sizeof(uint32_t)));
-    VD_TRY(ensure(c->mark, N));
-    VD_TRY(ensure(c->child, N * sizeof(int2)));
+    VD_TRY(ensure(c->split, N * sizeof(int)));
     VD_TRY(ensure(c->pint, N * sizeof(int)));
     VD_TRY(ensure(c->pleaf, N * sizeof(int)));
     VD_TRY(ensure(c->range, N * sizeof(int2)));
-    VD_TRY(ensure(c->counters, vd::box_table_size(n) * sizeof(vd::NodeChild)));
+    VD_TRY(ensure(c->boxes, vd::box_table_size(n) * sizeof(vd::NodeChild)));
     VD_TRY(ensure(c->nodes, N * sizeof(vd::Node)));
-    VD_TRY(ensure(c->hist, vd::radix_hist_size(n) * sizeof(uint32_t)));
-    VD_TRY(ensure(c->stmp, vd::scan_tmp_size((int64_t)vd::radix_hist_size(n)) * sizeof(uint64_t)));
+    const size_t sort_words = vd::sort_scratch_words(n);
+    VD_TRY(ensure(c->sort_tmp, sort_words * sizeof(uint32_t)));
     VD_TRY(ensure(c->bbox, 8 * sizeof(float)));
-    VD_TRY(ensure(c->bpart, 1024 * 6 * sizeof(float)));
+    VD_TRY(ensure(c->bpart, vd::kBoxPartials * 6 * sizeof(float)));
     VD_TRY(ensure(c->misc, kMiscWords * sizeof(uint32_t)));
     VD_TRY(ensure(c->loc, N * sizeof(uint32_t)));
     VD_TRY(ensure(c->cnt_v, N * sizeof(uint32_t)));
@@ -264,49 +269,43 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     VD_TRY(ensure(c->offv, (N + 1) * sizeof(int64_t)));
     VD_TRY(ensure(c->offf, (N + 1) * sizeof(int64_t)));
     VD_TRY(ensure(c->offn, (N + 1) * sizeof(int64_t)));
-    VD_TRY(ensure(c->scan_tmp, vd::scan_tmp_size(n) * sizeof(int64_t)));
+    VD_TRY(ensure(c->scan_tmp, 3 * vd::scan_tmp_size(n) * sizeof(int64_t)));
     // lists[0] is the retry list of the 64-vertex pass
     for (int t = 0; t < vd::kTiers; ++t) VD_TRY(ensure(c->lists[t], N * sizeof(uint32_t)));
-    VD_TRY(ensure(c->stats, vd::kStatCount * sizeof(unsigned long long)));
+    if (!c->result) {
+        hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->result), sizeof(vd::BuildResult), hipHostMallocDefault);
+        if (e != hipSuccess) {
+            c->result = nullptr;
+            (void)hipGetLastError();
+            return fail(VD_ERR_OOM, "hipHostMalloc of the result block failed");
+        }
+    }
     VD_TRY(ensure(c->ctr, vd::kTiers * vd::kCtrCount * sizeof(unsigned long long)));
     VD_TRY(ensure_stage(c, 0, n));
 
     // misc: [0] error bits, [1] cells left undone for want of slots, [4] count
-    // of the retry list, [4 + t] list count of tier t >= 1, [16 + 8 t ..] the
-    // kWorkRanges work counters of tier t, those of the retry list last
+    // of the retry list, [4 + t] list count of tier t >= 1, from kCounterWord
+    // the work counters of every tier and of the retry list, then the statistics
     uint32_t* misc = as<uint32_t>(c->misc);
+    unsigned long long* stats = reinterpret_cast<unsigned long long*>(misc + kStatWord);
     if (prof) VD_HIP(hipEventRecord(c->ev[0], s));
     VD_HIP(hipMemsetAsync(misc, 0, kMiscWords * sizeof(uint32_t), s));
+    VD_HIP(hipMemsetAsync(c->sort_tmp.p, 0, sort_words * sizeof(uint32_t), s));
     if (o.counters) VD_HIP(hipMemsetAsync(c->ctr.p, 0, vd::kTiers * vd::kCtrCount * sizeof(unsigned long long), s));
-    VD_HIP(hipMemsetAsync(c->stats.p, 0, vd::kStatCount * sizeof(unsigned long long), s));
     float4* pts = as<float4>(c->pts);
     float* dbbox = as<float>(c->bbox);
-    VD_HIP(vd::launch_pack(xyz, w, n, pts, misc, s));
-    if (bbox) {
-        VD_HIP(hipMemcpyAsync(dbbox, bbox, 6 * sizeof(float), hipMemcpyHostToDevice, s));
-        VD_HIP(vd::launch_check_bbox(dbbox, misc, s));
-    } else {
-        VD_HIP(vd::launch_bbox(pts, n, as<float>(c->bpart), 1024, dbbox, misc, s));
-    }
-    VD_HIP(vd::launch_morton(pts, n, dbbox, as<uint64_t>(c->keys[0]), as<uint32_t>(c->vals[0]), s));
-    bool in_tmp = false;
-    VD_HIP(vd::radix_sort(as<uint64_t>(c->keys[0]), as<uint32_t>(c->vals[0]), as<uint64_t>(c->keys[1]),
-                          as<uint32_t>(c->vals[1]), n, 63, as<uint32_t>(c->hist), as<uint32_t>(c->stmp), s,
-                          &in_tmp));
-    const uint64_t* skeys = as<uint64_t>(c->keys[in_tmp ? 1 : 0]);
-    const uint32_t* order = as<uint32_t>(c->vals[in_tmp ? 1 : 0]);
+    const uint64_t* skeys = as<uint64_t>(c->keys[0]);
+    const uint32_t* order = as<uint32_t>(c->vals[0]);
     float4* spts = as<float4>(c->spts);
-    VD_HIP(vd::launch_gather(pts, order, n, spts, as<uint32_t>(c->inv), s));
-    VD_HIP(vd::launch_losers(spts, skeys, order, n, as<uint8_t>(c->mark), s));
-    uint32_t root;
-    if (n > o.leaf_size) {
-        VD_HIP(vd::launch_karras(skeys, n, as<int2>(c->child), as<uint32_t>(c->pint), as<int2>(c->range), s));
-        VD_HIP(vd::launch_bounds(spts, n, as<int2>(c->child), as<int2>(c->range), as<vd::NodeChild>(c->counters),
-                                 as<vd::Node>(c->nodes), as<uint32_t>(c->pleaf), o.leaf_size, s));
-        root = 0;
-    } else {
-        root = vd::leaf_ref(0u, (uint32_t)n);
-    }
+    vd::BoxArg box{};
+    if (bbox) std::memcpy(box.v, bbox, sizeof(box.v));
+    VD_HIP(vd::launch_sort_sites(xyz, w, n, bbox ? &box : nullptr, dbbox, as<float>(c->bpart), pts,
+                                 as<uint64_t>(c->keys[0]), as<uint32_t>(c->vals[0]), as<uint64_t>(c->keys[1]),
+                                 as<uint32_t>(c->vals[1]), as<uint32_t>(c->sort_tmp), misc, s));
+    VD_HIP(vd::launch_tree(pts, skeys, order, n, spts, as<uint32_t>(c->inv), as<vd::NodeChild>(c->boxes),
+                           as<int>(c->split), as<uint32_t>(c->pint), as<int2>(c->range), as<vd::Node>(c->nodes),
+                           as<uint32_t>(c->pleaf), o.leaf_size, s));
+    const uint32_t root = n > o.leaf_size ? 0u : vd::leaf_ref(0u, (uint32_t)n);
 
     vd::ClipArgs a{};
     a.pts = spts;
@@ -331,7 +330,7 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     a.vol = as<float>(c->vol);
     a.cen = as<float>(c->cen);
     a.flags = as<uint8_t>(c->flags);
-    a.stats = as<unsigned long long>(c->stats);
+    a.stats = stats;
     a.ctr = o.counters ? as<unsigned long long>(c->ctr) : nullptr;
     a.err = misc;
     a.retry_list = as<uint32_t>(c->lists[0]);
@@ -349,13 +348,12 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     // undone and counts them; the one synchronisation at the end then sees the
     // counts, the buffers grow, and the passes run again (a first build of a
     // larger workload; the LBVH is kept).
-    uint32_t hmisc[16];
-    int64_t tot[3];
-    unsigned long long st[vd::kStatCount];
+    const uint32_t* hmisc = c->result->misc;
+    const int64_t* tot = c->result->tot;
+    const unsigned long long* st = c->result->stats;
     for (int attempt = 0;; ++attempt) {
         if (attempt > 0) {
             VD_HIP(hipMemsetAsync(misc + 1, 0, (kMiscWords - 1) * sizeof(uint32_t), s));
-            VD_HIP(hipMemsetAsync(c->stats.p, 0, vd::kStatCount * sizeof(unsigned long long), s));
             if (o.counters)
                 VD_HIP(hipMemsetAsync(c->ctr.p, 0, vd::kTiers * vd::kCtrCount * sizeof(unsigned long long), s));
         }
@@ -388,7 +386,7 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
         for (int tier = 0; tier < vd::kTiers; ++tier) {
             const bool last = tier + 1 == vd::kTiers;
             a.tier = tier;
-            a.work_counter = misc + 16 + vd::kWorkRanges * tier;
+            a.work_counter = misc + kCounterWord + kCounterWords * tier;
             a.list = tier ? as<uint32_t>(c->lists[tier]) : nullptr;
             a.list_count = tier ? misc + 4 + tier : nullptr;
             a.slots = slots[tier];
@@ -409,7 +407,7 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
                 // what it left, built by the general pass
                 a.list = a.retry_list;
                 a.list_count = a.retry_count;
-                a.work_counter = misc + 16 + vd::kWorkRanges * vd::kTiers;
+                a.work_counter = misc + kCounterWord + kCounterWords * vd::kTiers;
                 a.retry = 1;
             }
             VD_HIP(vd::launch_clip(a, workers, last ? c->arena.p : nullptr, s));
@@ -418,16 +416,23 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
             if (prof && tier == 1) VD_HIP(hipEventRecord(c->ev[6], s));
         }
         if (prof) VD_HIP(hipEventRecord(c->ev[3], s));
-        VD_HIP(vd::scan_counts(as<uint32_t>(c->cnt_v), n, as<int64_t>(c->offv), as<int64_t>(c->scan_tmp), s));
-        VD_HIP(vd::scan_counts(as<uint32_t>(c->cnt_f), n, as<int64_t>(c->offf), as<int64_t>(c->scan_tmp), s));
-        VD_HIP(vd::scan_counts(as<uint32_t>(c->cnt_n), n, as<int64_t>(c->offn), as<int64_t>(c->scan_tmp), s));
-        VD_HIP(hipMemcpyAsync(&tot[0], as<int64_t>(c->offv) + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        VD_HIP(hipMemcpyAsync(&tot[1], as<int64_t>(c->offf) + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        VD_HIP(hipMemcpyAsync(&tot[2], as<int64_t>(c->offn) + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        if (prof) VD_HIP(hipEventRecord(c->ev[4], s));
-        VD_HIP(hipMemcpyAsync(st, c->stats.p, sizeof(st), hipMemcpyDeviceToHost, s));
-        VD_HIP(hipMemcpyAsync(hmisc, misc, sizeof(hmisc), hipMemcpyDeviceToHost, s));
-        if (prof) VD_HIP(hipEventRecord(c->ev[5], s));
+        vd::Scan3Args sc{};
+        sc.n = n;
+        sc.in[0] = a.cnt_v;
+        sc.in[1] = a.cnt_f;
+        sc.in[2] = a.cnt_n;
+        sc.out[0] = as<int64_t>(c->offv);
+        sc.out[1] = as<int64_t>(c->offf);
+        sc.out[2] = as<int64_t>(c->offn);
+        sc.partial = as<int64_t>(c->scan_tmp);
+        sc.stats = stats;
+        sc.misc = misc;
+        sc.res = c->result;
+        VD_HIP(vd::launch_scan3(sc, s));
+        if (prof) {
+            VD_HIP(hipEventRecord(c->ev[4], s));
+            VD_HIP(hipEventRecord(c->ev[5], s));
+        }
         VD_HIP(hipStreamSynchronize(s));  // the one synchronisation of a build
         if (hmisc[0] & 1u) return fail(VD_ERR_INVALID_ARG, "vd_build: non-finite site coordinate or weight");
         if (hmisc[0] & 2u) return fail(VD_ERR_INVALID_ARG, "vd_build: degenerate bounding box");
@@ -504,16 +509,18 @@ VD_API vd_status vd_write(vd_context* c, const vd_outputs* out, void* stream) {
     a.fv = out->fv;
     a.vert = out->vert;
     a.vert_planes = out->vert_planes;
-    if (a.nbr || a.facet_nbr || a.fv_off || a.fv || a.vert || a.vert_planes) VD_HIP(vd::launch_write(a, s));
-    const size_t off_bytes = (size_t)(n + 1) * sizeof(int64_t);
-    if (out->nbr_off) VD_HIP(hipMemcpyAsync(out->nbr_off, c->offn.p, off_bytes, hipMemcpyDeviceToDevice, s));
-    if (out->facet_off) VD_HIP(hipMemcpyAsync(out->facet_off, c->offf.p, off_bytes, hipMemcpyDeviceToDevice, s));
-    if (out->vert_off) VD_HIP(hipMemcpyAsync(out->vert_off, c->offv.p, off_bytes, hipMemcpyDeviceToDevice, s));
-    if (out->fv_off) VD_HIP(vd::launch_set_i64(out->fv_off + c->sizes.n_facet, c->sizes.n_fv, s));
-    if (out->vol) VD_HIP(hipMemcpyAsync(out->vol, c->vol.p, (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
-    if (out->centroid)
-        VD_HIP(hipMemcpyAsync(out->centroid, c->cen.p, 3 * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
-    if (out->flags) VD_HIP(hipMemcpyAsync(out->flags, c->flags.p, (size_t)n, hipMemcpyDeviceToDevice, s));
+    a.nbr_off = out->nbr_off;
+    a.facet_off = out->facet_off;
+    a.vert_off = out->vert_off;
+    a.vol_out = out->vol;
+    a.cen_out = out->centroid;
+    a.flags_out = out->flags;
+    a.vol = as<float>(c->vol);
+    a.cen = as<float>(c->cen);
+    a.flags = as<uint8_t>(c->flags);
+    a.fv_end = out->fv_off ? out->fv_off + c->sizes.n_facet : nullptr;
+    a.n_fv = c->sizes.n_fv;
+    VD_HIP(vd::launch_write(a, s));
     if (prof) {
         VD_HIP(hipEventRecord(c->ev[8], s));
         c->write_profiled = true;

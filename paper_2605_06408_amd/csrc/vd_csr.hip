@@ -107,14 +107,59 @@ hipError_t scan_counts(const uint32_t* in, int64_t n, int64_t* out, int64_t* tmp
     return hipGetLastError();
 }
 
-hipError_t scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* tmp, hipStream_t s) {
-    int64_t nblk = (n + kScanTile - 1) / kScanTile;
-    if (nblk < 1) nblk = 1;
-    hipLaunchKernelGGL((k_scan_reduce<uint32_t, uint32_t>), dim3((unsigned)nblk), dim3(kScanThreads), 0, s, in, n,
-                       tmp);
-    hipLaunchKernelGGL((k_scan_mid<uint32_t>), dim3(1), dim3(kScanThreads), 0, s, tmp, nblk);
-    hipLaunchKernelGGL((k_scan_final<uint32_t, uint32_t, uint32_t>), dim3((unsigned)nblk), dim3(kScanThreads), 0, s,
-                       in, n, tmp, out, 0);
+// The three scans of a build.  A tile is kScanTile counts; its block sums the
+// totals of the tiles before it by itself (they are few), so there is no
+// launch in between, and up to one tile there is only the last kernel.  The
+// last block also puts what the host waits for into host memory: one
+// synchronisation, no copies.  Three scans of three kernels each and five
+// copies took 90 us of a build of a thousand sites.
+__global__ __launch_bounds__(kScanThreads) void k_scan3_reduce(Scan3Args a) {
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    for (int q = 0; q < 3; ++q) {
+        int64_t s = 0;
+        for (int k = 0; k < kScanItems; ++k)
+            if (base + k < a.n) s += (int64_t)a.in[q][base + k];
+        int64_t tot;
+        block_exclusive_scan<int64_t>(s, &tot);
+        if (threadIdx.x == 0) a.partial[(int64_t)q * gridDim.x + blockIdx.x] = tot;
+    }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan3_final(Scan3Args a) {
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    for (int q = 0; q < 3; ++q) {
+        int64_t before = 0, carry = 0;
+        for (int64_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads)
+            before += a.partial[(int64_t)q * gridDim.x + t];
+        block_exclusive_scan<int64_t>(before, &carry);
+        uint32_t v[kScanItems];
+        int64_t s = 0;
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = base + k < a.n ? a.in[q][base + k] : 0u;
+            s += (int64_t)v[k];
+        }
+        int64_t tot;
+        int64_t e = block_exclusive_scan<int64_t>(s, &tot) + carry;
+        for (int k = 0; k < kScanItems; ++k) {
+            if (base + k < a.n) a.out[q][base + k] = e;
+            e += (int64_t)v[k];
+        }
+        if (last && threadIdx.x == 0) {
+            a.out[q][a.n] = carry + tot;
+            a.res->tot[q] = carry + tot;
+        }
+    }
+    if (last) {
+        if (threadIdx.x < kStatCount) a.res->stats[threadIdx.x] = a.stats[threadIdx.x];
+        if (threadIdx.x < 16) a.res->misc[threadIdx.x] = a.misc[threadIdx.x];
+    }
+}
+
+hipError_t launch_scan3(const Scan3Args& a, hipStream_t s) {
+    const int64_t nblk = (a.n + kScanTile - 1) / kScanTile;
+    if (nblk > 1) hipLaunchKernelGGL(k_scan3_reduce, dim3((unsigned)nblk), dim3(kScanThreads), 0, s, a);
+    hipLaunchKernelGGL(k_scan3_final, dim3((unsigned)nblk), dim3(kScanThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -126,11 +171,32 @@ hipError_t scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* tmp,
 // flight per wave is what fills the memory system.
 constexpr int kWriteLanes = 16;
 
-__global__ __launch_bounds__(256) void k_write(WriteArgs a) {
+// The last `copies` blocks of the launch copy the arrays that are one value per
+// cell (seven copies of their own were seven launches).
+__device__ void write_copies(const WriteArgs& a, int64_t i, int64_t step) {
+    if (a.fv_end && i == 0) *a.fv_end = a.n_fv;
+    for (int64_t k = i; k <= a.n; k += step) {
+        if (a.nbr_off) a.nbr_off[k] = a.off_n[k];
+        if (a.facet_off) a.facet_off[k] = a.off_f[k];
+        if (a.vert_off) a.vert_off[k] = a.off_v[k];
+        if (k == a.n) break;
+        if (a.vol_out) a.vol_out[k] = a.vol[k];
+        if (a.flags_out) a.flags_out[k] = a.flags[k];
+    }
+    if (a.cen_out)
+        for (int64_t k = i; k < 3 * a.n; k += step) a.cen_out[k] = a.cen[k];
+}
+
+__global__ __launch_bounds__(256) void k_write(WriteArgs a, int copies) {
     constexpr int LP = kWriteLanes;
+    const int64_t rows = (int64_t)gridDim.x - copies;
+    if (blockIdx.x >= rows) {
+        write_copies(a, ((int64_t)blockIdx.x - rows) * blockDim.x + threadIdx.x, (int64_t)copies * blockDim.x);
+        return;
+    }
     const int ln = threadIdx.x & (LP - 1);
     const int64_t grp = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LP;
-    const int64_t ngrp = ((int64_t)gridDim.x * blockDim.x) / LP;
+    const int64_t ngrp = (rows * blockDim.x) / LP;
     for (int64_t i = grp; i < a.n; i += ngrp) {
         const uint32_t k = a.inv[i];
         const uint32_t loc = a.loc[k];
@@ -189,10 +255,14 @@ __global__ __launch_bounds__(256) void k_write(WriteArgs a) {
 }
 
 hipError_t launch_write(const WriteArgs& a, hipStream_t s) {
+    const bool rows = a.nbr || a.facet_nbr || a.fv_off || a.fv || a.vert || a.vert_planes;
+    const bool flat = a.nbr_off || a.facet_off || a.vert_off || a.vol_out || a.cen_out || a.flags_out || a.fv_end;
     const int64_t groups = a.n < 4 * 65536 ? a.n : 4 * 65536;
-    int64_t blocks = (groups * kWriteLanes + 255) / 256;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_write, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    const int64_t blocks = rows ? (groups * kWriteLanes + 255) / 256 : 0;
+    int64_t copies = flat ? (a.n + 1023) / 1024 : 0;
+    if (copies > 1024) copies = 1024;
+    if (blocks + copies < 1) return hipSuccess;
+    hipLaunchKernelGGL(k_write, dim3((unsigned)(blocks + copies)), dim3(256), 0, s, a, (int)copies);
     return hipGetLastError();
 }
 
@@ -262,15 +332,6 @@ hipError_t launch_tet_count(const TetArgs& a, hipStream_t s) {
 
 hipError_t launch_tet_write(const TetArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_tets<true>, dim3((unsigned)tet_blocks(a.n)), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-__global__ void k_set_i64(int64_t* dst, int64_t value) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = value;
-}
-
-hipError_t launch_set_i64(int64_t* dst, int64_t value, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(64), 0, s, dst, value);
     return hipGetLastError();
 }
 

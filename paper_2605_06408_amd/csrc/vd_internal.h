@@ -189,6 +189,19 @@ struct WriteArgs {
     int32_t* fv;
     float* vert;
     int32_t* vert_planes;
+    // arrays copied as they are (null: not wanted): the three offset arrays,
+    // volumes, centroids, flags
+    int64_t* nbr_off;
+    int64_t* facet_off;
+    int64_t* vert_off;
+    float* vol_out;
+    float* cen_out;
+    uint8_t* flags_out;
+    const float* vol;
+    const float* cen;
+    const uint8_t* flags;
+    int64_t* fv_end;          // last entry of fv_off
+    int64_t n_fv;
 };
 
 // Inputs and outputs of the backward pass over the last build.
@@ -233,37 +246,53 @@ int64_t bwd_waves(int64_t n);
 // ---------------------------------------------------------------- launches
 // (host wrappers; each returns the hipError_t of its launch)
 
-hipError_t launch_pack(const float* xyz, const float* w, int64_t n, float4* pts, uint32_t* err, hipStream_t s);
-hipError_t launch_bbox(const float4* pts, int64_t n, float* partial, int nblk_max, float* bbox, uint32_t* err,
-                       hipStream_t s);
-hipError_t launch_check_bbox(float* bbox, uint32_t* err, hipStream_t s);
+// The initial cell, given by the caller.
+struct BoxArg {
+    float v[6];
+};
+constexpr int kBoxPartials = 1024;  // partial boxes of the sites' own box (6 floats each)
+
+// Packs the sites, makes the box (the caller's, or with box == null that of
+// the sites; 6 floats) and sorts the Morton codes: pts in the caller's order,
+// keys sorted with vals[k] the site at position k.  scratch: zeroed
+// sort_scratch_words(n) words; keys_tmp, vals_tmp: as keys and vals; bpart:
+// kBoxPartials * 6 floats.  Rejected input sets bits of *err.
+size_t sort_scratch_words(int64_t n);
+hipError_t launch_sort_sites(const float* xyz, const float* w, int64_t n, const BoxArg* box, float* bbox, float* bpart,
+                             float4* pts, uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp,
+                             uint32_t* scratch, uint32_t* err, hipStream_t s);
 hipError_t launch_morton(const float4* pts, int64_t n, const float* bbox, uint64_t* keys, uint32_t* vals,
                          hipStream_t s);
-// LSD radix sort of 64-bit keys with 32-bit values over `bits` low bits.
-// tmp buffers: same sizes; hist: radix_hist_size(n) uint32.
-size_t radix_hist_size(int64_t n);
-hipError_t radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp, int64_t n, int bits,
-                      uint32_t* hist, uint32_t* scan_tmp, hipStream_t s, bool* result_in_tmp);
-hipError_t launch_gather(const float4* pts, const uint32_t* order, int64_t n, float4* spts, uint32_t* inv,
-                         hipStream_t s);
-hipError_t launch_losers(float4* spts, const uint64_t* keys, const uint32_t* order, int64_t n, uint8_t* mark,
-                         hipStream_t s);
-// Binary radix tree over the sorted codes: children, ranges, and the parent
-// link of every internal node ((parent << 1) | which child; kNoParent at the
-// root).
-hipError_t launch_karras(const uint64_t* keys, int64_t n, int2* child, uint32_t* up, int2* range, hipStream_t s);
-// Child boxes and max weights of every internal node (range reductions over a
-// sparse table of 64-site block boxes; table: box_table_size(n) entries), and
-// the leaf record of every site ((node << 1) | which child, by Morton position).
+// The sites in Morton order with coincident ones resolved, and the hierarchy
+// over them (if n > leaf_size): parent link of every internal node ((parent
+// << 1) | which child; kNoParent at the root), child records of the nodes above
+// the leaves, leaf record of every site.  table: box_table_size(n) entries.
 size_t box_table_size(int64_t n);
-hipError_t launch_bounds(const float4* spts, int64_t n, const int2* child, const int2* range, NodeChild* table,
-                         Node* nodes, uint32_t* leaf_of, int leaf_size, hipStream_t s);
+hipError_t launch_tree(const float4* pts, const uint64_t* keys, const uint32_t* order, int64_t n, float4* spts,
+                       uint32_t* inv, NodeChild* table, int* split, uint32_t* up, int2* range, Node* nodes,
+                       uint32_t* leaf_of, int leaf_size, hipStream_t s);
 
 // Exclusive scan of uint32 counts into int64 offsets [n+1] (out[n] = total).
 size_t scan_tmp_size(int64_t n);
 hipError_t scan_counts(const uint32_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s);
-// Exclusive scan of uint32 -> uint32 (for radix histograms).
-hipError_t scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* tmp, hipStream_t s);
+// The three scans of a build at once, and what the host waits for: the
+// totals, the statistics and the first words of the counters, written to host
+// memory (res, seen by the device).
+struct BuildResult {
+    int64_t tot[3];
+    unsigned long long stats[kStatCount];
+    uint32_t misc[16];
+};
+struct Scan3Args {
+    int64_t n;
+    const uint32_t* in[3];
+    int64_t* out[3];
+    int64_t* partial;         // scan_tmp_size(n) * 3
+    const unsigned long long* stats;
+    const uint32_t* misc;
+    BuildResult* res;
+};
+hipError_t launch_scan3(const Scan3Args& a, hipStream_t s);
 
 // Cell workers to launch for a clipping pass (a wave in the two register
 // tiers, a workgroup of waves sharing one cell in the two larger ones), and
@@ -274,7 +303,6 @@ size_t arena_bytes_per_worker();
 hipError_t launch_clip(const ClipArgs& a, int workers, void* arena, hipStream_t s);
 // The 64-vertex pass of FP32 builds with the default search options.
 hipError_t launch_clip64(const ClipArgs& a, int num_cu, hipStream_t s);
-hipError_t launch_set_i64(int64_t* dst, int64_t value, hipStream_t s);
 hipError_t launch_write(const WriteArgs& a, hipStream_t s);
 
 // Dual tetrahedra of the staged cells (see vd_tetrahedra): count per cell,
