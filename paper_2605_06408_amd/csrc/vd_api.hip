@@ -68,8 +68,8 @@ struct vd_context {
 namespace {
 
 using vd::kTierCap;
-constexpr int kCounterWords = vd::kWorkRanges;  // work counters of one pass
-constexpr int kCounterWord = 16;
+constexpr int kCounterWords = vd::kWorkRanges * vd::kCounterStride;  // work counters of one pass
+constexpr int kCounterWord = 64;
 constexpr int kStatWord = kCounterWord + kCounterWords * (vd::kTiers + 1);
 constexpr int kMiscWords = kStatWord + 2 * vd::kStatCount;
 static_assert(kStatWord % 2 == 0, "the statistics are 64-bit words");

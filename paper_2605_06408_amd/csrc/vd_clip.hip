@@ -2230,6 +2230,8 @@ struct Cell {
     }
 };
 
+constexpr int kWaves1 = 4, kWaves2 = 2;  // waves per block of the two register tiers
+
 // The work loop shared by every tier (per wave, or per wave group with gx
 // its exchange tables).
 template <int VPL, bool kLds, bool kCount, int G = 1, bool kSoS = false, bool kW = true, bool kOpt = true>
@@ -2242,37 +2244,13 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
     if (count == 0) return;  // a larger pass with no cell
     Cell<VPL, kLds, kCount, G, kSoS, kW, kOpt> C(M, A, gx);
     unsigned long long st_empty = 0, st_large = 0, st_unc = 0, st_fail = 0, st_fp64 = 0, st_res = 0, st_pert = 0;
-    // Cells are split into kWorkRanges contiguous (Morton-ordered) ranges, one
-    // per XCD: the waves of workgroup b take chunks of their own range b % 8
-    // first, so neighbouring cells (which walk the same nodes and sites) share
-    // one L2, then help the other ranges.  A worker claims one cell at a time:
-    // in the later passes, which get the few cells that overflowed, claiming
-    // several made one worker build several large cells in a row while others
-    // idled, and in the first pass single claims also end the pass sooner.
-    uint32_t r = blockIdx.x % kWorkRanges;
-    int tried = 0;
-    uint32_t cur = 0, end = 0;
+    constexpr uint32_t kWorkers = G > 1 ? 1u : (VPL == 1 ? kWaves1 : kWaves2);
+    Work<kWorkers> work(count);
     for (;;) {
-        if (cur >= end) {
-            bool got = false;
-            while (tried < kWorkRanges) {
-                const uint32_t lo = (uint32_t)((uint64_t)count * r / kWorkRanges);
-                const uint32_t hi = (uint32_t)((uint64_t)count * (r + 1) / kWorkRanges);
-                uint32_t c0 = 0;
-                if (C.ln == 0 && C.lead()) c0 = atomicAdd(&cold_args()->work_counter[r], 1u);
-                c0 = C.bcast(c0);
-                if (c0 < hi - lo) {
-                    cur = lo + c0;
-                    end = cur + 1;
-                    got = true;
-                    break;
-                }
-                r = (r + 1) % kWorkRanges;
-                ++tried;
-            }
-            if (!got) break;
-        }
-        const uint32_t c = cur++;
+        uint32_t c = 0;
+        if (C.lead()) c = work.next(G > 1 ? 0u : uni((uint32_t)threadIdx.x >> 6));
+        c = C.bcast(c);
+        if (c == kNoCell) break;
         KArgs* kc = cold_args();
         if (kc->list && c >= kc->slots) {
             // no staging slot: left undone and counted (the build runs the
@@ -2453,11 +2431,11 @@ int clip_grid_workers(int tier, int num_cu) {
     int per_cu = 0;
     hipError_t e = hipSuccess;
     if (tier == 0) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip<1, 4, false>, 256, 0);
-        per_cu *= 4;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip<1, kWaves1, false>, 64 * kWaves1, 0);
+        per_cu *= kWaves1;
     } else if (tier == 1) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip<2, 2, false>, 128, 0);
-        per_cu *= 2;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip<2, kWaves2, false>, 64 * kWaves2, 0);
+        per_cu *= kWaves2;
     } else if (tier == 2) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip_lds<false>, 64 * kGroupLds, 0);
         if (e == hipSuccess && per_cu > 0) return per_cu * num_cu;
@@ -2476,19 +2454,19 @@ void launch_tier(const ClipArgs& a, int workers, void* arena, hipStream_t s) {
     switch (a.tier) {
         case 0:
             if (kSoS || !def)
-                hipLaunchKernelGGL((k_clip<1, 4, kCount, kSoS>), dim3((workers + 3) / 4), dim3(256), 0, s, a);
+                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, kSoS>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
             else if (a.weighted)
-                hipLaunchKernelGGL((k_clip<1, 4, kCount, false, true, false>), dim3((workers + 3) / 4), dim3(256), 0, s, a);
+                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, true, false>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
             else
-                hipLaunchKernelGGL((k_clip<1, 4, kCount, false, false, false>), dim3((workers + 3) / 4), dim3(256), 0, s, a);
+                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, false, false>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
             break;
         case 1:
             if (kSoS || !def)
-                hipLaunchKernelGGL((k_clip<2, 2, kCount, kSoS>), dim3((workers + 1) / 2), dim3(128), 0, s, a);
+                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, kSoS>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
             else if (a.weighted)
-                hipLaunchKernelGGL((k_clip<2, 2, kCount, false, true, false>), dim3((workers + 1) / 2), dim3(128), 0, s, a);
+                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, true, false>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
             else
-                hipLaunchKernelGGL((k_clip<2, 2, kCount, false, false, false>), dim3((workers + 1) / 2), dim3(128), 0, s, a);
+                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, false, false>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
             break;
         case 2:
             hipLaunchKernelGGL((k_clip_lds<kCount, kSoS>), dim3(workers), dim3(64 * kGroupLds), 0, s, a);

@@ -115,6 +115,8 @@ union WaveMem64 {
     FinalMem f;
 };
 
+constexpr int kWaves64 = 4;  // waves per block
+
 #pragma clang attribute push(__attribute__((always_inline)), apply_to = function)
 
 template <bool kW>
@@ -945,36 +947,15 @@ struct Cell64 {
     }
 };
 
-// Cells are split into kWorkRanges contiguous (Morton-ordered) ranges, one
-// per XCD; a wave claims one cell at a time from its own range, then helps
-// the others.
 template <bool kW>
 __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
-    KArgs* ka = cold_args();
-    if (*ka->err != 0u) return;  // rejected input
-    const uint32_t count = (uint32_t)A.n;
+    if (*cold_args()->err != 0u) return;  // rejected input
     Cell64<kW> C(M, A);
     unsigned long long st_empty = 0;
-    uint32_t r = blockIdx.x % kWorkRanges;
-    int tried = 0;
+    Work<kWaves64> work((uint32_t)A.n);
     for (;;) {
-        uint32_t k = 0;
-        bool got = false;
-        while (tried < kWorkRanges) {
-            const uint32_t lo = (uint32_t)((uint64_t)count * r / kWorkRanges);
-            const uint32_t hi = (uint32_t)((uint64_t)count * (r + 1) / kWorkRanges);
-            uint32_t c0 = 0;
-            if (C.ln == 0) c0 = atomicAdd(&cold_args()->work_counter[r], 1u);
-            c0 = uni(c0);
-            if (c0 < hi - lo) {
-                k = lo + c0;
-                got = true;
-                break;
-            }
-            r = (r + 1) % kWorkRanges;
-            ++tried;
-        }
-        if (!got) break;
+        const uint32_t k = work.next(uni((uint32_t)threadIdx.x >> 6));
+        if (k == kNoCell) break;
         const uint32_t orig = cold_args()->order[k];
         int res = kEmptied;  // also a site that lost its position to a heavier one
         if (C.init(k)) {
@@ -1002,8 +983,6 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
 }
 
 #pragma clang attribute pop
-
-constexpr int kWaves64 = 4;  // waves per block
 
 // 72 registers for 7 waves per SIMD: the loops fit, finishing a cell spills a
 // few values.  A build of clustered 1M sites: 20.7 ms at 4 waves, 18.8 at 5,

@@ -13,8 +13,9 @@ constexpr int kMaxLeaf = 64;                 // leaf refs store count-1 in 6 bit
 constexpr int64_t kMaxSites = int64_t(1) << 25;  // leaf refs store `first` in 25 bits
 constexpr int kDefaultLeaf = 32;
 // Work distribution of the clip kernels: one contiguous range of cells per
-// XCD (workgroup b runs on XCD b % 8), claimed one cell at a time.
+// XCD (workgroup b runs on XCD b % 8).
 constexpr int kWorkRanges = 8;
+constexpr int kCounterStride = 64;  // words between the counters of two ranges (256 bytes)
 // Vertex (= plane) capacity of a cell in each clipping pass.
 constexpr int kTiers = 4;
 constexpr int kTierCap[kTiers] = {64, 128, 1024, 16384};
@@ -136,7 +137,8 @@ struct ClipArgs {
     int weighted;             // 0: no weights were given (every weight is zero)
     int tier;                 // 0..3 (capacity kTierCap[tier])
     // work: cells c in [0, count) are list[c] (or c itself when list == null),
-    // split into kWorkRanges contiguous ranges with one counter each (zeroed)
+    // split into kWorkRanges contiguous ranges with one counter each (zeroed,
+    // kCounterStride words apart)
     uint32_t* work_counter;
     const uint32_t* list;
     const uint32_t* list_count;   // device count (list != null), else count = n

@@ -143,6 +143,76 @@ __device__ __forceinline__ void wave_sync() {
     }
 }
 
+// Hands out the cells of a pass to its workers (a wave, or a group of waves
+// that share one cell), one at a time.  The cells are split into kWorkRanges
+// contiguous (Morton-ordered) ranges, one per XCD: the workers of workgroup b
+// take cells of range b % 8 first, so that neighbouring cells, which walk the
+// same nodes and sites, share one L2, then help the other ranges.
+//
+// A worker's first cell is fixed by its number, so a pass with fewer cells
+// than workers claims nothing; after that each range has a counter, on a cache
+// line of its own, and a worker whose range is used up reads all eight
+// counters at once before it claims elsewhere.  Additions to one line go
+// through one after the other, about 20 ns each over the whole device: with
+// the eight counters side by side and a try at each by every worker in the
+// end, 10k cells took 600 to 800 us of which the cells were 250, and a pass
+// over a single large cell took 280 us.
+constexpr uint32_t kNoCell = 0xFFFFFFFFu;
+template <uint32_t kPerBlock>  // workers per workgroup
+struct Work {
+    uint32_t count;  // cells of the pass
+    uint32_t stage;  // 0: first cell, 1: own range, 2: the others
+
+    __device__ __forceinline__ explicit Work(uint32_t n) : count(n), stage(0) {}
+    __device__ __forceinline__ uint32_t start(uint32_t q) const { return (uint32_t)((uint64_t)count * q / kWorkRanges); }
+    // cells of range q, and those given out by number
+    __device__ __forceinline__ uint32_t cells(uint32_t q) const { return start(q + 1) - start(q); }
+    __device__ __forceinline__ uint32_t workers(uint32_t q) const {
+        return (gridDim.x + kWorkRanges - 1 - q) / kWorkRanges * kPerBlock;
+    }
+    // The next cell, or kNoCell; called by one whole wave, the worker-th of
+    // its workgroup.  The counter of range q is at work_counter[q * kCounterStride].
+    __device__ __forceinline__ uint32_t next(uint32_t worker) {
+        const uint32_t range = blockIdx.x % kWorkRanges;
+        uint32_t ln = lane_id();
+        asm volatile("" : "+v"(ln));  // nothing of this is kept through the cells
+        if (stage == 0) {
+            stage = 1;
+            const uint32_t number = blockIdx.x / kWorkRanges * kPerBlock + worker;
+            if (number < cells(range)) return start(range) + number;
+        }
+        uint32_t* const counter = cold_args()->work_counter;
+        if (stage == 1) {
+            const uint32_t given = workers(range), all = cells(range);
+            if (given < all) {
+                uint32_t c = 0;
+                if (ln == 0) c = atomicAdd(&counter[range * kCounterStride], 1u);
+                c = uni(c) + given;
+                if (c < all) return start(range) + c;
+            }
+            stage = 2;
+        }
+        for (;;) {
+            // lane q: are there cells left in range q?  Counters only grow, so
+            // a failed claim is not repeated and the loop ends.
+            const uint32_t q = ln % kWorkRanges, given = workers(q), all = cells(q);
+            bool left = given < all;
+            if (ballot(left) == 0) return kNoCell;
+            if (left)
+                left = __hip_atomic_load(&counter[q * kCounterStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                       all - given;
+            const uint32_t m = (uint32_t)ballot(left) & 0xFFu;
+            if (m == 0) return kNoCell;
+            const uint32_t turned = ((m | (m << 8)) >> range) & 0xFFu;  // the next range after the own one first
+            const uint32_t pick = (range + (uint32_t)__builtin_ctz(turned)) % kWorkRanges;
+            uint32_t c = 0;
+            if (ln == 0) c = atomicAdd(&counter[pick * kCounterStride], 1u);
+            c = uni(c) + workers(pick);
+            if (c < cells(pick)) return start(pick) + c;
+        }
+    }
+};
+
 // queue capacity of the pass of vertex capacity cap
 constexpr int queue_cap(int cap) { return cap < kQueue0 ? kQueue0 : cap; }
 
