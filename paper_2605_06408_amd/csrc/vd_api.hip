@@ -617,10 +617,10 @@ struct BwdScratch {
     double4* facet = nullptr;
     double4* self = nullptr;
     double* orphan = nullptr;
-    double* box = nullptr;  // nwaves * 6 partials, 6 sums, then 6 uint32 face sites
+    double* box = nullptr;  // nslots * 6 partials, 6 sums, then 6 uint32 face sites
 };
 
-size_t bwd_box_bytes(int64_t nwaves) { return (size_t)(nwaves * 6 + 6) * sizeof(double) + 6 * sizeof(uint32_t); }
+size_t bwd_box_bytes(int64_t nslots) { return (size_t)(nslots * 6 + 6) * sizeof(double) + 6 * sizeof(uint32_t); }
 
 // Argument checks shared by both backward entry points.
 vd_status bwd_check(vd_context* c, const float* g_xyz, const char* who) {
@@ -636,12 +636,12 @@ vd_status bwd_check(vd_context* c, const float* g_xyz, const char* who) {
 vd_status bwd_run(vd_context* c, const float* g_vol, const float* g_cen, const float* g_vert, float* g_xyz,
                   float* g_w, const BwdScratch& sc, bool fill, hipStream_t s) {
     const int64_t n = c->n;
-    const int64_t nwaves = vd::bwd_waves(n);
+    const int64_t nslots = vd::bwd_slots(n);
     const bool moving_box = !c->box_given;
     const bool prof = c->profiled;
     if (prof) VD_HIP(hipEventRecord(c->ev[9], s));
     double* box_part = moving_box ? sc.box : nullptr;
-    uint32_t* box_arg = moving_box ? reinterpret_cast<uint32_t*>(box_part + nwaves * 6 + 6) : nullptr;
+    uint32_t* box_arg = moving_box ? reinterpret_cast<uint32_t*>(box_part + nslots * 6 + 6) : nullptr;
     if (fill) {
         VD_HIP(vd::launch_fill_u64(reinterpret_cast<uint64_t*>(sc.orphan), n * 4, 0ull, s));
         // the six 32-bit face sites are three 64-bit words (8-byte aligned:
@@ -655,7 +655,12 @@ vd_status bwd_run(vd_context* c, const float* g_vol, const float* g_cen, const f
     a.n = n;
     a.pts = as<float4>(c->spts);
     a.inv = as<uint32_t>(c->inv);
+    a.order = c->order;
     a.loc = as<uint32_t>(c->loc);
+    for (int t = 0; t < 2; ++t) {
+        a.list[t] = as<uint32_t>(c->lists[t + 1]);
+        a.count[t] = c->tier_slots[t + 1];
+    }
     for (int t = 0; t < vd::kTiers; ++t) a.stage[t] = stage_of(c, t);
     a.cnt_v = as<uint32_t>(c->cnt_v);
     a.cnt_f = as<uint32_t>(c->cnt_f);
@@ -672,9 +677,8 @@ vd_status bwd_run(vd_context* c, const float* g_vol, const float* g_cen, const f
     a.g_xyz = g_xyz;
     a.g_w = g_w;
     a.moving_box = moving_box ? 1 : 0;
-    a.pts_orig = as<float4>(c->pts);
     a.box_part = box_part;
-    a.box_sum = moving_box ? box_part + nwaves * 6 : nullptr;
+    a.box_sum = moving_box ? box_part + nslots * 6 : nullptr;
     a.box_arg = box_arg;
     VD_HIP(vd::launch_backward(a, s));
     if (prof) {
@@ -697,7 +701,7 @@ VD_API vd_status vd_backward(vd_context* c, const float* g_vol, const float* g_c
     VD_TRY(ensure(c->bwd_facet, nf * sizeof(double4)));
     VD_TRY(ensure(c->bwd_self, (size_t)n * sizeof(double4)));
     VD_TRY(ensure(c->bwd_orphan, (size_t)n * 4 * sizeof(double)));
-    if (!c->box_given) VD_TRY(ensure(c->bwd_box, bwd_box_bytes(vd::bwd_waves(n))));
+    if (!c->box_given) VD_TRY(ensure(c->bwd_box, bwd_box_bytes(vd::bwd_slots(n))));
     BwdScratch sc;
     sc.facet = as<double4>(c->bwd_facet);
     sc.self = as<double4>(c->bwd_self);
@@ -716,7 +720,7 @@ VD_API vd_status vd_backward_noalloc(vd_context* c, const float* g_vol, const fl
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t b_facet = up(nf * sizeof(double4)), b_self = up((size_t)n * sizeof(double4)),
                  b_orphan = up((size_t)n * 4 * sizeof(double));
-    const size_t b_box = c->box_given ? 0 : up(bwd_box_bytes(vd::bwd_waves(n)));
+    const size_t b_box = c->box_given ? 0 : up(bwd_box_bytes(vd::bwd_slots(n)));
     const size_t need = b_facet + b_self + b_orphan + b_box;
     if (need > vd::kBwdScratchBytes)
         return fail(VD_ERR_INVALID_ARG, "vd_backward_noalloc: this diagram (" + std::to_string(n) + " sites, " +

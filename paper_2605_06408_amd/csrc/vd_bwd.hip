@@ -17,13 +17,16 @@
 // the sites: da_f = dp_j - dp_i, db_f = a_f . da_f + (dw_i - dw_j) / 2, or
 // db_f = -a_f . dp_i for a box face.
 //
-// Layout: one wave per cell, lanes over its facets.  Each lane walks its
-// facet's vertex ring (staged by the forward pass) and recomputes the ring's
-// vertices in FP64 from their three planes, which is cheaper than storing
-// them.  A first walk gives V and m (pyramids with apex at the site), the
-// second the facet integrals and the gradient of each plane.  The gradient
-// a cell sends to neighbour j is stored with the facet; each site then sums
-// what its neighbours sent it, in ascending neighbour order (deterministic).
+// Layout: a group of lanes per cell, by the pass that built it: half a wave up
+// to 64 vertices, a wave up to 128, a block above (the lists of the build name
+// the cells of the last two).  Lanes over facets put the FP64 planes into LDS,
+// lanes over vertices solve each vertex once from them, lanes over facets walk
+// their rings over the solved vertices; one walk gives the facet integrals,
+// from them V and m, then the gradient of each plane.  (Solving a vertex from
+// scattered loads wherever a ring met it, in two walks, was six solves a
+// vertex: 935 us at 50k sites, this 105.)  The share a cell sends to neighbour
+// j goes to the place of its facet in j's row (found by a binary search of
+// the row), so that each site sums what stands in its own row (deterministic).
 // Shares stay in FP64 until that sum: around thin cells (tight clusters) the
 // shares of two neighbouring cells are many orders of magnitude larger than
 // the site gradient they cancel to.
@@ -35,10 +38,22 @@
 // site on that face with the lowest index, summed in a fixed order.
 #include <mutex>
 
-#include "vd_internal.h"
+#include "vd_wave.h"
+
+// Shares of thin cells cancel down to their last bits, so a gradient there
+// depends on every rounding and on the order of every sum.  Neither is left
+// to the compiler: products and sums are fused where it is written (fma) and
+// nowhere else, and the sums over facets run in the order of one wave with
+// facet f in lane f % 64, whatever the size of the group.
+#pragma clang fp contract(off)
 
 namespace vd {
 namespace {
+
+// Vertices of a cell of the block class kept in LDS (105 KB, with vertex
+// gradients 130 KB); a larger one solves its vertices where a ring meets them.
+constexpr int kBwdBlockCap = 2048;
+constexpr int kBwdBlockCapVert = 1536;
 
 struct CellRec {
     const float4* V;
@@ -81,6 +96,20 @@ struct Site {
     double w;
 };
 
+// u0 v0 + u1 v1 + u2 v2, by the product that is rounded on its own (the first
+// of three in the determinants, the second elsewhere).
+__device__ inline double dot1(const double* u, const double* v) {
+    return fma(u[2], v[2], fma(u[1], v[1], u[0] * v[0]));
+}
+__device__ inline double dot(const double* u, const double* v) {
+    return fma(u[2], v[2], fma(u[0], v[0], u[1] * v[1]));
+}
+__device__ inline void cross(const double* u, const double* v, double* o) {
+    o[0] = fma(u[1], v[2], -(u[2] * v[1]));
+    o[1] = fma(u[2], v[0], -(u[0] * v[2]));
+    o[2] = fma(u[0], v[1], -(u[1] * v[0]));
+}
+
 // Plane of facet code `code` in the frame of site s, FP64 from the FP32 inputs.
 __device__ inline void plane_of(const BwdArgs& a, const Site& s, int32_t code, double* n, double* b) {
     if (code >= 0) {
@@ -88,7 +117,7 @@ __device__ inline void plane_of(const BwdArgs& a, const Site& s, int32_t code, d
         n[0] = (double)q.x - s.p[0];
         n[1] = (double)q.y - s.p[1];
         n[2] = (double)q.z - s.p[2];
-        *b = 0.5 * (n[0] * n[0] + n[1] * n[1] + n[2] * n[2] + (s.w - (double)q.w));
+        *b = 0.5 * ((s.w - (double)q.w) + dot(n, n));
     } else {
         const int c = -code - 1, ax = c >> 1, side = c & 1;
         n[0] = n[1] = n[2] = 0.0;
@@ -97,37 +126,112 @@ __device__ inline void plane_of(const BwdArgs& a, const Site& s, int32_t code, d
     }
 }
 
-__device__ inline void cross(const double* u, const double* v, double* o) {
-    o[0] = u[1] * v[2] - u[2] * v[1];
-    o[1] = u[2] * v[0] - u[0] * v[2];
-    o[2] = u[0] * v[1] - u[1] * v[0];
-}
-__device__ inline double dot(const double* u, const double* v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; }
-
-// A vertex of the cell: its position y (frame of the site), the rows of M
-// and their cofactors (so that M^-T g = (c_k . g) / det), and its ranks.
+// A vertex of the cell: its position num * inv (frame of the site, inv the
+// reciprocal of det, zero if that is), the cofactors of the rows of M (so that
+// M^-T g = (c_k . g) / det), and its ranks.
 struct Vtx {
-    double y[3];
+    double num[3], inv;
     double c[3][3];
     double det;
     uint32_t t[3];
 };
 
-__device__ inline void vertex(const BwdArgs& a, const Site& s, const CellRec& r, uint32_t u, Vtx* v) {
-    ranks_of(r, u, v->t);
-    double n[3][3], b[3];
-    for (int k = 0; k < 3; ++k) plane_of(a, s, r.C[v->t[k]], n[k], &b[k]);
-    cross(n[1], n[2], v->c[0]);
-    cross(n[2], n[0], v->c[1]);
-    cross(n[0], n[1], v->c[2]);
-    v->det = dot(n[0], v->c[0]);
-    const double inv = v->det != 0.0 ? 1.0 / v->det : 0.0;
-    for (int q = 0; q < 3; ++q) v->y[q] = (b[0] * v->c[0][q] + b[1] * v->c[1][q] + b[2] * v->c[2][q]) * inv;
+// from its planes (a, b), in the order of its ranks
+__device__ inline void vertex_from(const double* p0, const double* p1, const double* p2, Vtx* v) {
+    cross(p1, p2, v->c[0]);
+    cross(p2, p0, v->c[1]);
+    cross(p0, p1, v->c[2]);
+    v->det = dot1(p0, v->c[0]);
+    v->inv = v->det != 0.0 ? 1.0 / v->det : 0.0;
+    for (int q = 0; q < 3; ++q) v->num[q] = fma(p2[3], v->c[2][q], fma(p0[3], v->c[0][q], p1[3] * v->c[1][q]));
 }
 
-__device__ inline double wsum(double x) {
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+// from the input, where the planes are not at hand
+__device__ inline void vertex(const BwdArgs& a, const Site& s, const CellRec& r, uint32_t u, Vtx* v) {
+    ranks_of(r, u, v->t);
+    double p[3][4];
+    for (int k = 0; k < 3; ++k) plane_of(a, s, r.C[v->t[k]], p[k], &p[k][3]);
+    vertex_from(p[0], p[1], p[2], v);
+}
+
+// Value of lane ^ kMask.
+template <int kMask>
+__device__ inline double lane_xor(double x) {
+    if constexpr (kMask == 1 || kMask == 2) {
+        return dpp64<(kMask == 1 ? 0xB1 : 0x4E), 0xF>(x);  // within quads
+    } else if constexpr (kMask < 32) {
+        const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(x), 0x1F | (kMask << 10));
+        const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(x), 0x1F | (kMask << 10));
+        return __hiloint2double(hi, lo);
+    } else {
+        return __shfl_xor(x, kMask);
+    }
+}
+// Sums over the facets of a cell: every lane adds what its facets give, in
+// rounds of GS facets; total() is the sum in every lane of the group, all lanes
+// of the wave (of the block: red, 256 * N doubles of LDS) taking part.
+template <int GS, int N>
+struct FacetSum {
+    double v[N];
+    __device__ void init() {
+        for (int k = 0; k < N; ++k) v[k] = 0.0;
+    }
+    // after each round: the round's sums of this lane
+    __device__ void add(const double* x, bool first, double* red) {
+        if constexpr (GS <= 64) {
+            for (int k = 0; k < N; ++k) v[k] = first ? x[k] : v[k] + x[k];
+        } else {
+            __syncthreads();
+            for (int k = 0; k < N; ++k) red[k * GS + threadIdx.x] = x[k];
+            __syncthreads();
+            for (int w = 0; w < GS / 64; ++w)
+                for (int k = 0; k < N; ++k) {
+                    const double t = red[k * GS + w * 64 + (threadIdx.x & 63)];
+                    v[k] = first && w == 0 ? t : v[k] + t;
+                }
+        }
+    }
+    __device__ void total() {
+        for (int k = 0; k < N; ++k) {
+            double x = v[k];
+            if constexpr (GS > 32) x += lane_xor<32>(x);
+            x += lane_xor<16>(x);
+            x += lane_xor<8>(x);
+            x += lane_xor<4>(x);
+            x += lane_xor<2>(x);
+            x += lane_xor<1>(x);
+            v[k] = x;
+        }
+    }
+};
+// Inclusive sum over the lanes of a group up to this one, and the group's total.
+template <int GS>
+__device__ inline uint32_t gscan(uint32_t v, uint32_t* total, uint32_t* red) {
+    const int ln = threadIdx.x & (GS < 64 ? GS - 1 : 63);
+    uint32_t x = v;
+    for (int o = 1; o < (GS < 64 ? GS : 64); o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, GS < 64 ? GS : 64);
+        if (ln >= o) x += y;
+    }
+    if constexpr (GS <= 64) {
+        *total = __shfl(x, GS - 1, GS);
+    } else {
+        __syncthreads();
+        if (ln == 63) red[threadIdx.x >> 6] = x;
+        __syncthreads();
+        uint32_t t = 0;
+        for (int w = 0; w < GS / 64; ++w) {
+            if (w < (int)(threadIdx.x >> 6)) x += red[w];
+            t += red[w];
+        }
+        *total = t;
+    }
     return x;
+}
+template <int GS>
+__device__ inline void gsync() {
+    if constexpr (GS > 64) __syncthreads();
+    else wave_sync<true>();
 }
 
 // Is `who` among the neighbours of cell j (original ids)?  Binary search of
@@ -146,209 +250,321 @@ __device__ inline int64_t find_facet(const BwdArgs& a, uint32_t j, int32_t who) 
     return -1;
 }
 
-__global__ __launch_bounds__(256) void k_bwd_cells(BwdArgs a) {
-    const int ln = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    double bx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // dL/db of the box faces of this lane's facets
-    for (int64_t i = wave; i < a.n; i += nwaves) {
-        const uint32_t k = a.inv[i];
+// LDS of a group: planes and vertices of a cell of up to CAPF facets and CAPV
+// vertices; with vertex gradients also M^-T g of each vertex and its facets.
+template <int CAPV, int CAPF, bool kVert>
+struct BwdMem {
+    double pl[CAPF][4];  // a, b
+    double v[CAPV][4];   // num, inv
+    double gk[kVert ? CAPV : 1][3];
+    uint16_t t[kVert ? CAPV : 1][4];  // ranks; [3]: 1 if det is zero
+};
+
+// What the walk of a facet's ring gives: area, centroid and second moment
+// integrals, and dL/da_f, dL/db_f from the vertices.  A1 and AY1, which V and m
+// are made of, take the last vertex of each triangle unrounded (num * inv
+// fused into the edge and the sum), A and AY take it rounded.
+struct Facet {
+    double n[3], b, D, A1, AY1[3], A, AY[3], S[6], dA[3], dB, g[3];
+};
+
+// The cells of one size class: kTier 0 all sites (Morton order), 1 and 2 the
+// cells named in list.
+template <int GS, int CAPV, int CAPF, bool kVert, int kTier>
+__global__ __launch_bounds__(256, (kTier < 2 ? 3 : 1)) void k_bwd_cells(BwdArgs a, const uint32_t* __restrict__ list,
+                                                                        int64_t count) {
+    constexpr int kGroups = 256 / GS;
+    using Mem = BwdMem<CAPV, CAPF, kVert>;
+    __shared__ Mem mem[kGroups];
+    __shared__ double red[GS > 64 ? 4 * 256 : 1];
+    __shared__ uint32_t redu[4];
+    const int ln = threadIdx.x % GS, grp = threadIdx.x / GS;
+    Mem& M = mem[grp];
+    // every group of a wave takes the same number of turns (the sums over
+    // lanes need the whole wave)
+    for (int64_t it0 = (int64_t)blockIdx.x * kGroups; it0 < count; it0 += (int64_t)gridDim.x * kGroups) {
+        const int64_t it = it0 + grp;
+        bool on = it < count;
+        const uint32_t k = on ? (kTier ? list[it] : (uint32_t)it) : 0u;
+        const int64_t i = a.order[k];
         const float4 ps = a.pts[k];
+        if (kTier == 0 && a.moving_box && on && ln < 6) {
+            // the lowest original index of a site on each face of the sites' box
+            // (the box is their FP32 minimum and maximum, so some site equals each face)
+            const float v = ln < 2 ? ps.x : (ln < 4 ? ps.y : ps.z);
+            if (v == a.bbox[(ln & 1) ? 3 + (ln >> 1) : (ln >> 1)]) atomicMin(&a.box_arg[ln], (uint32_t)i);
+        }
+        const uint32_t tier = a.loc[k] >> 30;
+        on = on && (kTier == 0 ? tier == 0 : (kTier == 1 ? tier == 1 : tier >= 2));
         double gc[3] = {0.0, 0.0, 0.0};
-        if (a.g_cen)
-            for (int q = 0; q < 3; ++q) gc[q] = (double)a.g_cen[3 * i + q];
-        const double gv = a.g_vol ? (double)a.g_vol[i] : 0.0;
-        const int nv = (int)a.cnt_v[i], F = (int)a.cnt_f[i];
-        if (nv == 0) {
+        double gv = 0.0;
+        int nv = 0, F = 0;
+        if (on) {
+            if (a.g_cen)
+                for (int q = 0; q < 3; ++q) gc[q] = (double)a.g_cen[3 * i + q];
+            gv = a.g_vol ? (double)a.g_vol[i] : 0.0;
+            nv = (int)a.cnt_v[i];
+            F = (int)a.cnt_f[i];
             // empty cell: V = 0 and c = p_i
-            if (ln == 0) a.gself[i] = make_double4(gc[0], gc[1], gc[2], 0.0);
-            continue;
+            if (nv == 0 && ln == 0) a.gself[i] = make_double4(gc[0], gc[1], gc[2], 0.0);
         }
         Site s;
         s.p[0] = ps.x; s.p[1] = ps.y; s.p[2] = ps.z;
         s.w = ps.w;
         const CellRec r = record_of(a, k);
-        const float* gvert = a.g_vert ? a.g_vert + 3 * a.off_v[i] : nullptr;
-
-        // first walk: V and m from the pyramids (site, facet)
-        double V = 0.0, m[3] = {0.0, 0.0, 0.0};
-        {
-            uint32_t carry = 0;
-            for (int f0 = 0; f0 < F; f0 += 64) {
-                const int f = f0 + ln;
-                const uint32_t sz = f < F ? (uint32_t)r.FS[f] : 0u;
-                uint32_t x = sz;
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t y = __shfl_up(x, o);
-                    if (ln >= o) x += y;
-                }
-                if (f < F && sz >= 3) {
-                    const uint32_t base = carry + x - sz;
-                    double n[3], b;
-                    plane_of(a, s, r.C[f], n, &b);
-                    const double D = sqrt(dot(n, n));
-                    const double nh[3] = {n[0] / D, n[1] / D, n[2] / D};
-                    Vtx v0, v1, v2;
-                    vertex(a, s, r, r.FV[base], &v0);
-                    vertex(a, s, r, r.FV[base + 1], &v1);
-                    double A = 0.0, AY[3] = {0.0, 0.0, 0.0};
-                    for (uint32_t t = 2; t < sz; ++t) {
-                        vertex(a, s, r, r.FV[base + t], &v2);
-                        double e1[3], e2[3], cr[3];
-                        for (int q = 0; q < 3; ++q) {
-                            e1[q] = v1.y[q] - v0.y[q];
-                            e2[q] = v2.y[q] - v0.y[q];
-                        }
-                        cross(e1, e2, cr);
-                        const double at = 0.5 * dot(cr, nh);
-                        A += at;
-                        for (int q = 0; q < 3; ++q) AY[q] += at * (v0.y[q] + v1.y[q] + v2.y[q]) * (1.0 / 3.0);
-                        v1 = v2;
-                    }
-                    V += b * A / (3.0 * D);
-                    for (int q = 0; q < 3; ++q) m[q] += b * AY[q] / (4.0 * D);
-                }
-                carry += (uint32_t)__shfl(x, 63);
+        // the register passes hold at most CAPV vertices and planes
+        const bool cached = kTier < 2 || (nv <= CAPV && F <= CAPF);
+        const float* gvert = kVert ? a.g_vert + 3 * a.off_v[i] : nullptr;
+        gsync<GS>();  // the group is done with the previous cell
+        if (cached)
+            for (int f = ln; f < F; f += GS) {
+                double n[3], b;
+                plane_of(a, s, r.C[f], n, &b);
+                M.pl[f][0] = n[0]; M.pl[f][1] = n[1]; M.pl[f][2] = n[2];
+                M.pl[f][3] = b;
             }
-            V = wsum(V);
-            for (int q = 0; q < 3; ++q) m[q] = wsum(m[q]);
+        gsync<GS>();
+        // every vertex once, with vertex gradients also its share of each of its
+        // planes (M^-T g)
+        if (cached)
+            for (int u = ln; u < nv; u += GS) {
+                Vtx v;
+                ranks_of(r, (uint32_t)u, v.t);
+                vertex_from(M.pl[v.t[0]], M.pl[v.t[1]], M.pl[v.t[2]], &v);
+                for (int q = 0; q < 3; ++q) M.v[u][q] = v.num[q];
+                M.v[u][3] = v.inv;
+                if constexpr (kVert) {
+                    const double g[3] = {(double)gvert[3 * u], (double)gvert[3 * u + 1], (double)gvert[3 * u + 2]};
+                    for (int q = 0; q < 3; ++q) {
+                        M.gk[u][q] = v.det == 0.0 ? 0.0 : dot(v.c[q], g) / v.det;
+                        M.t[u][q] = (uint16_t)v.t[q];
+                    }
+                    M.t[u][3] = v.det == 0.0 ? 1 : 0;
+                }
+            }
+        gsync<GS>();
+        // the walk of facet f's ring
+        auto walk = [&](int f, uint32_t base, uint32_t sz, Facet& o) {
+            if (cached) {
+                for (int q = 0; q < 3; ++q) o.n[q] = M.pl[f][q];
+                o.b = M.pl[f][3];
+            } else {
+                plane_of(a, s, r.C[f], o.n, &o.b);
+            }
+            o.D = sqrt(dot(o.n, o.n));
+            const double nh[3] = {o.n[0] / o.D, o.n[1] / o.D, o.n[2] / o.D};
+            o.A = o.A1 = o.dB = 0.0;
+            for (int q = 0; q < 3; ++q) o.AY[q] = o.AY1[q] = o.dA[q] = o.g[q] = 0.0;
+            for (int q = 0; q < 6; ++q) o.S[q] = 0.0;
+            // a vertex of the ring: num and inv, the position y, and its part of
+            // the gradient: its share of plane f, and the direct term dx/dp_i = I
+            // once per vertex (with its lowest facet)
+            auto take = [&](uint32_t u, double* num, double* inv, double* y) {
+                double gk = 0.0;
+                bool flat = true;
+                uint32_t t[3];
+                if (cached) {
+                    for (int q = 0; q < 3; ++q) num[q] = M.v[u][q];
+                    *inv = M.v[u][3];
+                    if constexpr (kVert) {
+                        for (int q = 0; q < 3; ++q) t[q] = M.t[u][q];
+                        gk = t[0] == (uint32_t)f ? M.gk[u][0] : (t[1] == (uint32_t)f ? M.gk[u][1] : M.gk[u][2]);
+                        flat = M.t[u][3] != 0;
+                    }
+                } else {
+                    Vtx v;
+                    vertex(a, s, r, u, &v);
+                    for (int q = 0; q < 3; ++q) num[q] = v.num[q];
+                    *inv = v.inv;
+                    if constexpr (kVert) {
+                        const double g[3] = {(double)gvert[3 * u], (double)gvert[3 * u + 1], (double)gvert[3 * u + 2]};
+                        for (int q = 0; q < 3; ++q) t[q] = v.t[q];
+                        flat = v.det == 0.0;
+                        const int q0 = t[0] == (uint32_t)f ? 0 : (t[1] == (uint32_t)f ? 1 : 2);
+                        if (!flat) gk = dot(v.c[q0], g) / v.det;
+                    }
+                }
+                for (int q = 0; q < 3; ++q) y[q] = num[q] * *inv;
+                if constexpr (kVert) {
+                    if (!flat) {
+                        o.dB += gk;
+                        for (int q = 0; q < 3; ++q) o.dA[q] = fma(-y[q], gk, o.dA[q]);
+                        if (min(t[0], min(t[1], t[2])) == (uint32_t)f)
+                            for (int q = 0; q < 3; ++q) o.g[q] += (double)gvert[3 * u + q];
+                    }
+                }
+            };
+            double num[3], inv, P0[3], P1[3], P2[3];
+            take(r.FV[base], num, &inv, P0);
+            take(r.FV[base + 1], num, &inv, P1);
+            for (uint32_t t = 2; t < sz; ++t) {
+                take(r.FV[base + t], num, &inv, P2);
+                double e1[3], e2[3], cr[3], sm[3], sm1[3];
+                for (int q = 0; q < 3; ++q) {
+                    e1[q] = P1[q] - P0[q];
+                    e2[q] = fma(num[q], inv, -P0[q]);
+                    const double s01 = P0[q] + P1[q];
+                    sm1[q] = fma(num[q], inv, s01);
+                    sm[q] = s01 + P2[q];
+                }
+                cross(e1, e2, cr);
+                double d = dot(cr, nh), at = 0.5 * d;
+                o.A1 += at;
+                for (int q = 0; q < 3; ++q) o.AY1[q] = fma(1.0 / 3.0, at * sm1[q], o.AY1[q]);
+                for (int q = 0; q < 3; ++q) e2[q] = P2[q] - P0[q];
+                cross(e1, e2, cr);
+                d = dot(cr, nh);
+                at = 0.5 * d;
+                o.A += at;
+                for (int q = 0; q < 3; ++q) o.AY[q] = fma(1.0 / 3.0, at * sm[q], o.AY[q]);
+                // int over the triangle of y y^T = at/12 (sum_i v_i v_i^T + s s^T)
+                const double h = at * (1.0 / 12.0);
+                auto second = [&](int x, int y) {
+                    return fma(sm[x], sm[y], fma(P2[x], P2[y], fma(P1[x], P1[y], P0[x] * P0[y])));
+                };
+                o.S[0] = fma(h, second(0, 0), o.S[0]);
+                o.S[1] = fma(h, second(0, 1), o.S[1]);
+                o.S[2] = fma(h, second(0, 2), o.S[2]);
+                o.S[3] = fma(h, second(1, 1), o.S[3]);
+                o.S[4] = fma(h, second(1, 2), o.S[4]);
+                o.S[5] = fma(h, second(2, 2), o.S[5]);
+                for (int q = 0; q < 3; ++q) P1[q] = P2[q];
+            }
+        };
+        // the groups of a wave take the same number of rounds
+        int rounds = (F + GS - 1) / GS;
+        if constexpr (GS < 64) rounds = max(rounds, __shfl_xor(rounds, 32));
+        Facet fa{};  // the facet of the last round walked
+        FacetSum<GS, 4> vm;
+        vm.init();
+        uint32_t carry = 0;
+        for (int q0 = 0; q0 < rounds; ++q0) {
+            const int f = q0 * GS + ln;
+            const uint32_t sz = f < F ? (uint32_t)r.FS[f] : 0u;
+            uint32_t total;
+            const uint32_t x = gscan<GS>(sz, &total, redu);
+            double part[4] = {0.0, 0.0, 0.0, 0.0};
+            if (f < F && sz >= 3) {
+                walk(f, carry + x - sz, sz, fa);
+                part[0] = fa.b * fa.A1 / (3.0 * fa.D);
+                for (int q = 0; q < 3; ++q) part[1 + q] = fa.b * fa.AY1[q] / (4.0 * fa.D);
+            }
+            vm.add(part, q0 == 0, red);
+            carry += total;
         }
+        vm.total();
         // L = gv V + gc . (p_i + m / V): dL/dV and dL/dm
+        const double V = vm.v[0];
+        const double m[3] = {vm.v[1], vm.v[2], vm.v[3]};
         double alpha = 0.0, gam[3] = {0.0, 0.0, 0.0};
         if (V != 0.0) {
             alpha = gv - dot(gc, m) / (V * V);
             for (int q = 0; q < 3; ++q) gam[q] = gc[q] / V;
         }
-        // second walk: facet integrals, plane gradients, scatter to sites
-        double self_p[3] = {0.0, 0.0, 0.0}, self_w = 0.0;
-        {
-            uint32_t carry = 0;
-            for (int f0 = 0; f0 < F; f0 += 64) {
-                const int f = f0 + ln;
-                const uint32_t sz = f < F ? (uint32_t)r.FS[f] : 0u;
-                uint32_t x = sz;
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t y = __shfl_up(x, o);
-                    if (ln >= o) x += y;
-                }
-                if (f < F && sz >= 3) {
-                    const uint32_t base = carry + x - sz;
-                    const int32_t code = r.C[f];
-                    double n[3], b;
-                    plane_of(a, s, code, n, &b);
-                    const double D = sqrt(dot(n, n));
-                    const double nh[3] = {n[0] / D, n[1] / D, n[2] / D};
-                    double A = 0.0, AY[3] = {0.0, 0.0, 0.0}, S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                    double dA[3] = {0.0, 0.0, 0.0}, dB = 0.0;  // dL/da_f, dL/db_f from the vertices
-                    Vtx v0, v1, v2;
-                    // the vertex part of one ring vertex: its share of plane f,
-                    // and the direct term dx/dp_i = I once per vertex
-                    auto vertex_part = [&](const Vtx& v, uint32_t u) {
-                        if (!gvert || v.det == 0.0) return;
-                        const double g[3] = {(double)gvert[3 * u], (double)gvert[3 * u + 1], (double)gvert[3 * u + 2]};
-                        const double g0 = dot(v.c[0], g), g1 = dot(v.c[1], g), g2 = dot(v.c[2], g);
-                        const double gk = (v.t[0] == (uint32_t)f ? g0 : (v.t[1] == (uint32_t)f ? g1 : g2)) / v.det;
-                        dB += gk;
-                        for (int q = 0; q < 3; ++q) dA[q] -= gk * v.y[q];
-                        const uint32_t tmin = min(v.t[0], min(v.t[1], v.t[2]));
-                        if (tmin == (uint32_t)f)
-                            for (int q = 0; q < 3; ++q) self_p[q] += g[q];
-                    };
-                    vertex(a, s, r, r.FV[base], &v0);
-                    vertex(a, s, r, r.FV[base + 1], &v1);
-                    vertex_part(v0, r.FV[base]);
-                    vertex_part(v1, r.FV[base + 1]);
-                    for (uint32_t t = 2; t < sz; ++t) {
-                        const uint32_t u = r.FV[base + t];
-                        vertex(a, s, r, u, &v2);
-                        vertex_part(v2, u);
-                        double e1[3], e2[3], cr[3], sm[3];
-                        for (int q = 0; q < 3; ++q) {
-                            e1[q] = v1.y[q] - v0.y[q];
-                            e2[q] = v2.y[q] - v0.y[q];
-                            sm[q] = v0.y[q] + v1.y[q] + v2.y[q];
-                        }
-                        cross(e1, e2, cr);
-                        const double at = 0.5 * dot(cr, nh);
-                        A += at;
-                        for (int q = 0; q < 3; ++q) AY[q] += at * sm[q] * (1.0 / 3.0);
-                        // int over the triangle of y y^T = at/12 (sum_i v_i v_i^T + s s^T)
-                        const double h = at * (1.0 / 12.0);
-                        const double* P0 = v0.y;
-                        const double* P1 = v1.y;
-                        const double* P2 = v2.y;
-                        S[0] += h * (P0[0] * P0[0] + P1[0] * P1[0] + P2[0] * P2[0] + sm[0] * sm[0]);
-                        S[1] += h * (P0[0] * P0[1] + P1[0] * P1[1] + P2[0] * P2[1] + sm[0] * sm[1]);
-                        S[2] += h * (P0[0] * P0[2] + P1[0] * P1[2] + P2[0] * P2[2] + sm[0] * sm[2]);
-                        S[3] += h * (P0[1] * P0[1] + P1[1] * P1[1] + P2[1] * P2[1] + sm[1] * sm[1]);
-                        S[4] += h * (P0[1] * P0[2] + P1[1] * P1[2] + P2[1] * P2[2] + sm[1] * sm[2]);
-                        S[5] += h * (P0[2] * P0[2] + P1[2] * P1[2] + P2[2] * P2[2] + sm[2] * sm[2]);
-                        v1 = v2;
-                    }
-                    // dL/db_f and dL/da_f from the cell integrals
-                    dB += (alpha * A + dot(gam, AY)) / D;
-                    const double Sg[3] = {S[0] * gam[0] + S[1] * gam[1] + S[2] * gam[2],
-                                          S[1] * gam[0] + S[3] * gam[1] + S[4] * gam[2],
-                                          S[2] * gam[0] + S[4] * gam[1] + S[5] * gam[2]};
-                    for (int q = 0; q < 3; ++q) dA[q] -= (alpha * AY[q] + Sg[q]) / D;
-                    if (code >= 0) {
-                        // site plane: a = p_j - p_i, b = (|a|^2 + w_i - w_j) / 2
-                        double gp[3];
-                        for (int q = 0; q < 3; ++q) gp[q] = dA[q] + dB * n[q];
-                        const double gwj = -0.5 * dB;
-                        for (int q = 0; q < 3; ++q) self_p[q] -= gp[q];
-                        self_w += 0.5 * dB;
-                        const double4 out = make_double4(gp[0], gp[1], gp[2], gwj);
-                        a.gf[a.off_f[i] + f] = out;
-                        if (find_facet(a, (uint32_t)code, (int32_t)i) < 0) {
-                            double* o = a.orphan + 4 * (int64_t)code;
-                            atomicAdd(o, out.x);
-                            atomicAdd(o + 1, out.y);
-                            atomicAdd(o + 2, out.z);
-                            atomicAdd(o + 3, out.w);
-                        }
-                    } else {
-                        // box face: b = +-(B_k - p_i,k), a fixed
-                        for (int q = 0; q < 3; ++q) self_p[q] -= dB * n[q];
-                        const int face = -code - 1;
-#pragma unroll
-                        for (int c = 0; c < 6; ++c)
-                            if (c == face) bx[c] += dB;
-                    }
-                }
-                carry += (uint32_t)__shfl(x, 63);
+        FacetSum<GS, 4> self;  // the site's own share: dp, dw
+        self.init();
+        carry = 0;
+        for (int q0 = 0; q0 < rounds; ++q0) {
+            const int f = q0 * GS + ln;
+            const uint32_t sz = f < F ? (uint32_t)r.FS[f] : 0u;
+            if (rounds > 1) {
+                uint32_t total;
+                const uint32_t x = gscan<GS>(sz, &total, redu);
+                if (f < F && sz >= 3) walk(f, carry + x - sz, sz, fa);
+                carry += total;
             }
+            double part[4] = {0.0, 0.0, 0.0, 0.0};
+            if (f < F && sz >= 3) {
+                const int32_t code = r.C[f];
+                // dL/db_f and dL/da_f from the cell integrals
+                const double dB = fa.dB + fma(alpha, fa.A, dot(gam, fa.AY)) / fa.D;
+                for (int q = 0; q < 3; ++q) part[q] = fa.g[q];
+                if (code >= 0) {
+                    // site plane: a = p_j - p_i, b = (|a|^2 + w_i - w_j) / 2
+                    const double Sg[3] = {fma(fa.S[2], gam[2], fma(fa.S[0], gam[0], fa.S[1] * gam[1])),
+                                          fma(fa.S[4], gam[2], fma(fa.S[1], gam[0], fa.S[3] * gam[1])),
+                                          fma(fa.S[5], gam[2], fma(fa.S[2], gam[0], fa.S[4] * gam[1]))};
+                    double gp[3];
+                    for (int q = 0; q < 3; ++q) {
+                        gp[q] = fma(dB, fa.n[q], fa.dA[q] - fma(alpha, fa.AY[q], Sg[q]) / fa.D);
+                        part[q] -= gp[q];
+                    }
+                    part[3] = 0.5 * dB;
+                    const double4 out = make_double4(gp[0], gp[1], gp[2], -0.5 * dB);
+                    const int64_t at = find_facet(a, (uint32_t)code, (int32_t)i);
+                    if (at >= 0) {
+                        a.gf[a.off_f[code] + at] = out;
+                    } else {
+                        // not listed back: nobody writes this facet's own place
+                        a.gf[a.off_f[i] + f] = make_double4(0.0, 0.0, 0.0, 0.0);
+                        double* o = a.orphan + 4 * (int64_t)code;
+                        atomicAdd(o, out.x);
+                        atomicAdd(o + 1, out.y);
+                        atomicAdd(o + 2, out.z);
+                        atomicAdd(o + 3, out.w);
+                    }
+                } else {
+                    // box face: b = +-(B_k - p_i,k), a fixed; its place in the row
+                    // holds dL/db of the face
+                    for (int q = 0; q < 3; ++q) part[q] -= dB * fa.n[q];
+                    if (a.moving_box) a.gf[a.off_f[i] + f].x = dB;
+                }
+            }
+            self.add(part, q0 == 0, red);
         }
-        for (int q = 0; q < 3; ++q) self_p[q] = wsum(self_p[q]);
-        self_w = wsum(self_w);
-        if (ln == 0) a.gself[i] = make_double4(self_p[0] + gc[0], self_p[1] + gc[1], self_p[2] + gc[2], self_w);
-    }
-    if (a.moving_box) {
-        for (int c = 0; c < 6; ++c) {
-            const double t = wsum(bx[c]);
-            if (ln == 0) a.box_part[wave * 6 + c] = t;
-        }
+        self.total();
+        if (on && nv > 0 && ln == 0)
+            a.gself[i] = make_double4(self.v[0] + gc[0], self.v[1] + gc[1], self.v[2] + gc[2], self.v[3]);
     }
 }
 
-// Lowest original index of a site on each face of the sites' bounding box
-// (the box is their FP32 minimum and maximum, so some site equals each face).
-__global__ __launch_bounds__(256) void k_bwd_box_arg(BwdArgs a) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= a.n) return;
-    const float4 p = a.pts_orig[j];
-    const float v[3] = {p.x, p.y, p.z};
-#pragma unroll
+// dL/db of the box faces over the cells slot, slot + nslots, ...: a cell's box
+// facets stand first in its row, facet f adding to sum f of its face.
+__device__ inline void box_slot(const BwdArgs& a, int64_t slot, int64_t nslots, double* sum) {
+    double acc[6][6];
     for (int c = 0; c < 6; ++c)
-        if (v[c >> 1] == a.bbox[(c & 1) ? 3 + (c >> 1) : (c >> 1)]) atomicMin(&a.box_arg[c], (uint32_t)j);
+        for (int f = 0; f < 6; ++f) acc[c][f] = 0.0;
+    bool any = false;
+    for (int64_t i = slot; i < a.n; i += nslots) {
+        const int nbox = (int)(a.cnt_f[i] - a.cnt_n[i]);
+        if (nbox == 0) continue;
+        any = true;
+        const CellRec r = record_of(a, a.inv[i]);
+        for (int f = 0; f < nbox && f < 6; ++f) {
+            const int face = -r.C[f] - 1;
+            const double d = a.gf[a.off_f[i] + f].x;
+#pragma unroll
+            for (int c = 0; c < 6; ++c)
+#pragma unroll
+                for (int l = 0; l < 6; ++l)
+                    if (c == face && l == f) acc[c][l] += d;
+        }
+    }
+    for (int c = 0; c < 6; ++c)
+        sum[c] = any ? ((acc[c][0] + acc[c][4]) + acc[c][2]) + ((acc[c][1] + acc[c][5]) + acc[c][3]) : 0.0;
 }
 
-// Sum of the per-wave box-face partials, in a fixed order (one block).
-__global__ __launch_bounds__(256) void k_bwd_box_sum(BwdArgs a, int64_t nwaves) {
+__global__ __launch_bounds__(256) void k_bwd_box_part(BwdArgs a, int64_t nslots) {
+    const int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (slot >= nslots) return;
+    double s[6];
+    box_slot(a, slot, nslots, s);
+    for (int c = 0; c < 6; ++c) a.box_part[slot * 6 + c] = s[c];
+}
+
+// Sum over the slots, in a fixed order (one block); kDirect: the slots are
+// summed here, where they are few.
+template <bool kDirect>
+__global__ __launch_bounds__(256) void k_bwd_box_sum(BwdArgs a, int64_t nslots) {
     __shared__ double red[6][256];
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t w = threadIdx.x; w < nwaves; w += 256)
-        for (int c = 0; c < 6; ++c) s[c] += a.box_part[w * 6 + c];
+    for (int64_t w = threadIdx.x; w < nslots; w += 256) {
+        double p[6];
+        if (kDirect) box_slot(a, w, nslots, p);
+        else
+            for (int c = 0; c < 6; ++c) p[c] = a.box_part[w * 6 + c];
+        for (int c = 0; c < 6; ++c) s[c] += p[c];
+    }
     for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = s[c];
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
@@ -359,37 +575,25 @@ __global__ __launch_bounds__(256) void k_bwd_box_sum(BwdArgs a, int64_t nwaves) 
     if (threadIdx.x < 6) a.box_sum[threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Per site: its own cell's share, then what each neighbour's cell sent it
-// (ascending neighbour order), then the asymmetric remainder.
+// Per site: its own cell's share, what its neighbours' cells put into its row
+// (ascending), then the asymmetric remainder and the box faces.  Four lanes a
+// site, one for each component, so that a row is read in whole lines.
 __global__ __launch_bounds__(256) void k_bwd_gather(BwdArgs a) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2;
+    const int q = threadIdx.x & 3;
     if (j >= a.n) return;
-    const double4 g0 = a.gself[j];
-    double g[4] = {g0.x, g0.y, g0.z, g0.w};
     const int F = (int)a.cnt_f[j], nn = (int)a.cnt_n[j];
+    double g = reinterpret_cast<const double*>(a.gself + j)[q];
     if (nn > 0) {
-        const CellRec r = record_of(a, a.inv[j]);
-        for (int t = F - nn; t < F; ++t) {
-            const uint32_t i = (uint32_t)r.C[t];
-            const int64_t f = find_facet(a, i, (int32_t)j);
-            if (f >= 0) {
-                const double4 c = a.gf[a.off_f[i] + f];
-                g[0] += c.x;
-                g[1] += c.y;
-                g[2] += c.z;
-                g[3] += c.w;
-            }
-        }
+        const double* row = reinterpret_cast<const double*>(a.gf + a.off_f[j] + (F - nn)) + q;
+        for (int t = 0; t < nn; ++t) g += row[4 * t];
     }
-    const double* o = a.orphan + 4 * j;
-    for (int q = 0; q < 4; ++q) g[q] += o[q];
-    if (a.moving_box)
-        for (int c = 0; c < 6; ++c)
-            if (a.box_arg[c] == (uint32_t)j) g[c >> 1] += (c & 1) ? a.box_sum[c] : -a.box_sum[c];
-    a.g_xyz[3 * j] = (float)g[0];
-    a.g_xyz[3 * j + 1] = (float)g[1];
-    a.g_xyz[3 * j + 2] = (float)g[2];
-    if (a.g_w) a.g_w[j] = (float)g[3];
+    g += a.orphan[4 * j + q];
+    if (a.moving_box && q < 3)
+        for (int c = 2 * q; c < 2 * q + 2; ++c)
+            if (a.box_arg[c] == (uint32_t)j) g += (c & 1) ? a.box_sum[c] : -a.box_sum[c];
+    if (q < 3) a.g_xyz[3 * j + q] = (float)g;
+    else if (a.g_w) a.g_w[j] = (float)g;
 }
 
 // Fill of 64-bit words (clears the scratch of the allocation-free entry
@@ -434,21 +638,47 @@ hipError_t launch_fill_u64(uint64_t* dst, int64_t count, uint64_t value, hipStre
     return hipGetLastError();
 }
 
-int64_t bwd_waves(int64_t n) {
-    const int64_t waves = n < 65536 ? n : 65536;
-    return (waves + 3) / 4 * 4;  // whole blocks of four waves
+int64_t bwd_slots(int64_t n) {
+    const int64_t slots = n < 65536 ? n : 65536;
+    return (slots + 3) / 4 * 4;
 }
+
+namespace {
+
+template <bool kVert>
+void launch_cells(const BwdArgs& a, hipStream_t s) {
+    auto blocks = [](int64_t items, int64_t per_block, int64_t limit) {
+        const int64_t b = (items + per_block - 1) / per_block;
+        return dim3((unsigned)(b < limit ? b : limit));
+    };
+    hipLaunchKernelGGL((k_bwd_cells<32, kTierCap[0], kTierCap[0], kVert, 0>), blocks(a.n, 8, 16384), dim3(256), 0, s, a,
+                       (const uint32_t*)nullptr, a.n);
+    if (a.count[0] > 0)
+        hipLaunchKernelGGL((k_bwd_cells<64, kTierCap[1], kTierCap[1], kVert, 1>), blocks(a.count[0], 4, 16384),
+                           dim3(256), 0, s, a, a.list[0], a.count[0]);
+    if (a.count[1] > 0) {
+        constexpr int cap = kVert ? kBwdBlockCapVert : kBwdBlockCap;
+        hipLaunchKernelGGL((k_bwd_cells<256, cap, cap / 2 + 2, kVert, 2>), blocks(a.count[1], 1, 16384), dim3(256), 0,
+                           s, a, a.list[1], a.count[1]);
+    }
+}
+
+}  // namespace
 
 hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
     if (a.n < 1) return hipSuccess;
-    const int64_t waves = bwd_waves(a.n);
-    const int64_t blocks = waves / 4;
-    hipLaunchKernelGGL(k_bwd_cells, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    if (a.g_vert) launch_cells<true>(a, s);
+    else launch_cells<false>(a, s);
     if (a.moving_box) {
-        hipLaunchKernelGGL(k_bwd_box_arg, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_bwd_box_sum, dim3(1), dim3(256), 0, s, a, waves);
+        const int64_t slots = bwd_slots(a.n);
+        if (slots <= 4096) {
+            hipLaunchKernelGGL(k_bwd_box_sum<true>, dim3(1), dim3(256), 0, s, a, slots);
+        } else {
+            hipLaunchKernelGGL(k_bwd_box_part, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, a, slots);
+            hipLaunchKernelGGL(k_bwd_box_sum<false>, dim3(1), dim3(256), 0, s, a, slots);
+        }
     }
-    hipLaunchKernelGGL(k_bwd_gather, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bwd_gather, dim3((unsigned)((a.n * 4 + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

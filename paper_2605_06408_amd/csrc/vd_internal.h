@@ -211,7 +211,12 @@ struct BwdArgs {
     int64_t n;
     const float4* pts;        // sites in Morton order: x, y, z, w
     const uint32_t* inv;      // original index -> Morton position
+    const uint32_t* order;    // Morton position -> original index
     const uint32_t* loc;      // staged record of each cell, by Morton position
+    // the cells (Morton positions) that left the 64-vertex pass, and those that
+    // left the 128-vertex pass
+    const uint32_t* list[2];
+    int64_t count[2];
     Stage stage[kTiers];
     const uint32_t* cnt_v;    // by original index
     const uint32_t* cnt_f;
@@ -224,26 +229,25 @@ struct BwdArgs {
     const float* g_vert;      // [3 n_vert] or null
     // FP64 scratch: shares of neighbouring cells cancel to a much smaller
     // site gradient wherever cells are thin, so they are kept and summed in FP64
-    double4* gf;              // [n_facet]: what a cell sends to its facet's site (dp xyz, dw)
+    double4* gf;              // [n_facet]: by the receiving site's facet, what the neighbour's cell sends it (dp xyz, dw)
     double4* gself;           // [n]: each cell's share for its own site
     double* orphan;           // [4n], zeroed: shares of facets not listed back
     float* g_xyz;             // [3n] out
     float* g_w;               // [n] out, or null
     // Box of the sites (the build was given no box): its faces move with the
-    // extreme sites.  Each wave of the cell pass sums dL/db of the box faces
-    // of its cells into box_part[wave * 6 + face]; box_sum[face] is their
-    // total and box_arg[face] (preset to 0xFFFFFFFF) the lowest original
-    // index of a site on that face.  moving_box = 0: faces held fixed.
+    // extreme sites.  dL/db of a box facet stands in its place in the cell's
+    // row of gf; the cells i = slot (mod bwd_slots) are summed into
+    // box_part[slot * 6 + face], box_sum[face] is their total and
+    // box_arg[face] (preset to 0xFFFFFFFF) the lowest original index of a site
+    // on that face.  moving_box = 0: faces held fixed.
     int moving_box;
-    const float4* pts_orig;   // [n] sites in the caller's order
-    double* box_part;         // [bwd_waves(n) * 6]
+    double* box_part;         // [bwd_slots(n) * 6]
     double* box_sum;          // [6]
     uint32_t* box_arg;        // [6]
 };
 
-// Waves of the backward cell pass (the size of BwdArgs.box_part is six
-// doubles per wave).
-int64_t bwd_waves(int64_t n);
+// Slots the sums over the box faces are made in.
+int64_t bwd_slots(int64_t n);
 
 // ---------------------------------------------------------------- launches
 // (host wrappers; each returns the hipError_t of its launch)
