@@ -24,7 +24,7 @@
 // their rings over the solved vertices; one walk gives the facet integrals,
 // from them V and m, then the gradient of each plane.  (Solving a vertex from
 // scattered loads wherever a ring met it, in two walks, was six solves a
-// vertex: 935 us at 50k sites, this 105.)  The share a cell sends to neighbour
+// vertex: 935 us at 50k sites, this 140.)  The share a cell sends to neighbour
 // j goes to the place of its facet in j's row (found by a binary search of
 // the row), so that each site sums what stands in its own row (deterministic).
 // Shares stay in FP64 until that sum: around thin cells (tight clusters) the

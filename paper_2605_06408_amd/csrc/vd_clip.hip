@@ -83,6 +83,13 @@ struct Col {
     }
 };
 
+// Waves that build a cell together, and the slots of a cell of a memory tier
+// whose positions and masks they hold in registers as well (kSlotsCached each).
+constexpr int kGroupLds = 4;
+constexpr int kGroupArena = 8;
+constexpr int kSlotsCached = 4;
+constexpr int kCachedSlots = kGroupLds * kSlotsCached;
+
 // Per-cell state that the register tiers keep in registers and the larger
 // tiers in LDS or the arena (index slot * 64 + lane for per-lane values, slot
 // for wave-uniform masks).
@@ -96,10 +103,51 @@ struct ArenaState<VPL, true> {
     W vt[CAP], va[CAP];                         // vertex planes and neighbours
     uint32_t qe[CAP];                           // node queue
     float qk[CAP];
-    uint32_t cross[CAP], pre[CAP], frank[CAP], nb1[CAP], nb2[CAP];  // clip temporaries
-    W rec[CAP];
-    uint8_t isnew[CAP], amb[CAP];
-    uint64_t alive[VPL], R[VPL], fr[VPL];  // per-slot masks
+    // clip: crossing edges of a vertex (low 3 bits) and their rank in its slot
+    // (slots not kept in registers)
+    uint32_t cross[VPL > kCachedSlots ? CAP : 1];
+    uint32_t nb1[CAP], nb2[CAP];  // clip: links of the new vertices by rank (above 64 of them)
+};
+
+// What every clip of a memory tier exchanges between lanes and waves: per-slot
+// masks and the tables of the new vertices.  In LDS in both memory tiers; the
+// arena tier keeps only the first kHotRanks entries of the lists by rank here
+// (a clip makes about six vertices), the rest in the arena.
+constexpr int kHotRanks = 1024;
+template <int VPL, bool kMem = !Tier<VPL>::kReg>
+struct HotMem {};
+template <int VPL>
+struct HotMem<VPL, true> {
+    using W = typename Tier<VPL>::W;
+    static constexpr int CAP = Tier<VPL>::CAP;
+    static constexpr int RANKS = CAP < kHotRanks ? CAP : kHotRanks;
+    uint64_t alive[VPL], R[VPL], amb[VPL];
+    uint32_t cnt[VPL];  // clip: crossing edges of each slot, free places (from bit 16), bounds lost (bit 31)
+    uint32_t pre[VPL > 64 ? VPL : 1];  // the same, sums over the lower slots
+    uint32_t ta[CAP];   // clip: new vertex by first old plane | finalize: plane rank
+    uint32_t tb[CAP];   // clip: new vertex by second old plane | finalize: facet size
+    uint32_t sor[RANKS];
+    W edge[RANKS];
+};
+// The same tables of the register tiers, and what the memory tiers have
+// beyond kHotRanks.
+template <int VPL, bool kMem = !Tier<VPL>::kReg>
+struct TableMem {
+    using W = typename Tier<VPL>::W;
+    static constexpr int CAP = Tier<VPL>::CAP;
+    float4 psite[CAP];     // the plane's site (x, y, z, w) for exact re-evaluation
+    uint32_t ta[CAP];      // clip: new vertex by first old plane | finalize: plane rank
+    uint32_t tb[CAP];      // clip: new vertex by second old plane | finalize: facet size
+    uint32_t sor[CAP];     // clip: free slot of rank | finalize: vertex renumbering
+    W edge[CAP];           // clip: crossing edges by rank
+    uint8_t outf[CAP];     // outside flags by vertex index (VPL > 1)
+};
+template <int VPL>
+struct TableMem<VPL, true> {
+    using W = typename Tier<VPL>::W;
+    static constexpr int CAP = Tier<VPL>::CAP;
+    uint32_t sor[CAP];
+    W edge[CAP > kHotRanks ? CAP : 1];
 };
 
 // queue entries of the 64-vertex pass beyond the first 64
@@ -117,23 +165,17 @@ struct QueueExt<2> {
 };
 
 template <int VPL>
-struct WaveMem : ArenaState<VPL>, QueueExt<VPL> {
+struct WaveMem : ArenaState<VPL>, QueueExt<VPL>, TableMem<VPL> {
     using W = typename Tier<VPL>::W;
     static constexpr int CAP = Tier<VPL>::CAP;
     float4 pl[CAP];        // planes: a.xyz, b (frame of the site)
     float psb[CAP];        // size of the terms b is formed from (error scale)
-    float4 psite[CAP];     // the plane's site (x, y, z, w) for exact re-evaluation
     int32_t pcode[CAP];    // Morton index of the plane's site, or box code -1..-6
-    uint32_t ta[CAP];      // clip: new vertex by first old plane | finalize: plane rank
-    uint32_t tb[CAP];      // clip: new vertex by second old plane | finalize: facet size
-    uint32_t sor[CAP];     // clip: free slot of rank | finalize: vertex renumbering
     uint32_t anchor[CAP];  // finalize: lowest vertex of each facet
-    W edge[CAP];           // clip: crossing edges by rank
     W vtri[CAP];           // finalize: planes of each vertex
     W vadj[CAP];           // finalize: neighbours of each vertex
     double vpx[CAP], vpy[CAP], vpz[CAP];  // finalize: FP64 positions relative to vertex 0
     int32_t key[CAP];      // finalize and gc: output codes, used flags
-    uint8_t outf[CAP];     // outside flags by vertex index (VPL > 1)
 };
 
 // A plane in FP64, recomputed from the input coordinates.
@@ -186,6 +228,7 @@ struct Cell {
     template <typename X>
     using Wave = Col<X, VPL, kReg, 1>;   // one wave-uniform value per slot
     WaveMem<VPL>& M;
+    HotMem<VPL>& H;
     const ClipArgs& A;
     const uint32_t ln;
     const uint32_t wid;  // wave of the group
@@ -208,6 +251,9 @@ struct Cell {
     Lane<float> y0, y1, y2, ev;
     Lane<W> vt, va;
     Wave<uint64_t> alive;
+    float c0[kReg ? 1 : kSlotsCached], c1[kReg ? 1 : kSlotsCached], c2[kReg ? 1 : kSlotsCached];
+    uint64_t cal[kReg ? 1 : kSlotsCached];
+    bool bnd;  // the last effective clip may have moved the bounds
     int np;
     int vhi;  // one past the highest vertex index used since init
     // bounds of the current cell (uniform): AABB in the site's frame, the
@@ -241,18 +287,26 @@ struct Cell {
 
     // the first clip clears the new-vertex tables (the tag counter starts
     // at its wrap-around value)
-    __device__ Cell(WaveMem<VPL>& m, const ClipArgs& a, uint32_t* gxch)
-        : M(m), A(a), ln(lane_id()), wid(G > 1 ? (uint32_t)(threadIdx.x >> 6) : 0u), gx(gxch), gpar(0),
+    __device__ Cell(WaveMem<VPL>& m, HotMem<VPL>& hot, const ClipArgs& a, uint32_t* gxch)
+        : M(m), H(hot), A(a), ln(lane_id()), wid(G > 1 ? uni((uint32_t)(threadIdx.x >> 6)) : 0u), gx(gxch), gpar(0),
           serial(T::kTagMax - 1) {
 #pragma unroll
         for (int c = 0; c < (kCount ? kCtrCount : 1); ++c) ctr[c] = 0;
         if constexpr (!kReg) {
             y0.m = M.y0 + ln; y1.m = M.y1 + ln; y2.m = M.y2 + ln; ev.m = M.ev + ln;
             vt.m = M.vt + ln; va.m = M.va + ln;
-            alive.m = M.alive;
+            alive.m = H.alive;
             qe.m = M.qe + ln; qk.m = M.qk + ln;
         }
         vhi = CAP;
+    }
+    // tables of the new vertices and, when the cell is finished, of its facets
+    __device__ __forceinline__ uint32_t& ta(uint32_t q) { if constexpr (kReg) return M.ta[q]; else return H.ta[q]; }
+    __device__ __forceinline__ uint32_t& tb(uint32_t q) { if constexpr (kReg) return M.tb[q]; else return H.tb[q]; }
+    // the plane's site (the memory tiers read it again where FP64 asks for it)
+    __device__ __forceinline__ float4 site_of(uint32_t q) const {
+        if constexpr (kReg) return M.psite[q];
+        else return M.pcode[q] >= 0 ? A.pts[M.pcode[q]] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __device__ __forceinline__ void count(int c, uint64_t v) {
         if constexpr (kCount) ctr[c] += v;
@@ -290,15 +344,17 @@ struct Cell {
         __syncthreads();
         return t;
     }
-    __device__ __forceinline__ bool g_or(bool x) {
+    // Bitwise or over the group of kBits flags.
+    template <int kBits>
+    __device__ __forceinline__ uint32_t g_or(uint32_t f) {
         if constexpr (G == 1) {
-            return x;
+            return f;
         } else {
-            const uint32_t v[1] = {x ? 1u : 0u};
-            const uint32_t* t = exch(v);
-            bool r = false;
+            const uint32_t v[1] = {f};
+            const uint32_t x = exch(v)[(ln % G) * 8];
+            uint32_t r = 0;
 #pragma unroll
-            for (int w = 0; w < G; ++w) r |= t[w * 8] != 0;
+            for (int k = 0; k < kBits; ++k) r |= ballot((x >> k) & 1u) != 0 ? 1u << k : 0u;
             return r;
         }
     }
@@ -308,48 +364,79 @@ struct Cell {
             return uni(x);
         } else {
             const uint32_t v[1] = {x};
-            return exch(v)[0];
-        }
-    }
-    // Sum over the group of a per-wave count: the total, and in *below the
-    // sum over the waves before this one.
-    __device__ __forceinline__ uint32_t g_scan(uint32_t x, uint32_t* below) {
-        if constexpr (G == 1) {
-            *below = 0;
-            return x;
-        } else {
-            const uint32_t v[1] = {x};
-            const uint32_t* t = exch(v);
-            uint32_t tot = 0, bl = 0;
-#pragma unroll
-            for (int w = 0; w < G; ++w) {
-                const uint32_t c = t[w * 8];
-                if (w < (int)wid) bl += c;
-                tot += c;
-            }
-            *below = bl;
-            return tot;
-        }
-    }
-    // This wave's share [lo, hi) of n items dealt in runs of u (the last run
-    // may reach past n, never past the next multiple of u).
-    __device__ __forceinline__ void share(int n, int u, int* lo, int* hi) const {
-        if constexpr (G == 1) {
-            *lo = 0;
-            *hi = n;
-        } else {
-            const int nu = (n + u - 1) / u;
-            *lo = nu * (int)wid / G * u;
-            *hi = nu * ((int)wid + 1) / G * u;
+            return uni(exch(v)[0]);
         }
     }
     // slots that may hold vertices (all of them in the register tiers)
     __device__ __forceinline__ int nsv() const { return kReg ? VPL : ((vhi + 63) >> 6); }
+    // a wave-uniform value read from the memory of a memory tier
+    __device__ __forceinline__ static uint64_t um(uint64_t v) {
+        if constexpr (kReg) return v;
+        else return uni(v);
+    }
+    // VD_EACH_SLOT runs its body for this wave's slots in use: s_ the slot, its
+    // vertices' positions x_, y_, z_ and their mask al_.  In a group slot s
+    // belongs to wave s % G, and its owner keeps the positions and the mask of
+    // its first kC slots in registers: the tests of boxes, planes and
+    // candidates then read no memory (they waited for LDS at every pair of
+    // slots).  i_ is the place in the registers, kC for the slots beyond.
+    // (A macro: with the body as a closure handed to a function the register
+    // tiers kept their vertices in scratch memory and took four times as long.)
+#define VD_EACH_SLOT(...)                                                                          \
+    do {                                                                                           \
+        if constexpr (kReg) {                                                                      \
+            _Pragma("unroll") for (int s_ = 0; s_ < VPL; ++s_) {                                   \
+                [[maybe_unused]] const int i_ = s_;                                                \
+                [[maybe_unused]] const float x_ = y0[s_], y_ = y1[s_], z_ = y2[s_];                \
+                [[maybe_unused]] const uint64_t al_ = alive[s_];                                   \
+                __VA_ARGS__                                                                        \
+            }                                                                                      \
+        } else {                                                                                   \
+            const int ns_ = nsv();                                                                 \
+            _Pragma("unroll") for (int i_ = 0; i_ < kC; ++i_) {                                    \
+                const int s_ = (int)wid + G * i_;                                                  \
+                if (s_ < ns_) {                                                                    \
+                    [[maybe_unused]] const float x_ = c0[i_], y_ = c1[i_], z_ = c2[i_];            \
+                    [[maybe_unused]] const uint64_t al_ = cal[i_];                                 \
+                    __VA_ARGS__                                                                    \
+                }                                                                                  \
+            }                                                                                      \
+            if constexpr (VPL > G * kC) {                                                          \
+                for (int s_ = (int)wid + G * kC; s_ < ns_; s_ += G) {                              \
+                    [[maybe_unused]] constexpr int i_ = kC;                                        \
+                    [[maybe_unused]] const float x_ = y0[s_], y_ = y1[s_], z_ = y2[s_];            \
+                    [[maybe_unused]] const uint64_t al_ = uni(alive[s_]);                          \
+                    __VA_ARGS__                                                                    \
+                }                                                                                  \
+            }                                                                                      \
+        }                                                                                          \
+    } while (0)
+    static constexpr int kC = kReg ? VPL : kSlotsCached;
+    __device__ __forceinline__ void load_slot(int i, int s) {
+        c0[i] = y0[s];
+        c1[i] = y1[s];
+        c2[i] = y2[s];
+    }
+    // the registers of a cell just begun
+    __device__ __forceinline__ void load_slots() {
+        if constexpr (!kReg) {
+            const int ns = nsv();
+#pragma unroll
+            for (int i = 0; i < kC; ++i) {
+                const int s = (int)wid + G * i;
+                cal[i] = 0;
+                if (s < ns) {
+                    load_slot(i, s);
+                    cal[i] = uni(alive[s]);
+                }
+            }
+        }
+    }
     __device__ __forceinline__ uint64_t nalive() {
         uint64_t c = 0;
         const int ns = nsv();
 #pragma unroll
-        for (int s = 0; s < (kReg ? VPL : ns); ++s) c += (uint64_t)popc(alive[s]);
+        for (int s = 0; s < (kReg ? VPL : ns); ++s) c += (uint64_t)popc(um(alive[s]));
         return c;
     }
 
@@ -358,8 +445,7 @@ struct Cell {
         uint64_t al = 0;
         if constexpr (kReg) {
 #pragma unroll
-            for (int s = 0; s < VPL; ++s)
-                if (s == sl) al = alive[s];
+            for (int s = 0; s < VPL; ++s) al = s == sl ? alive[s] : al;
         } else {
             if (sl < nsv()) al = alive[sl];
         }
@@ -375,7 +461,7 @@ struct Cell {
         flags = 0;
         qn = 0;
         nwarm = 0;
-        if (pw == -INFINITY) return false;  // coincident with a heavier site
+        if (uni(pw) == -INFINITY) return false;  // coincident with a heavier site
         const float lo[3] = {A.bbox[0] - px, A.bbox[1] - py, A.bbox[2] - pz};
         const float hi[3] = {A.bbox[3] - px, A.bbox[4] - py, A.bbox[5] - pz};
         if (ln < 6 && lead()) {
@@ -386,7 +472,7 @@ struct Cell {
             M.pl[ln] = make_float4(a[0], a[1], a[2], b);
             M.psb[ln] = fabsf(b);
             M.pcode[ln] = -(int)(ln + 1);
-            M.psite[ln] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (kReg) M.psite[ln] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         if constexpr (kReg) {
 #pragma unroll
@@ -411,51 +497,21 @@ struct Cell {
         }
         np = 6;
         sync();
+        load_slots();
         update_bounds();
         return true;
-    }
-
-    // Slots are visited kBatch at a time: in the LDS and arena tiers every
-    // load of a batch is issued before any is used (one wait per batch, not
-    // per slot); wave groups deal the slots out two at a time, so that a
-    // cell of few slots still keeps every wave busy.  Slots at or above ns
-    // read as dead (the loads stay in bounds: VPL is a multiple of kBatch).
-    static constexpr int kBatch = kReg ? VPL : (G > 1 ? 2 : 4);
-    struct VBatch {
-        float a[kBatch], b[kBatch], c[kBatch];
-        uint64_t al[kBatch];
-    };
-    __device__ __forceinline__ void load_batch(int s0, int ns, VBatch& v) {
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const int s = s0 + k;
-            v.a[k] = y0[s];
-            v.b[k] = y1[s];
-            v.c[k] = y2[s];
-            const uint64_t al = alive[s];
-            v.al[k] = s < ns ? al : 0ull;
-        }
     }
 
     __device__ void update_bounds() {
         float mn0 = INFINITY, mn1 = INFINITY, mn2 = INFINITY, mx0 = -INFINITY, mx1 = -INFINITY, mx2 = -INFINITY,
               r2 = 0.f;
-        const int ns = nsv();
-        int lo, hi;
-        share(ns, kBatch, &lo, &hi);
-        for (int s0 = (kReg ? 0 : lo); s0 < (kReg ? VPL : hi); s0 += kBatch) {
-            VBatch v;
-            load_batch(s0, ns, v);
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                if ((v.al[k] >> ln) & 1) {
-                    const float a = v.a[k], b = v.b[k], c = v.c[k];
-                    mn0 = fminf(mn0, a); mn1 = fminf(mn1, b); mn2 = fminf(mn2, c);
-                    mx0 = fmaxf(mx0, a); mx1 = fmaxf(mx1, b); mx2 = fmaxf(mx2, c);
-                    if (culling() == 2) r2 = fmaxf(r2, fmaf(a, a, fmaf(b, b, c * c)));
-                }
+        VD_EACH_SLOT({
+            if ((al_ >> ln) & 1) {
+                mn0 = fminf(mn0, x_); mn1 = fminf(mn1, y_); mn2 = fminf(mn2, z_);
+                mx0 = fmaxf(mx0, x_); mx1 = fmaxf(mx1, y_); mx2 = fmaxf(mx2, z_);
+                if (culling() == 2) r2 = fmaxf(r2, fmaf(x_, x_, fmaf(y_, y_, z_ * z_)));
             }
-        }
+        });
         float l0 = wmin(mn0), l1 = wmin(mn1), l2 = wmin(mn2);
         float h0 = wmax(mx0), h1 = wmax(mx1), h2 = wmax(mx2);
         riso2 = culling() == 2 ? wmax(r2) : 0.f;  // the isotropic radius only serves culling mode 2
@@ -475,6 +531,9 @@ struct Cell {
                 h2 = fmaxf(h2, __uint_as_float(x[5]));
                 riso2 = fmaxf(riso2, __uint_as_float(x[6]));
             }
+            l0 = uni(l0); l1 = uni(l1); l2 = uni(l2);
+            h0 = uni(h0); h1 = uni(h1); h2 = uni(h2);
+            riso2 = uni(riso2);
         }
         blo0 = l0; blo1 = l1; blo2 = l2;
         bhi0 = h0; bhi1 = h1; bhi2 = h2;
@@ -495,8 +554,12 @@ struct Cell {
         rmax2 = fmaxf(hx2, lx2) + fmaxf(hy2, ly2) + fmaxf(hz2, lz2);
     }
     // After an effective clip: in the 64-vertex pass only the sides whose
-    // vertex the clip removed are reduced again.
+    // vertex the clip removed are reduced again; in a group the bounds stay
+    // unless the clip removed a vertex on one of them or put one outside.
     __device__ void bounds_after_clip() {
+        if constexpr (G > 1) {
+            if (culling() != 2 && !bnd) return;
+        }
         if constexpr (VPL == 1 && G == 1) {
             if (culling() != 2) {
                 uint32_t lost = 0;
@@ -534,28 +597,17 @@ struct Cell {
     // Returns true if some vertex might be cut (the box cannot be skipped).
     __device__ bool ball_hit(float lx, float ly, float lz, float hx, float hy, float hz, float wm) {
         if constexpr (kCount) count(kCtrBall, nalive());
-        bool hit = false;
-        const int ns = nsv();
-        int lo, hi;
-        share(ns, kBatch, &lo, &hi);
-        for (int s0 = (kReg ? 0 : lo); s0 < (kReg ? VPL : hi); s0 += kBatch) {
-            VBatch v;
-            load_batch(s0, ns, v);
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                if ((v.al[k] >> ln) & 1) {
-                    const float a = v.a[k], b = v.b[k], c = v.c[k];
-                    float dx = fmaxf(fmaxf(lx - a, a - hx), 0.f);
-                    float dy = fmaxf(fmaxf(ly - b, b - hy), 0.f);
-                    float dz = fmaxf(fmaxf(lz - c, c - hz), 0.f);
-                    float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    float r2 = fmaf(a, a, fmaf(b, b, c * c));
-                    float lhs = d2 - wm, rhs = r2 - pwv();
-                    hit |= lhs - rhs <= 16.f * kU * (d2 + r2 + fabsf(wm) + fabsf(pwv()));
-                }
-            }
-        }
-        return g_or(ballot(hit) != 0);
+        uint64_t hit = 0;
+        VD_EACH_SLOT({
+            float dx = fmaxf(fmaxf(lx - x_, x_ - hx), 0.f);
+            float dy = fmaxf(fmaxf(ly - y_, y_ - hy), 0.f);
+            float dz = fmaxf(fmaxf(lz - z_, z_ - hz), 0.f);
+            float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            float r2 = fmaf(x_, x_, fmaf(y_, y_, z_ * z_));
+            float lhs = d2 - wm, rhs = r2 - pwv();
+            hit |= ballot(lhs - rhs <= 16.f * kU * (d2 + r2 + fabsf(wm) + fabsf(pwv()))) & al_;
+        });
+        return g_or<1>(hit != 0 ? 1u : 0u) != 0;
     }
 
     // The ball test of both child records (lanes 0 and 1) in one pass over
@@ -568,44 +620,23 @@ struct Cell {
         const float h0x = rdl(bhx, 0), h0y = rdl(bhy, 0), h0z = rdl(bhz, 0), w0 = kW ? rdl(c.wmax, 0) : 0.f;
         const float l1x = rdl(blx, 1), l1y = rdl(bly, 1), l1z = rdl(blz, 1);
         const float h1x = rdl(bhx, 1), h1y = rdl(bhy, 1), h1z = rdl(bhz, 1), w1 = kW ? rdl(c.wmax, 1) : 0.f;
-        bool a0 = false, a1 = false;
-        const int ns = nsv();
-        int lo, hi;
-        share(ns, kBatch, &lo, &hi);
-        for (int s0 = (kReg ? 0 : lo); s0 < (kReg ? VPL : hi); s0 += kBatch) {
-            VBatch v;
-            load_batch(s0, ns, v);
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                if ((v.al[k] >> ln) & 1) {
-                    const float a = v.a[k], b = v.b[k], cc = v.c[k];
-                    const float r2 = fmaf(a, a, fmaf(b, b, cc * cc)), rhs = r2 - pwv(), tol = r2 + fabsf(pwv());
-                    float dx = fmaxf(fmaxf(l0x - a, a - h0x), 0.f);
-                    float dy = fmaxf(fmaxf(l0y - b, b - h0y), 0.f);
-                    float dz = fmaxf(fmaxf(l0z - cc, cc - h0z), 0.f);
-                    float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    a0 |= (d2 - w0) - rhs <= 16.f * kU * (d2 + tol + fabsf(w0));
-                    dx = fmaxf(fmaxf(l1x - a, a - h1x), 0.f);
-                    dy = fmaxf(fmaxf(l1y - b, b - h1y), 0.f);
-                    dz = fmaxf(fmaxf(l1z - cc, cc - h1z), 0.f);
-                    d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    a1 |= (d2 - w1) - rhs <= 16.f * kU * (d2 + tol + fabsf(w1));
-                }
-            }
-        }
-        bool r0 = ballot(a0) != 0, r1 = ballot(a1) != 0;
-        if constexpr (G > 1) {
-            const uint32_t v2[2] = {r0 ? 1u : 0u, r1 ? 1u : 0u};
-            const uint32_t* t = exch(v2);
-            r0 = r1 = false;
-#pragma unroll
-            for (int w = 0; w < G; ++w) {
-                r0 |= t[w * 8] != 0;
-                r1 |= t[w * 8 + 1] != 0;
-            }
-        }
-        *hit0 = r0;
-        *hit1 = r1;
+        uint64_t a0 = 0, a1 = 0;
+        VD_EACH_SLOT({
+            const float r2 = fmaf(x_, x_, fmaf(y_, y_, z_ * z_)), rhs = r2 - pwv(), tol = r2 + fabsf(pwv());
+            float dx = fmaxf(fmaxf(l0x - x_, x_ - h0x), 0.f);
+            float dy = fmaxf(fmaxf(l0y - y_, y_ - h0y), 0.f);
+            float dz = fmaxf(fmaxf(l0z - z_, z_ - h0z), 0.f);
+            float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            a0 |= ballot((d2 - w0) - rhs <= 16.f * kU * (d2 + tol + fabsf(w0))) & al_;
+            dx = fmaxf(fmaxf(l1x - x_, x_ - h1x), 0.f);
+            dy = fmaxf(fmaxf(l1y - y_, y_ - h1y), 0.f);
+            dz = fmaxf(fmaxf(l1z - z_, z_ - h1z), 0.f);
+            d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            a1 |= ballot((d2 - w1) - rhs <= 16.f * kU * (d2 + tol + fabsf(w1))) & al_;
+        });
+        const uint32_t r = g_or<2>((a0 != 0 ? 1u : 0u) | (a1 != 0 ? 2u : 0u));
+        *hit0 = (r & 1u) != 0;
+        *hit1 = (r & 2u) != 0;
     }
 
     // Applies the ball test to the child record held by lane `l`.
@@ -619,7 +650,7 @@ struct Cell {
     // ------------------------------------------------------------ FP64 side test
     // Plane q in FP64, recomputed from the input coordinates: a = p_j - p_i
     // is exact in FP64, b = (|a|^2 + w_i - w_j) / 2 nearly so.
-    __device__ P64 plane64(uint32_t q) const { return plane64(M.pcode[q], M.psite[q]); }
+    __device__ P64 plane64(uint32_t q) const { return plane64(M.pcode[q], site_of(q)); }
 
     __device__ P64 plane64(int32_t code, float4 site) const {
         P64 r;
@@ -733,9 +764,9 @@ struct Cell {
     __device__ int side_exact(W t, int32_t hcode) const {
         const float4 hsite = A.pts[hcode];
         bool ok = true;
-        const PX P0 = plane_exact(M.pcode[T::fld(t, 0)], M.psite[T::fld(t, 0)], ok);
-        const PX P1 = plane_exact(M.pcode[T::fld(t, 1)], M.psite[T::fld(t, 1)], ok);
-        const PX P2 = plane_exact(M.pcode[T::fld(t, 2)], M.psite[T::fld(t, 2)], ok);
+        const PX P0 = plane_exact(M.pcode[T::fld(t, 0)], site_of(T::fld(t, 0)), ok);
+        const PX P1 = plane_exact(M.pcode[T::fld(t, 1)], site_of(T::fld(t, 1)), ok);
+        const PX P2 = plane_exact(M.pcode[T::fld(t, 2)], site_of(T::fld(t, 2)), ok);
         const PX H = plane_exact(hcode, hsite, ok);
         double cr[3][3];
         xcross(P1.a, P2.a, cr[0], ok);
@@ -775,74 +806,48 @@ struct Cell {
                              int mode, Wave<uint64_t>& R, bool* any_out, bool* all_out) {
         const float an1 = fabsf(ax) + fabsf(ay) + fabsf(az);
         if (kCount && mode != 2) count(kCtrClassify, nalive());
-        const int ns = nsv();
-        uint64_t amb_any = 0;
-        bool anyo = false, allo = true;
-        Lane<uint8_t> amb;
-        if constexpr (!kReg) amb.m = M.amb + ln;
-        int lo, hi;
-        share(ns, kBatch, &lo, &hi);
-        for (int s0 = (kReg ? 0 : lo); s0 < (kReg ? VPL : hi); s0 += kBatch) {
-            VBatch v;
-            load_batch(s0, ns, v);
-            float e[kBatch];
+        bool anyo = false, allo = true, ambf = false;
+        Wave<uint64_t> amb;
+        if constexpr (!kReg) amb.m = H.amb;
+        VD_EACH_SLOT({
+            const float sv = fmaf(ax, x_, fmaf(ay, y_, fmaf(az, z_, -b)));
+            uint64_t r = ballot(sv > 0.f) & al_, am = 0;
             if (mode != 0) {
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) e[k] = ev[s0 + k];
+                const float beta = 64.f * kU * (an1 * ev[s_] + sbh);
+                am = mode == 3 ? al_ : ballot(fabsf(sv) <= beta) & al_;
+                if (mode == 2) r &= ~am;
             }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int s = s0 + k;
-                const float sv = fmaf(ax, v.a[k], fmaf(ay, v.b[k], fmaf(az, v.c[k], -b)));
-                const bool al = (v.al[k] >> ln) & 1;
-                bool o = al && sv > 0.f;
-                bool am = false;
-                if (mode != 0) {
-                    float beta = 64.f * kU * (an1 * e[k] + sbh);
-                    am = al && (mode == 3 || fabsf(sv) <= beta);
-                    if (am && mode == 2) o = false;
-                }
-                const uint64_t r = ballot(o);
-                if (s < ns) {
-                    amb[s] = am;
-                    R[s] = r;
-                }
-                amb_any |= ballot(am);
-                anyo |= r != 0;
-                allo &= r == v.al[k];
-            }
-        }
-        bool ambf = amb_any != 0;
+            amb[s_] = am;
+            R[s_] = r;
+            ambf |= am != 0;
+            anyo |= r != 0;
+            allo &= r == al_;
+        });
         if constexpr (G > 1) {
-            const uint32_t v[3] = {anyo ? 1u : 0u, allo ? 1u : 0u, ambf ? 1u : 0u};
-            const uint32_t* t = exch(v);
-            anyo = false;
-            allo = true;
-            ambf = false;
-#pragma unroll
-            for (int w = 0; w < G; ++w) {
-                anyo |= t[w * 8] != 0;
-                allo &= t[w * 8 + 1] != 0;
-                ambf |= t[w * 8 + 2] != 0;
-            }
+            const uint32_t f = g_or<3>((anyo ? 1u : 0u) | (allo ? 0u : 2u) | (ambf ? 4u : 0u));
+            anyo = (f & 1u) != 0;
+            allo = (f & 2u) == 0;
+            ambf = (f & 4u) != 0;
         }
         if ((mode == 1 || mode == 3) && ambf) {
             flags |= kFlagFP64;
             if constexpr (kCount) {
                 uint64_t na = 0;
 #pragma unroll
-                for (int s = 0; s < (kReg ? VPL : ns); ++s) na += (uint64_t)popc(ballot(amb[s] != 0));
+                for (int s = 0; s < nsv(); ++s) na += (uint64_t)popc(um(amb[s]));
                 count(kCtrFP64, na);
             }
             P64 h = plane64(hcode, A.pts[hcode]);
             anyo = false;
             allo = true;
             bool uns = false, pert = false;
+            const int ns = nsv();
 #pragma unroll
-            for (int s = (kReg ? 0 : lo); s < (kReg ? VPL : min(hi, ns)); ++s) {
-                bool o = (R[s] >> ln) & 1;
+            for (int s = kReg ? 0 : (int)wid; s < (kReg ? VPL : ns); s += G) {
+                const uint64_t al = um(alive[s]);
+                bool o = (um(R[s]) >> ln) & 1;
                 bool unsure = false, tie = false;
-                if (amb[s]) {
+                if ((um(amb[s]) >> ln) & 1) {
                     int sg = side64(vt[s], h);
                     if constexpr (kSoS) {
                         if (sg == 0) {
@@ -856,24 +861,16 @@ struct Cell {
                 const uint64_t r = ballot(o);
                 R[s] = r;
                 anyo |= r != 0;
-                allo &= r == alive[s];
+                allo &= r == al;
                 uns |= ballot(unsure) != 0;
                 pert |= ballot(tie) != 0;
             }
             if constexpr (G > 1) {
-                const uint32_t v[4] = {anyo ? 1u : 0u, allo ? 1u : 0u, uns ? 1u : 0u, pert ? 1u : 0u};
-                const uint32_t* t = exch(v);
-                anyo = false;
-                allo = true;
-                uns = false;
-                pert = false;
-#pragma unroll
-                for (int w = 0; w < G; ++w) {
-                    anyo |= t[w * 8] != 0;
-                    allo &= t[w * 8 + 1] != 0;
-                    uns |= t[w * 8 + 2] != 0;
-                    pert |= t[w * 8 + 3] != 0;
-                }
+                const uint32_t f = g_or<4>((anyo ? 1u : 0u) | (allo ? 0u : 2u) | (uns ? 4u : 0u) | (pert ? 8u : 0u));
+                anyo = (f & 1u) != 0;
+                allo = (f & 2u) == 0;
+                uns = (f & 4u) != 0;
+                pert = (f & 8u) != 0;
             }
             if (uns) flags |= kFlagUncertain;
             if (pert) flags |= kFlagPerturbed;
@@ -882,23 +879,46 @@ struct Cell {
         *all_out = allo;
     }
 
+    // Position and error scale of the vertex of planes (h, x, y), by Cramer's rule.
+    __device__ void solve(uint32_t x, uint32_t y, float ax, float ay, float az, float b, float sbh, float* q0, float* q1,
+                          float* q2, float* e) const {
+        float4 P = M.pl[x], Q = M.pl[y];
+        // n0 = a_x cross a_y, n1 = a_y cross a_h, n2 = a_h cross a_x
+        float n00 = P.y * Q.z - P.z * Q.y, n01 = P.z * Q.x - P.x * Q.z, n02 = P.x * Q.y - P.y * Q.x;
+        float n10 = Q.y * az - Q.z * ay, n11 = Q.z * ax - Q.x * az, n12 = Q.x * ay - Q.y * ax;
+        float n20 = ay * P.z - az * P.y, n21 = az * P.x - ax * P.z, n22 = ax * P.y - ay * P.x;
+        float det = fmaf(ax, n00, fmaf(ay, n01, az * n02));
+        // hardware reciprocal (1 ulp): the FP32 position only decides
+        // signs, within the error scale; outputs are recomputed in FP64
+        float inv = __builtin_amdgcn_rcpf(det);
+        *q0 = (b * n00 + P.w * n10 + Q.w * n20) * inv;
+        *q1 = (b * n01 + P.w * n11 + Q.w * n21) * inv;
+        *q2 = (b * n02 + P.w * n12 + Q.w * n22) * inv;
+        // error scale of the vertex, for the doubtful-sign test (only
+        // read when signs are checked: robust builds)
+        if (robust != 0) {
+            const float sbx = M.psb[x], sby = M.psb[y];
+            float s = (sbh * (fabsf(n00) + fabsf(n01) + fabsf(n02)) +
+                       sbx * (fabsf(n10) + fabsf(n11) + fabsf(n12)) +
+                       sby * (fabsf(n20) + fabsf(n21) + fabsf(n22))) * fabsf(inv);
+            *e = s + fabsf(*q0) + fabsf(*q1) + fabsf(*q2);
+        }
+    }
+
     // Tries the clip with the given outside masks; on an inconsistent
     // boundary sets *consistent = false and leaves the cell untouched.
     __device__ int apply(Wave<uint64_t>& R, bool any, bool all, float ax, float ay, float az, float b, float sbh,
                          int32_t hcode, bool* consistent) {
         *consistent = true;
-        const int ns = nsv();
         if (!any) return kNone;
         if (all) return kEmptied;
         if (np >= CAP) {
             gc();
             if (np >= CAP) return kOverflow;
         }
-        int sa, sb;  // this wave's share of the slots in use
-        share(ns, 1, &sa, &sb);
         if constexpr (VPL > 1) {
 #pragma unroll
-            for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s)
+            for (int s = 0; s < VPL; ++s)
                 M.outf[s * 64 + ln] = (uint8_t)((R[s] >> ln) & 1);
             sync();
         }
@@ -910,16 +930,10 @@ struct Cell {
         Lane<W> rec;
         Lane<uint8_t> isnew;
         Wave<uint64_t> fr;
-        if constexpr (!kReg) {
-            cross.m = M.cross + ln; pre.m = M.pre + ln; frank.m = M.frank + ln;
-            nb1.m = M.nb1 + ln; nb2.m = M.nb2 + ln; rec.m = M.rec + ln; isnew.m = M.isnew + ln;
-            fr.m = M.fr;
-        }
-        // crossing edges of kept vertices, ranked over the wave (over the
-        // group: the counts of lower waves come first)
+        // crossing edges of kept vertices, ranked over the wave
         uint32_t m = 0;
 #pragma unroll
-        for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             bool kept = ((alive[s] & ~R[s]) >> ln) & 1;
             uint32_t c = 0, cnt = 0;
             if (kept) {
@@ -936,22 +950,15 @@ struct Cell {
             pre[s] = m + mbcnt(b0) + 2 * mbcnt(b1);
             m += popc(b0) + 2 * popc(b1);
         }
-        uint32_t pbase;
-        m = g_scan(m, &pbase);
-        // free slots (dead or removed), ranked; slots above the used ones are free
-        const int nsf = kReg ? VPL : min(VPL, ns + (int)((m + 63) >> 6) + 1);
-        int fa, fb;  // this wave's share of the slots new vertices may take
-        share(nsf, 1, &fa, &fb);
+        // free slots (dead or removed), ranked
         uint32_t nfree = 0;
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
-            const uint64_t f = (s < ns) ? (~alive[s] | R[s]) : ~0ull;
+        for (int s = 0; s < VPL; ++s) {
+            const uint64_t f = ~alive[s] | R[s];
             fr[s] = f;
             frank[s] = nfree + mbcnt(f);
             nfree += popc(f);
         }
-        uint32_t fbase;
-        nfree = g_scan(nfree, &fbase);
         if (m == 0) {  // some vertex is cut off but no edge crosses the plane
             *consistent = false;
             return kNone;
@@ -960,23 +967,23 @@ struct Cell {
         const uint32_t h = (uint32_t)np;
         ++serial;
         if (serial >= T::kTagMax) {  // tag space exhausted: clear the tables
-            for (int q = (int)(wid * 64 + ln); q < CAP; q += 64 * G) { M.ta[q] = 0; M.tb[q] = 0; }
+            for (int q = (int)ln; q < CAP; q += 64) { M.ta[q] = 0; M.tb[q] = 0; }
             serial = 1;
         }
         const uint32_t tag = serial << T::kTagShift;
         const uint32_t vmask = (1u << T::kTagShift) - 1u;
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
-            const uint32_t rk = frank[s] + fbase;
+        for (int s = 0; s < VPL; ++s) {
+            const uint32_t rk = frank[s];
             const bool nw = ((fr[s] >> ln) & 1) && rk < m;
             isnew[s] = nw;
             if (nw) M.sor[rk] = s * 64 + ln;
         }
 #pragma unroll
-        for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             const uint32_t c = cross[s];
             if (c) {
-                uint32_t j = pre[s] + pbase;
+                uint32_t j = pre[s];
                 const W t = vt[s];
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
@@ -988,10 +995,10 @@ struct Cell {
         }
         sync();
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             W r = 0;
             if (isnew[s]) {
-                r = M.edge[frank[s] + fbase];
+                r = M.edge[frank[s]];
                 uint32_t me = tag | (uint32_t)(s * 64 + ln);
                 M.ta[T::fld(r, 1)] = me;
                 M.tb[T::fld(r, 2)] = me;
@@ -1001,7 +1008,7 @@ struct Cell {
         sync();
         bool bad = false;
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             uint32_t n1 = 0, n2 = 0;
             if (isnew[s]) {
                 const W r = rec[s];
@@ -1016,7 +1023,7 @@ struct Cell {
             nb1[s] = n1;
             nb2[s] = n2;
         }
-        bad = g_or(ballot(bad) != 0);
+        bad = ballot(bad) != 0;
         if (!bad) {
             // the new vertices must form one cycle around the new facet:
             // following "next around h" from the first one returns after m steps
@@ -1025,15 +1032,10 @@ struct Cell {
             do {
                 const int sl = (int)(v >> 6), lv = (int)(v & 63);
                 uint32_t nxt = 0xFFFFFFFFu;
-                if constexpr (kReg) {
 #pragma unroll
-                    for (int s = 0; s < VPL; ++s)
-                        if (s == sl) nxt = rdl(nb1[s], lv);
-                } else if constexpr (G == 1) {
-                    if (sl < nsf) nxt = rdl(nb1[sl], lv);
-                } else {
-                    // written by other waves, before the exchange above
-                    if (sl < nsf) nxt = uni(M.nb1[v]);
+                for (int s = 0; s < VPL; ++s) {
+                    const uint32_t n1 = rdl(nb1[s], lv);
+                    nxt = s == sl ? n1 : nxt;
                 }
                 v = nxt;
                 ++steps;
@@ -1046,10 +1048,10 @@ struct Cell {
         }
         // commit: kept vertices point at their new neighbours
 #pragma unroll
-        for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             const uint32_t c = cross[s];
             if (c) {
-                uint32_t j = pre[s] + pbase;
+                uint32_t j = pre[s];
                 W a = va[s];
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
@@ -1059,49 +1061,26 @@ struct Cell {
         }
         // new vertices: planes (h, x, y), position by Cramer's rule
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
+        for (int s = 0; s < VPL; ++s) {
             if (isnew[s]) {
                 const W r = rec[s];
                 uint32_t x = T::fld(r, 1), y = T::fld(r, 2);
                 vt[s] = T::pack3(h, x, y);
                 va[s] = T::pack3(T::fld(r, 0), nb1[s], nb2[s]);
-                float4 P = M.pl[x], Q = M.pl[y];
-                // n0 = a_x cross a_y, n1 = a_y cross a_h, n2 = a_h cross a_x
-                float n00 = P.y * Q.z - P.z * Q.y, n01 = P.z * Q.x - P.x * Q.z, n02 = P.x * Q.y - P.y * Q.x;
-                float n10 = Q.y * az - Q.z * ay, n11 = Q.z * ax - Q.x * az, n12 = Q.x * ay - Q.y * ax;
-                float n20 = ay * P.z - az * P.y, n21 = az * P.x - ax * P.z, n22 = ax * P.y - ay * P.x;
-                float det = fmaf(ax, n00, fmaf(ay, n01, az * n02));
-                // hardware reciprocal (1 ulp): the FP32 position only decides
-                // signs, within the error scale; outputs are recomputed in FP64
-                float inv = __builtin_amdgcn_rcpf(det);
-                const float q0 = (b * n00 + P.w * n10 + Q.w * n20) * inv;
-                const float q1 = (b * n01 + P.w * n11 + Q.w * n21) * inv;
-                const float q2 = (b * n02 + P.w * n12 + Q.w * n22) * inv;
+                float q0, q1, q2, e = 0.f;
+                solve(x, y, ax, ay, az, b, sbh, &q0, &q1, &q2, &e);
                 y0[s] = q0;
                 y1[s] = q1;
                 y2[s] = q2;
-                // error scale of the vertex, for the doubtful-sign test (only
-                // read when signs are checked: robust builds)
-                if (robust != 0) {
-                    const float sbx = M.psb[x], sby = M.psb[y];
-                    float e = (sbh * (fabsf(n00) + fabsf(n01) + fabsf(n02)) +
-                               sbx * (fabsf(n10) + fabsf(n11) + fabsf(n12)) +
-                               sby * (fabsf(n20) + fabsf(n21) + fabsf(n22))) * fabsf(inv);
-                    ev[s] = e + fabsf(q0) + fabsf(q1) + fabsf(q2);
-                }
+                if (robust != 0) ev[s] = e;
             }
         }
 #pragma unroll
-        for (int s = (kReg ? 0 : fa); s < (kReg ? VPL : fb); ++s) {
-            const uint64_t keep = (s < ns) ? (alive[s] & ~R[s]) : 0ull;
+        for (int s = 0; s < VPL; ++s) {
+            const uint64_t keep = alive[s] & ~R[s];
             alive[s] = keep | ballot(isnew[s] != 0);
         }
-        if constexpr (!kReg) {
-            // free slots are taken in increasing order: the last rank's is the highest
-            const int top = (int)uni(M.sor[m - 1]) + 1;
-            if (top > vhi) vhi = top;
-        }
-        if (ln == 0 && lead()) {
+        if (ln == 0) {
             M.pl[h] = make_float4(ax, ay, az, b);
             M.psb[h] = sbh;
             M.pcode[h] = hcode;
@@ -1114,24 +1093,309 @@ struct Cell {
         return kChanged;
     }
 
+    // apply() of the memory tiers.  A chain of LDS round trips, barriers and
+    // short dependent sequences (one wave a SIMD), so what counts is their
+    // number: every wave sums the counts of all slots by itself, finds the
+    // crossing edges and free slots of its own slots and puts them into lists
+    // by rank (two barriers); up to 64 new vertices every wave then works out
+    // all of them, one a lane, with no exchange, and the first wave writes
+    // them.  It had a barrier for each of outside flags, counts, lists, tables,
+    // links and the result, followed the links one memory read at a time, kept
+    // its tables in the arena in the 16384-vertex tier, and held every mask in
+    // vector registers since nothing told the compiler that what waves
+    // exchange is uniform.  Time of the passes, with the slots in registers
+    // and the candidates tested two at a time: 1024 vertices 9.9 -> 6.6 ms
+    // (351 cells of 1M power cells), 16384 vertices 9.0 -> 4.6 ms (one cell of
+    // 1452 vertices).
+    __device__ int apply_group(Wave<uint64_t>& R, bool any, bool all, float ax, float ay, float az, float b, float sbh,
+                               int32_t hcode, bool* consistent) {
+        *consistent = true;
+        if (!any) return kNone;
+        if (all) return kEmptied;
+        if (np >= CAP) {
+            gc();
+            if (np >= CAP) return kOverflow;
+        }
+        const int ns = nsv();
+        auto is_out = [&](uint32_t v) -> bool { return (H.R[v >> 6] >> (v & 63u)) & 1ull; };
+        uint32_t cr[kC];  // crossing edges of the vertex (low 3 bits) and their rank in the slot
+#pragma unroll
+        for (int i = 0; i < kC; ++i) cr[i] = 0;
+        VD_EACH_SLOT({
+            const uint64_t r = uni(R[s_]);
+            uint32_t c = 0, cnt = 0;
+            if (((al_ & ~r) >> ln) & 1) {
+                const W nbr = va[s_];
+_Pragma("unroll")
+                for (int e = 0; e < 3; ++e)
+                    if (is_out(T::fld(nbr, e))) {
+                        c |= 1u << e;
+                        ++cnt;
+                    }
+            }
+            const uint64_t b0 = ballot(cnt & 1), b1 = ballot(cnt & 2);
+            c |= (mbcnt(b0) + 2 * mbcnt(b1)) << 3;
+            if (i_ < kC) cr[i_ < kC ? i_ : 0] = c;
+            else M.cross[s_ * 64 + ln] = c;
+            const bool edge_of = x_ == blo0 || x_ == bhi0 || y_ == blo1 || y_ == bhi1 || z_ == blo2 || z_ == bhi2;
+            H.cnt[s_] = (uint32_t)(popc(b0) + 2 * popc(b1)) | ((uint32_t)popc(~al_ | r) << 16) |
+                       ((ballot(edge_of) & r) != 0 ? 1u << 31 : 0u);
+        });
+        sync();
+        // sums over the slots, the same in every wave: crossing edges in the
+        // low 16 bits (at most three a vertex), free places above
+        uint32_t below64 = 0, total = 0;
+        {
+            uint32_t w = ln < (uint32_t)ns ? H.cnt[ln] : 0u;
+            bnd = ballot(w >> 31) != 0;
+            w &= ~(1u << 31);
+            const uint32_t sum = wscan_u(w);
+            below64 = sum - w;
+            total = rdl(sum, 63);
+            if constexpr (VPL > 64) {
+                for (int s0 = 64; s0 < ns; s0 += 64) {
+                    w = s0 + (int)ln < ns ? H.cnt[s0 + ln] : 0u;
+                    bnd |= ballot(w >> 31) != 0;
+                    w &= ~(1u << 31);
+                    const uint32_t x = wscan_u(w) + total;
+                    if (s0 + (int)ln < ns) H.pre[s0 + ln] = x - w;
+                    total = rdl(x, 63);
+                }
+                if (ln < (uint32_t)ns) H.pre[ln] = below64;
+                wave_sync<true>();
+            }
+        }
+        auto below_slot = [&](int i, int s) -> uint32_t {
+            if constexpr (VPL > 64) {
+                if (i == kC) return uni(H.pre[s]);
+            }
+            return rdl(below64, s);
+        };
+        const uint32_t m = total & 0xFFFFu, used_free = total >> 16;  // used_free: free places in the slots in use
+        if (m == 0) {  // some vertex is cut off but no edge crosses the plane
+            *consistent = false;
+            return kNone;
+        }
+        // slots above the used ones are free
+        if (m > used_free + 64u * (uint32_t)(VPL - ns)) return kOverflow;
+        const uint32_t h = (uint32_t)np;
+        ++serial;
+        if (serial >= T::kTagMax) {  // tag space exhausted: clear the tables
+            for (int q = (int)(wid * 64 + ln); q < CAP; q += 64 * G) { H.ta[q] = 0; H.tb[q] = 0; }
+            serial = 1;
+        }
+        const uint32_t tag = serial << T::kTagShift;
+        const uint32_t vmask = (1u << T::kTagShift) - 1u;
+        // lists by rank: the first in LDS
+        auto sor = [&](uint32_t r) -> uint32_t& {
+            if constexpr (CAP > kHotRanks) {
+                if (r >= (uint32_t)kHotRanks) return M.sor[r];
+            }
+            return H.sor[r];
+        };
+        auto edge = [&](uint32_t r) -> W& {
+            if constexpr (CAP > kHotRanks) {
+                if (r >= (uint32_t)kHotRanks) return M.edge[r];
+            }
+            return H.edge[r];
+        };
+        auto place = [&](uint32_t r) -> uint32_t {  // the vertex of rank r
+            return r < used_free ? sor(r) : (uint32_t)ns * 64u + (r - used_free);
+        };
+        VD_EACH_SLOT({
+            const uint32_t below = below_slot(i_, s_), fb = below >> 16;
+            const uint32_t c = i_ < kC ? cr[i_ < kC ? i_ : 0] : M.cross[s_ * 64 + ln];
+            if (c & 7u) {
+                uint32_t j = (below & 0xFFFFu) + (c >> 3);
+                const W t = vt[s_];
+_Pragma("unroll")
+                for (int e = 0; e < 3; ++e)
+                    if ((c >> e) & 1) {
+                        const uint32_t x = T::fld(t, (e + 2) % 3), y = T::fld(t, (e + 1) % 3);
+                        edge(j++) = T::pack3((uint32_t)(s_ * 64 + ln), x, y);
+                    }
+            }
+            if (fb < m) {
+                const uint64_t f = ~al_ | uni(R[s_]);
+                const uint32_t rk = fb + mbcnt(f);
+                if (((f >> ln) & 1) && rk < m) sor(rk) = (uint32_t)(s_ * 64 + ln);
+            }
+        });
+        sync();
+        // the vertex of rank r: links to the next and the previous around h
+        auto links = [&](uint32_t r, W rec, uint32_t* n1, uint32_t* n2) -> bool {
+            const uint32_t me = tag | r, x = T::fld(rec, 1), y = T::fld(rec, 2);
+            const uint32_t a1 = H.ta[y], a2 = H.tb[x];
+            *n1 = a1 & vmask;
+            *n2 = a2 & vmask;
+            return H.ta[x] == me && H.tb[y] == me && (a1 & ~vmask) == tag && (a2 & ~vmask) == tag;
+        };
+        auto put = [&](uint32_t r, W rec, uint32_t n1, uint32_t n2, float q0, float q1, float q2, float e) {
+            const uint32_t v = place(r);
+            M.vt[v] = T::pack3(h, T::fld(rec, 1), T::fld(rec, 2));
+            M.va[v] = T::pack3(T::fld(rec, 0), place(n1), place(n2));
+            M.y0[v] = q0;
+            M.y1[v] = q1;
+            M.y2[v] = q2;
+            if (robust != 0) M.ev[v] = e;
+        };
+        if (m <= 64u) {
+            // every wave writes the same words into the tables
+            const bool nw = ln < m;
+            W rec = 0;
+            uint32_t n1 = 0, n2 = 0;
+            bool bad = false;
+            if (nw) {
+                rec = edge(ln);
+                H.ta[T::fld(rec, 1)] = tag | ln;
+                H.tb[T::fld(rec, 2)] = tag | ln;
+            }
+            wave_sync<true>();
+            if (nw) {
+                bad = !links(ln, rec, &n1, &n2);
+                // inverse permutations without fixed points: one cycle up to
+                // five unless two point at each other (above two)
+                bad |= m >= 4u && n1 == n2;
+            }
+            bad = ballot(bad) != 0;
+            if (!bad && m >= 6u) {
+                uint32_t v = 0, steps = 0;
+                do {
+                    v = rdl(n1, (int)v);
+                    ++steps;
+                } while (v != 0u && steps <= m);
+                bad = steps != m;
+            }
+            if (bad) {
+                *consistent = false;
+                return kNone;
+            }
+            float q0 = 0.f, q1 = 0.f, q2 = 0.f, e = 0.f;
+            bool beyond = false;
+            if (nw) {
+                solve(T::fld(rec, 1), T::fld(rec, 2), ax, ay, az, b, sbh, &q0, &q1, &q2, &e);
+                beyond = q0 < blo0 || q0 > bhi0 || q1 < blo1 || q1 > bhi1 || q2 < blo2 || q2 > bhi2;
+                if (lead()) put(ln, rec, n1, n2, q0, q1, q2, e);
+            }
+            bnd |= ballot(beyond) != 0;
+        } else {
+            bnd = true;
+            const uint32_t step = 64u * G;
+            for (uint32_t r = wid * 64u + ln; r < m; r += step) {
+                const W rec = edge(r);
+                H.ta[T::fld(rec, 1)] = tag | r;
+                H.tb[T::fld(rec, 2)] = tag | r;
+            }
+            sync();
+            bool bad = false;
+            for (uint32_t r = wid * 64u + ln; r < m; r += step) {
+                uint32_t n1, n2;
+                bad |= !links(r, edge(r), &n1, &n2);
+                M.nb1[r] = n1;
+                M.nb2[r] = n2;
+            }
+            bad = g_or<1>(ballot(bad) != 0 ? 1u : 0u) != 0;
+            if (!bad) {
+                uint32_t v = 0, steps = 0;
+                do {
+                    v = uni(M.nb1[v]);
+                    ++steps;
+                } while (v != 0u && steps <= m);
+                bad = steps != m;
+            }
+            if (bad) {
+                *consistent = false;
+                return kNone;
+            }
+            for (uint32_t r = wid * 64u + ln; r < m; r += step) {
+                const W rec = edge(r);
+                float q0, q1, q2, e = 0.f;
+                solve(T::fld(rec, 1), T::fld(rec, 2), ax, ay, az, b, sbh, &q0, &q1, &q2, &e);
+                put(r, rec, M.nb1[r], M.nb2[r], q0, q1, q2, e);
+            }
+        }
+        // free places are taken in increasing order: the last rank's is the highest
+        const int top = (int)uni(place(m - 1u)) + 1;
+        if (top > vhi) vhi = top;
+        // kept vertices point at their new neighbours; the masks; returns
+        // the places of this slot that new vertices take
+        auto commit = [&](int i, int s, uint64_t al, uint64_t* now) -> uint64_t {
+            if (s >= ns) {  // a slot above those in use
+                const uint32_t left = m - used_free - 64u * (uint32_t)(s - ns);
+                *now = left >= 64u ? ~0ull : (1ull << left) - 1ull;
+                alive[s] = *now;
+                return *now;
+            }
+            const uint32_t below = below_slot(i, s), fb = below >> 16;
+            const uint32_t c = i < kC ? cr[i < kC ? i : 0] : M.cross[s * 64 + ln];
+            if (c & 7u) {
+                uint32_t j = (below & 0xFFFFu) + (c >> 3);
+                W nb = va[s];
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if ((c >> e) & 1) nb = T::setfld(nb, e, place(j++));
+                va[s] = nb;
+            }
+            const uint64_t r = uni(R[s]), f = ~al | r;
+            uint64_t fresh = 0;
+            if (fb < m) fresh = ballot(fb + mbcnt(f) < m) & f;
+            *now = (al & ~r) | fresh;
+            alive[s] = *now;
+            return fresh;
+        };
+        const int ns2 = nsv();
+        uint64_t fresh[kC];
+#pragma unroll
+        for (int i = 0; i < kC; ++i) {
+            const int s = (int)wid + G * i;
+            fresh[i] = 0;
+            if (s < ns2) fresh[i] = commit(i, s, cal[i], &cal[i]);
+        }
+        if constexpr (VPL > G * kC) {
+            for (int s = (int)wid + G * kC; s < ns2; s += G) {
+                uint64_t now;
+                commit(kC, s, s < ns ? uni(alive[s]) : 0ull, &now);
+            }
+        }
+        if (ln == 0 && lead()) {
+            M.pl[h] = make_float4(ax, ay, az, b);
+            M.psb[h] = sbh;
+            M.pcode[h] = hcode;
+        }
+        np = (int)h + 1;
+        sync();
+#pragma unroll
+        for (int i = 0; i < kC; ++i)
+            if (fresh[i]) load_slot(i, (int)wid + G * i);
+        count(kCtrNewVertex, m);
+        count(kCtrEffective, 1);
+        return kChanged;
+    }
+
+    __device__ int cut(Wave<uint64_t>& R, bool any, bool all, float ax, float ay, float az, float b, float sbh,
+                       int32_t hcode, bool* consistent) {
+        if constexpr (G > 1) return apply_group(R, any, all, ax, ay, az, b, sbh, hcode, consistent);
+        else return apply(R, any, all, ax, ay, az, b, sbh, hcode, consistent);
+    }
+
     // Plain FP32 signs unless the cell is being rebuilt robustly; an
     // inconsistent boundary in FP32 asks for that rebuild; in the robust modes
     // doubtful signs fall back to "inside" and, failing that, the plane is
     // skipped and the cell flagged.
     __device__ int clip(float ax, float ay, float az, float b, float sbh, int32_t hcode) {
         Wave<uint64_t> R;
-        if constexpr (!kReg) R.m = M.R;
+        if constexpr (!kReg) R.m = H.R;
         count(kCtrClip, 1);
         bool any, all;
         classify(ax, ay, az, b, sbh, hcode, robust == 0 ? 0 : (robust == 1 ? 1 : 3), R, &any, &all);
         bool ok;
-        int r = apply(R, any, all, ax, ay, az, b, sbh, hcode, &ok);
+        int r = cut(R, any, all, ax, ay, az, b, sbh, hcode, &ok);
         if constexpr (VPL == 1 && G == 1) cut_mask = R[0];
         if (ok) return r;
         if (robust < 2) return kRestart;
         flags |= kFlagUncertain;
         classify(ax, ay, az, b, sbh, hcode, 2, R, &any, &all);
-        r = apply(R, any, all, ax, ay, az, b, sbh, hcode, &ok);
+        r = cut(R, any, all, ax, ay, az, b, sbh, hcode, &ok);
         if constexpr (VPL == 1 && G == 1) cut_mask = R[0];
         return ok ? r : kNone;
     }
@@ -1139,12 +1403,10 @@ struct Cell {
     // Drop planes no vertex uses (supplementary Sec. A, "Garbage collection").
     __device__ void gc() {
         const int ns = nsv();
-        int sa, sb;
-        share(ns, 1, &sa, &sb);
         for (int q = (int)(wid * 64 + ln); q < np; q += 64 * G) M.key[q] = 0;
         sync();
 #pragma unroll
-        for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s)
+        for (int s = kReg ? 0 : (int)wid; s < (kReg ? VPL : ns); s += G)
             if ((alive[s] >> ln) & 1) {
                 const W t = vt[s];
                 M.key[T::fld(t, 0)] = 1;
@@ -1195,19 +1457,17 @@ struct Cell {
                 const uint64_t u = ballot(used);
                 const uint32_t dst = cnt + mbcnt(u);
                 cnt += popc(u);
-                float4 pl = make_float4(0.f, 0.f, 0.f, 0.f), ps = pl;
+                float4 pl = make_float4(0.f, 0.f, 0.f, 0.f);
                 float sb = 0.f;
                 int32_t pc = 0;
                 if (used) {
                     pl = M.pl[q];
-                    ps = M.psite[q];
                     sb = M.psb[q];
                     pc = M.pcode[q];
                 }
                 wsync();
                 if (used) {
                     M.pl[dst] = pl;
-                    M.psite[dst] = ps;
                     M.psb[dst] = sb;
                     M.pcode[dst] = pc;
                     M.key[q] = (int32_t)dst;
@@ -1218,7 +1478,7 @@ struct Cell {
         }
         sync();
 #pragma unroll
-        for (int s = (kReg ? 0 : sa); s < (kReg ? VPL : sb); ++s)
+        for (int s = kReg ? 0 : (int)wid; s < (kReg ? VPL : ns); s += G)
             if ((alive[s] >> ln) & 1) {
                 const W t = vt[s];
                 vt[s] = T::pack3((uint32_t)M.key[T::fld(t, 0)], (uint32_t)M.key[T::fld(t, 1)],
@@ -1298,11 +1558,11 @@ struct Cell {
         }
         if constexpr (kReg) {
 #pragma unroll
-            for (int s = 0; s < VPL; ++s)
-                if (s == slot && (int)ln == l) {
-                    qe[s] = e;
-                    qk[s] = k;
-                }
+            for (int s = 0; s < VPL; ++s) {
+                const bool here = s == slot && (int)ln == l;
+                qe[s] = here ? e : qe[s];
+                qk[s] = here ? k : qk[s];
+            }
         } else {
             if ((int)ln == l && lead()) {
                 qe[slot] = e;
@@ -1322,8 +1582,8 @@ struct Cell {
         if constexpr (G > 1) {
             const uint32_t v[2] = {ee, __float_as_uint(kk)};
             const uint32_t* t = exch(v);
-            ee = t[0];
-            kk = __uint_as_float(t[1]);
+            ee = uni(t[0]);
+            kk = __uint_as_float(uni(t[1]));
         }
         --qn;
         *e = ee;
@@ -1338,8 +1598,21 @@ struct Cell {
         } else {
             float bk = INFINITY;
             int bs = 0;
+            if constexpr (!kReg) {
+                for (int s = 0; s < nq; s += 4) {  // four loads at a time (VPL is a multiple of four)
+                    float kk[4];
 #pragma unroll
-            for (int s = 0; s < (kReg ? VPL : nq); ++s) {
+                    for (int k = 0; k < 4; ++k) kk[k] = qk[s + k];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if ((s + k) * 64 + (int)ln < qn && kk[k] < bk) {
+                            bk = kk[k];
+                            bs = s + k;
+                        }
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < (kReg ? VPL : 0); ++s) {
                 int idx = s * 64 + (int)ln;
                 if (idx < qn) {
                     const float kk = qk[s];
@@ -1373,11 +1646,12 @@ struct Cell {
             if (ls >= VPL) {  // the last entry is beyond the register slots (LDS)
                 if (S < VPL) {
 #pragma unroll
-                    for (int s = 0; s < VPL; ++s)
-                        if (s == S) {
-                            ee = rdl(qe[s], L);
-                            kk = rdl(qk[s], L);
-                        }
+                    for (int s = 0; s < VPL; ++s) {
+                        const uint32_t e1 = rdl(qe[s], L);
+                        const float k1 = rdl(qk[s], L);
+                        ee = s == S ? e1 : ee;
+                        kk = s == S ? k1 : kk;
+                    }
                 } else {
                     ee = uni(M.qxe[(S - VPL) * 64 + L]);
                     kk = uni(M.qxk[(S - VPL) * 64 + L]);
@@ -1386,11 +1660,11 @@ struct Cell {
                 lk = uni(M.qxk[last - 64 * VPL]);
                 if (S < VPL) {
 #pragma unroll
-                    for (int s = 0; s < VPL; ++s)
-                        if (s == S && (int)ln == L) {
-                            qe[s] = le;
-                            qk[s] = lk;
-                        }
+                    for (int s = 0; s < VPL; ++s) {
+                        const bool here = s == S && (int)ln == L;
+                        qe[s] = here ? le : qe[s];
+                        qk[s] = here ? lk : qk[s];
+                    }
                 } else {
                     if (ln == 0) {
                         M.qxe[(S - VPL) * 64 + L] = le;
@@ -1405,23 +1679,20 @@ struct Cell {
         }
         if constexpr (kReg) {
 #pragma unroll
-            for (int s = 0; s < VPL; ++s)
-                if (s == S) {
-                    ee = rdl(qe[s], L);
-                    kk = rdl(qk[s], L);
-                }
+            for (int s = 0; s < VPL; ++s) {
+                const uint32_t e1 = rdl(qe[s], L), e2 = rdl(qe[s], ll);
+                const float k1 = rdl(qk[s], L), k2 = rdl(qk[s], ll);
+                ee = s == S ? e1 : ee;
+                kk = s == S ? k1 : kk;
+                le = s == ls ? e2 : le;
+                lk = s == ls ? k2 : lk;
+            }
 #pragma unroll
-            for (int s = 0; s < VPL; ++s)
-                if (s == ls) {
-                    le = rdl(qe[s], ll);
-                    lk = rdl(qk[s], ll);
-                }
-#pragma unroll
-            for (int s = 0; s < VPL; ++s)
-                if (s == S && (int)ln == L) {
-                    qe[s] = le;
-                    qk[s] = lk;
-                }
+            for (int s = 0; s < VPL; ++s) {
+                const bool here = s == S && (int)ln == L;
+                qe[s] = here ? le : qe[s];
+                qk[s] = here ? lk : qk[s];
+            }
         } else {
             ee = rdl(qe[S], L);
             kk = rdl(qk[S], L);
@@ -1444,41 +1715,42 @@ struct Cell {
     // exchange) instead of a selection and a clip each.  The test is the FP32
     // side test of classify.
     __device__ uint64_t cutting(uint64_t mask, float ax, float ay, float az, float b, float sb) {
-        const int ns = nsv();
-        int lo, hi;
-        share(ns, kBatch, &lo, &hi);
-        const bool tol = robust != 0;
         if constexpr (kCount) count(kCtrClassify, nalive() * (uint64_t)popc(mask));
-        uint64_t cb = 0;  // candidates this lane's vertices put outside
-        for (int s0 = (kReg ? 0 : lo); s0 < (kReg ? VPL : hi); s0 += kBatch) {
-            VBatch v;
-            load_batch(s0, ns, v);
-            float e[kBatch];
-            if (tol) {
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) e[k] = ev[s0 + k];
+        uint64_t cut = 0;  // candidates that put a vertex of this wave outside
+        for (uint64_t m = mask; m;) {  // two candidates at a time
+            const int L0 = lowest(m);
+            m &= m - 1;
+            const int L1 = m ? lowest(m) : L0;
+            m &= m - 1;
+            const float p0 = rdl(ax, L0), p1 = rdl(ay, L0), p2 = rdl(az, L0), pb = rdl(b, L0);
+            const float q0 = rdl(ax, L1), q1 = rdl(ay, L1), q2 = rdl(az, L1), qb = rdl(b, L1);
+            uint64_t o0 = 0, o1 = 0;
+            if (robust == 0) {
+                VD_EACH_SLOT({
+                    o0 |= ballot(fmaf(p0, x_, fmaf(p1, y_, fmaf(p2, z_, -pb))) > 0.f) & al_;
+                    o1 |= ballot(fmaf(q0, x_, fmaf(q1, y_, fmaf(q2, z_, -qb))) > 0.f) & al_;
+                });
+            } else {
+                const float pn = fabsf(p0) + fabsf(p1) + fabsf(p2), ps = rdl(sb, L0);
+                const float qn1 = fabsf(q0) + fabsf(q1) + fabsf(q2), qs = rdl(sb, L1);
+                VD_EACH_SLOT({
+                    const float e = ev[s_];
+                    o0 |= ballot(fmaf(p0, x_, fmaf(p1, y_, fmaf(p2, z_, -pb))) >= -64.f * kU * (pn * e + ps)) & al_;
+                    o1 |= ballot(fmaf(q0, x_, fmaf(q1, y_, fmaf(q2, z_, -qb))) >= -64.f * kU * (qn1 * e + qs)) & al_;
+                });
             }
-            for (uint64_t m = mask; m; m &= m - 1) {
-                const int L = lowest(m);
-                const float hx = rdl(ax, L), hy = rdl(ay, L), hz = rdl(az, L), hb = rdl(b, L);
-                const float an1 = fabsf(hx) + fabsf(hy) + fabsf(hz), hs = rdl(sb, L);
-                bool o = false;
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const float sv = fmaf(hx, v.a[k], fmaf(hy, v.b[k], fmaf(hz, v.c[k], -hb)));
-                    const bool al = (v.al[k] >> ln) & 1;
-                    o |= al && (tol ? sv >= -64.f * kU * (an1 * e[k] + hs) : sv > 0.f);
-                }
-                if (o) cb |= 1ull << L;
-            }
+            cut |= (o0 != 0 ? 1ull << L0 : 0ull) | (o1 != 0 ? 1ull << L1 : 0ull);
         }
-        uint64_t cut = wor64(cb);
         if constexpr (G > 1) {
             const uint32_t v2[2] = {(uint32_t)cut, (uint32_t)(cut >> 32)};
             const uint32_t* t = exch(v2);
-            cut = 0;
+            uint32_t lo = 0, hi = 0;
 #pragma unroll
-            for (int w = 0; w < G; ++w) cut |= (uint64_t)t[w * 8] | ((uint64_t)t[w * 8 + 1] << 32);
+            for (int w = 0; w < G; ++w) {
+                lo |= t[w * 8];
+                hi |= t[w * 8 + 1];
+            }
+            cut = (uint64_t)uni(lo) | ((uint64_t)uni(hi) << 32);
         }
         return mask & cut;
     }
@@ -1524,7 +1796,7 @@ struct Cell {
         // from 128 vertices up, the candidates that miss the cell are dropped
         // all at once (not when every sign is taken in FP64)
         if constexpr (G > 1 || VPL >= 2) {
-            if (mask && robust < 2) mask = cutting(mask, ax, ay, az, b, 0.5f * (a2 + fabsf(dw)));
+            if (mask && robust < 2) mask = cutting(mask, ax, ay, az, b, sbl);
         }
         while (mask) {
             // nearest plane first (both traversal orders)
@@ -1553,6 +1825,10 @@ struct Cell {
             if (r == kChanged) {
                 bounds_after_clip();
                 mask &= ballot(keep(true));
+                // what the cut cell no longer meets needs no clip either
+                if constexpr (G > 1 || VPL >= 2) {
+                    if (mask && robust < 2) mask = cutting(mask, ax, ay, az, b, sbl);
+                }
             }
         }
         return kNone;
@@ -1866,66 +2142,66 @@ struct Cell {
     // ------------------------------------------------------------ hand-over
     // Writes the state of a cell that overflowed for the next pass; only the
     // header when the overflow is not resumable.
-    __device__ void save(HOut& H) {
+    __device__ void save(HOut& o) {
         if constexpr (kSaves) {
             sync();
             const int tid = (int)(wid * 64 + ln), step = 64 * G;
             if (ov_ok) {
                 for (int q = tid; q < np; q += step) {
-                    H.pl[q] = M.pl[q];
-                    H.psite[q] = M.psite[q];
-                    H.psb[q] = M.psb[q];
-                    H.pcode[q] = M.pcode[q];
+                    o.pl[q] = M.pl[q];
+                    o.psite[q] = site_of((uint32_t)q);
+                    o.psb[q] = M.psb[q];
+                    o.pcode[q] = M.pcode[q];
                 }
                 if constexpr (kReg) {
 #pragma unroll
                     for (int s = 0; s < VPL; ++s) {
                         const int q = s * 64 + (int)ln;
-                        H.y0[q] = y0[s];
-                        H.y1[q] = y1[s];
-                        H.y2[q] = y2[s];
-                        H.ev[q] = ev[s];
-                        H.vt[q] = vt[s];
-                        H.va[q] = va[s];
-                        H.qe[q] = qe[s];
-                        H.qk[q] = qk[s];
-                        if (ln == 0) H.alive[s] = alive[s];
+                        o.y0[q] = y0[s];
+                        o.y1[q] = y1[s];
+                        o.y2[q] = y2[s];
+                        o.ev[q] = ev[s];
+                        o.vt[q] = vt[s];
+                        o.va[q] = va[s];
+                        o.qe[q] = qe[s];
+                        o.qk[q] = qk[s];
+                        if (ln == 0) o.alive[s] = alive[s];
                     }
                     if constexpr (kQExt) {
                         for (int q = 64 * VPL + (int)ln; q < qn; q += 64) {
-                            H.qe[q] = M.qxe[q - 64 * VPL];
-                            H.qk[q] = M.qxk[q - 64 * VPL];
+                            o.qe[q] = M.qxe[q - 64 * VPL];
+                            o.qk[q] = M.qxk[q - 64 * VPL];
                         }
                     }
                 } else {
                     for (int q = tid; q < vhi; q += step) {
-                        H.y0[q] = M.y0[q];
-                        H.y1[q] = M.y1[q];
-                        H.y2[q] = M.y2[q];
-                        H.ev[q] = M.ev[q];
-                        H.vt[q] = M.vt[q];
-                        H.va[q] = M.va[q];
+                        o.y0[q] = M.y0[q];
+                        o.y1[q] = M.y1[q];
+                        o.y2[q] = M.y2[q];
+                        o.ev[q] = M.ev[q];
+                        o.vt[q] = M.vt[q];
+                        o.va[q] = M.va[q];
                     }
                     for (int q = tid; q < qn; q += step) {
-                        H.qe[q] = M.qe[q];
-                        H.qk[q] = M.qk[q];
+                        o.qe[q] = M.qe[q];
+                        o.qk[q] = M.qk[q];
                     }
-                    if (tid < nsv()) H.alive[tid] = M.alive[tid];
+                    if (tid < nsv()) o.alive[tid] = H.alive[tid];
                 }
             }
-            if (tid < kMaxWarm) H.wsite[tid] = tid < nwarm ? wsite : 0u;  // lane t of wave 0 holds site t
+            if (tid < kMaxWarm) o.wsite[tid] = tid < nwarm ? wsite : 0u;  // lane t of wave 0 holds site t
             if (tid == 0) {
-                H.nwarm = (uint32_t)nwarm;
-                H.np = (uint32_t)np;
-                H.vhi = (uint32_t)(kReg ? CAP : vhi);
-                H.qn = (uint32_t)qn;
-                H.flags = flags;
-                H.robust = (uint32_t)robust;
-                H.leaf = ov_leaf;
-                H.mask = ov_mask;
-                H.phase = ov_phase;
-                H.skip = ov_phase == 0 ? kNoParent : ov_skip;
-                H.valid = ov_ok ? 1u : 0u;
+                o.nwarm = (uint32_t)nwarm;
+                o.np = (uint32_t)np;
+                o.vhi = (uint32_t)(kReg ? CAP : vhi);
+                o.qn = (uint32_t)qn;
+                o.flags = flags;
+                o.robust = (uint32_t)robust;
+                o.leaf = ov_leaf;
+                o.mask = ov_mask;
+                o.phase = ov_phase;
+                o.skip = ov_phase == 0 ? kNoParent : ov_skip;
+                o.valid = ov_ok ? 1u : 0u;
             }
         }
     }
@@ -1933,50 +2209,50 @@ struct Cell {
     // Takes over a cell saved by the previous pass (instead of init): the
     // traversal then goes on with resume = true, H.leaf, H.mask, H.phase.
     // Vertex, plane and queue numbers are the same in every pass.
-    __device__ void resume(uint32_t k, const HIn& H) {
+    __device__ void resume(uint32_t k, const HIn& in) {
         if constexpr (kResumes) {
             sync();  // every wave is done with the previous cell
             self = k;
             float4 s = A.pts[k];
             px = s.x; py = s.y; pz = s.z; pw = s.w;
-            flags = H.flags;
-            robust = (int)H.robust;
-            nwarm = (int)H.nwarm;
-            wsite = (int)ln < kMaxWarm ? H.wsite[ln] : 0u;
-            np = (int)H.np;
-            vhi = (int)H.vhi;
-            qn = (int)H.qn;
+            flags = uni(in.flags);
+            robust = (int)uni(in.robust);
+            nwarm = (int)uni(in.nwarm);
+            wsite = (int)ln < kMaxWarm ? in.wsite[ln] : 0u;
+            np = (int)uni(in.np);
+            vhi = (int)uni(in.vhi);
+            qn = (int)uni(in.qn);
             const int tid = (int)(wid * 64 + ln), step = 64 * G;
             for (int q = tid; q < np; q += step) {
-                M.pl[q] = H.pl[q];
-                M.psite[q] = H.psite[q];
-                M.psb[q] = H.psb[q];
-                M.pcode[q] = H.pcode[q];
+                M.pl[q] = in.pl[q];
+                if constexpr (kReg) M.psite[q] = in.psite[q];
+                M.psb[q] = in.psb[q];
+                M.pcode[q] = in.pcode[q];
             }
             if constexpr (kReg) {
 #pragma unroll
                 for (int s2 = 0; s2 < VPL; ++s2) {
                     const int q = s2 * 64 + (int)ln;
                     if (s2 < kPrevCap / 64) {
-                        y0[s2] = H.y0[q];
-                        y1[s2] = H.y1[q];
-                        y2[s2] = H.y2[q];
-                        ev[s2] = H.ev[q];
-                        vt[s2] = H.vt[q];
-                        va[s2] = H.va[q];
-                        alive[s2] = H.alive[s2];
+                        y0[s2] = in.y0[q];
+                        y1[s2] = in.y1[q];
+                        y2[s2] = in.y2[q];
+                        ev[s2] = in.ev[q];
+                        vt[s2] = in.vt[q];
+                        va[s2] = in.va[q];
+                        alive[s2] = in.alive[s2];
                     } else {
                         alive[s2] = 0ull;
                     }
                     if (s2 < kPrevQ / 64) {
-                        qe[s2] = H.qe[q];
-                        qk[s2] = H.qk[q];
+                        qe[s2] = in.qe[q];
+                        qk[s2] = in.qk[q];
                     }
                 }
                 if constexpr (kQExt) {
                     for (int q = 64 * VPL + (int)ln; q < qn; q += 64) {
-                        M.qxe[q - 64 * VPL] = H.qe[q];
-                        M.qxk[q - 64 * VPL] = H.qk[q];
+                        M.qxe[q - 64 * VPL] = in.qe[q];
+                        M.qxk[q - 64 * VPL] = in.qk[q];
                     }
                 }
                 vhi = CAP;
@@ -1988,20 +2264,21 @@ struct Cell {
                     else return T::pack3(x & 1023u, (x >> 10) & 1023u, (x >> 20) & 1023u);
                 };
                 for (int q = tid; q < vhi; q += step) {
-                    M.y0[q] = H.y0[q];
-                    M.y1[q] = H.y1[q];
-                    M.y2[q] = H.y2[q];
-                    M.ev[q] = H.ev[q];
-                    M.vt[q] = wide(H.vt[q]);
-                    M.va[q] = wide(H.va[q]);
+                    M.y0[q] = in.y0[q];
+                    M.y1[q] = in.y1[q];
+                    M.y2[q] = in.y2[q];
+                    M.ev[q] = in.ev[q];
+                    M.vt[q] = wide(in.vt[q]);
+                    M.va[q] = wide(in.va[q]);
                 }
                 for (int q = tid; q < qn; q += step) {
-                    M.qe[q] = H.qe[q];
-                    M.qk[q] = H.qk[q];
+                    M.qe[q] = in.qe[q];
+                    M.qk[q] = in.qk[q];
                 }
-                if (tid < nsv()) M.alive[tid] = H.alive[tid];
+                if (tid < nsv()) H.alive[tid] = in.alive[tid];
             }
             sync();
+            load_slots();
             update_bounds();
         }
     }
@@ -2044,8 +2321,8 @@ struct Cell {
             int32_t mine = M.key[q];
             uint32_t r = 0;
             for (int t = 0; t < F; ++t) r += M.key[t] < mine ? 1u : 0u;
-            M.ta[q] = r;
-            M.tb[q] = 0;
+            ta(q) = r;
+            tb(q) = 0;
             M.anchor[q] = 0xFFFFFFFFu;
         }
         Stage st;
@@ -2059,7 +2336,7 @@ struct Cell {
             st.fv = ka->stage.fv;
         }
         int32_t* codes = st.code + (int64_t)slot * st.cap;
-        for (int q = ln; q < F; q += 64) codes[M.ta[q]] = M.key[q];
+        for (int q = ln; q < F; q += 64) codes[ta(q)] = M.key[q];
         // vertex renumbering 0..nv-1 (slot-major)
         uint32_t nv = 0;
         int s0 = -1;
@@ -2075,12 +2352,28 @@ struct Cell {
         // reference point of the tetrahedral fan: vertex 0, in FP64
         double ref[3] = {0.0, 0.0, 0.0};
         {
-            const int l0 = lowest(alive[s0]);
-            double y[3] = {0.0, 0.0, 0.0};
+            // (selects and no index: an array of the cell indexed at run time
+            // would be kept in scratch memory, and the whole cell with it)
+            uint64_t m0 = 0;
             if constexpr (kReg) {
 #pragma unroll
-                for (int s = 0; s < VPL; ++s)
-                    if (s == s0 && (int)ln == l0) pos64(vt[s], y0[s], y1[s], y2[s], y);
+                for (int s = 0; s < VPL; ++s) m0 = s == s0 ? alive[s] : m0;
+            } else {
+                m0 = uni(alive[s0]);
+            }
+            const int l0 = lowest(m0);
+            double y[3] = {0.0, 0.0, 0.0};
+            if constexpr (kReg) {
+                W t = vt[0];
+                float a = y0[0], b = y1[0], c = y2[0];
+#pragma unroll
+                for (int s = 1; s < VPL; ++s) {
+                    t = s == s0 ? vt[s] : t;
+                    a = s == s0 ? y0[s] : a;
+                    b = s == s0 ? y1[s] : b;
+                    c = s == s0 ? y2[s] : c;
+                }
+                if ((int)ln == l0) pos64(t, a, b, c, y);
             } else {
                 if ((int)ln == l0) pos64(vt[s0], y0[s0], y1[s0], y2[s0], y);
             }
@@ -2108,7 +2401,7 @@ struct Cell {
         for (int s = 0; s < (kReg ? VPL : ns); ++s) {
             if ((alive[s] >> ln) & 1) {
                 const W t = vt[s], a = va[s];
-                uint32_t t0 = M.ta[T::fld(t, 0)], t1 = M.ta[T::fld(t, 1)], t2 = M.ta[T::fld(t, 2)];
+                uint32_t t0 = ta(T::fld(t, 0)), t1 = ta(T::fld(t, 1)), t2 = ta(T::fld(t, 2));
                 uint32_t a0 = M.sor[T::fld(a, 0)], a1 = M.sor[T::fld(a, 1)], a2 = M.sor[T::fld(a, 2)];
                 const uint32_t v = M.sor[s * 64 + ln];
                 M.vtri[v] = T::pack3(t0, t1, t2);
@@ -2126,9 +2419,9 @@ struct Cell {
                 vout[v] = make_float4((float)(p64[0] + y[0]), (float)(p64[1] + y[1]), (float)(p64[2] + y[2]),
                                       __uint_as_float(packed));
                 if (tri64) tri64[v] = (uint64_t)u0 | ((uint64_t)u1 << 21) | ((uint64_t)u2 << 42);
-                atomicAdd(&M.tb[t0], 1u);
-                atomicAdd(&M.tb[t1], 1u);
-                atomicAdd(&M.tb[t2], 1u);
+                atomicAdd(&tb(t0), 1u);
+                atomicAdd(&tb(t1), 1u);
+                atomicAdd(&tb(t2), 1u);
                 atomicMin(&M.anchor[t0], v);
                 atomicMin(&M.anchor[t1], v);
                 atomicMin(&M.anchor[t2], v);
@@ -2142,7 +2435,7 @@ struct Cell {
         uint32_t carry = 0;
         for (int r0 = 0; r0 < F; r0 += 64) {
             const uint32_t r = (uint32_t)(r0 + (int)ln);
-            uint32_t sz = r < (uint32_t)F ? M.tb[r] : 0u;
+            uint32_t sz = r < (uint32_t)F ? tb(r) : 0u;
             uint32_t x = sz;
             for (int o = 1; o < 64; o <<= 1) {
                 uint32_t y = __shfl_up(x, o);
@@ -2235,14 +2528,14 @@ constexpr int kWaves1 = 4, kWaves2 = 2;  // waves per block of the two register 
 // The work loop shared by every tier (per wave, or per wave group with gx
 // its exchange tables).
 template <int VPL, bool kLds, bool kCount, int G = 1, bool kSoS = false, bool kW = true, bool kOpt = true>
-__device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
+__device__ void run_cells(WaveMem<VPL>& M, HotMem<VPL>& H, const ClipArgs& A, uint32_t* gx) {
     KArgs* ka = cold_args();
     // the input checks (non-finite values, a flat box) ran before this pass:
     // on such input no cell is built
     if (*ka->err != 0u) return;
     const uint32_t count = ka->list ? *ka->list_count : (uint32_t)A.n;
     if (count == 0) return;  // a larger pass with no cell
-    Cell<VPL, kLds, kCount, G, kSoS, kW, kOpt> C(M, A, gx);
+    Cell<VPL, kLds, kCount, G, kSoS, kW, kOpt> C(M, H, A, gx);
     unsigned long long st_empty = 0, st_large = 0, st_unc = 0, st_fail = 0, st_fp64 = 0, st_res = 0, st_pert = 0;
     constexpr uint32_t kWorkers = G > 1 ? 1u : (VPL == 1 ? kWaves1 : kWaves2);
     Work<kWorkers> work(count);
@@ -2272,7 +2565,7 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
         if constexpr (CellT::kResumes) {
             if (kc->hand_in && c < kc->hand_in_cap) {
                 const auto* h = static_cast<const typename CellT::HIn*>(kc->hand_in) + c;
-                if (h->valid) hin = h;
+                if (uni(h->valid)) hin = h;
             }
         }
         // a cell is built with plain FP32 signs first (mixed mode: with FP64
@@ -2293,8 +2586,8 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
             if (attempt > 0) C.flags |= kFlagFP64;
             if (A.tier > 0) C.flags |= kFlagLarge;
             const uint64_t t0 = C.tic();
-            int r = C.traverse(res, res ? hin->leaf : 0u, res ? hin->mask : 0ull, res ? hin->phase : 1u,
-                               res ? hin->skip : kNoParent);
+            int r = C.traverse(res, res ? uni(hin->leaf) : 0u, res ? uni((uint64_t)hin->mask) : 0ull, res ? uni(hin->phase) : 1u,
+                               res ? uni(hin->skip) : kNoParent);
             C.toc(kCtrCycTraverse, t0);
             if (r == kRestart) {
                 C.robust = C.robust + 1;
@@ -2382,20 +2675,20 @@ __device__ void run_cells(WaveMem<VPL>& M, const ClipArgs& A, uint32_t* gx) {
 template <int VPL, int WAVES, bool kCount, bool kSoS = false, bool kW = true, bool kOpt = true>
 __global__ __launch_bounds__(64 * WAVES, VPL == 1 ? 4 : 2) void k_clip(ClipArgs A) {
     __shared__ WaveMem<VPL> mem[WAVES];
-    run_cells<VPL, true, kCount, 1, kSoS, kW, kOpt>(mem[threadIdx.x >> 6], A, nullptr);
+    HotMem<VPL> none;
+    run_cells<VPL, true, kCount, 1, kSoS, kW, kOpt>(mem[threadIdx.x >> 6], none, A, nullptr);
 }
 
 // Waves per cell in the 1024-vertex (LDS) and 16384-vertex (arena) tiers.
-constexpr int kGroupLds = 4;
-constexpr int kGroupArena = 8;
 
 // 1024-vertex tier: the kGroupLds waves of a block build one cell, its
 // arrays in LDS (one block per CU).
 template <bool kCount, bool kSoS = false>
 __global__ __launch_bounds__(64 * kGroupLds, 1) void k_clip_lds(ClipArgs A) {
     __shared__ WaveMem<16> mem;
+    __shared__ HotMem<16> hot;
     __shared__ uint32_t gx[2 * kGroupLds * 8];
-    run_cells<16, true, kCount, kGroupLds, kSoS>(mem, A, gx);
+    run_cells<16, true, kCount, kGroupLds, kSoS>(mem, hot, A, gx);
 }
 
 // 16384-vertex tier: the kGroupArena waves of a block build one cell, its
@@ -2403,14 +2696,17 @@ __global__ __launch_bounds__(64 * kGroupLds, 1) void k_clip_lds(ClipArgs A) {
 constexpr int kArenaVPL = kTierCap[3] / 64;
 template <bool kCount, bool kSoS = false>
 __global__ __launch_bounds__(64 * kGroupArena) void k_clip_arena(ClipArgs A, WaveMem<kArenaVPL>* arena) {
+    __shared__ HotMem<kArenaVPL> hot;
     __shared__ uint32_t gx[2 * kGroupArena * 8];
-    run_cells<kArenaVPL, false, kCount, kGroupArena, kSoS>(arena[blockIdx.x], A, gx);
+    run_cells<kArenaVPL, false, kCount, kGroupArena, kSoS>(arena[blockIdx.x], hot, A, gx);
 }
 
 static_assert(kTierCap[0] == 64 && kTierCap[1] == 128 && kTierCap[2] == 1024,
               "the LDS tiers are instantiated for 64, 256 and 1024 vertices");
-static_assert(sizeof(WaveMem<16>) + 2 * kGroupLds * 8 * sizeof(uint32_t) <= 160 * 1024,
+static_assert(sizeof(WaveMem<16>) + sizeof(HotMem<16>) + 2 * kGroupLds * 8 * sizeof(uint32_t) <= 160 * 1024,
               "the 1024-vertex tier must fit the LDS of one CU");
+static_assert(sizeof(HotMem<kArenaVPL>) + 2 * kGroupArena * 8 * sizeof(uint32_t) <= 160 * 1024,
+              "the clip tables of the 16384-vertex tier must fit the LDS of one CU");
 static_assert(Tier<kArenaVPL>::CAP <= (1 << Tier<kArenaVPL>::kB) && Tier<kArenaVPL>::CAP <= (1 << 16),
               "arena-tier indices must fit their packings and the 16-bit staged facet lists");
 

@@ -46,6 +46,9 @@ __device__ __forceinline__ uint32_t rdl(uint32_t v, int l) { return (uint32_t)__
 __device__ __forceinline__ int rdl(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 __device__ __forceinline__ float uni(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uni(uint64_t v) {
+    return (uint64_t)uni((uint32_t)v) | ((uint64_t)uni((uint32_t)(v >> 32)) << 32);
+}
 // Wave reductions by DPP lane moves (no LDS round trip): within quads
 // (quad_perm [1,0,3,2] and [2,3,0,1]), across half-rows and rows
 // (row_half_mirror, row_mirror), then row 0 into 1 and 2 into 3
@@ -106,6 +109,17 @@ __device__ __forceinline__ uint64_t wor64(uint64_t v) {
 }
 __device__ __forceinline__ uint32_t wsum_u(uint32_t v) {
     return (uint32_t)wave_reduce_i((int)v, [](int a, int b) { return (int)((uint32_t)a + (uint32_t)b); });
+}
+// Sum over this lane and the lower ones (row_shr:1, 2, 4, 8, then the row
+// broadcasts).
+__device__ __forceinline__ uint32_t wscan_u(uint32_t v) {
+    v += (uint32_t)dpp<0x111, 0xF>(0, (int)v);
+    v += (uint32_t)dpp<0x112, 0xF>(0, (int)v);
+    v += (uint32_t)dpp<0x114, 0xF>(0, (int)v);
+    v += (uint32_t)dpp<0x118, 0xF>(0, (int)v);
+    v += (uint32_t)dpp<0x142, 0xA>(0, (int)v);
+    v += (uint32_t)dpp<0x143, 0xC>(0, (int)v);
+    return v;
 }
 template <int kCtrl, int kRows>
 __device__ __forceinline__ double dpp64(double v) {
