@@ -42,6 +42,15 @@ __device__ __forceinline__ uint32_t wrl(uint32_t x, int l, uint32_t v) {
 
 constexpr int kInfBits = 0x7F800000;
 
+// m without bit l, in one scalar instruction
+__device__ __forceinline__ uint64_t without(uint64_t m, int l) {
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(l));
+    return m;
+}
+
+// c ? a : b by value: the operator on two members selects between their
+// addresses, which can leave the whole cell in scratch memory
+__device__ __forceinline__ float pick(bool c, float a, float b) { return c ? a : b; }
 // The lanes of a uniform mask, as a condition: the mask is the execution or
 // carry mask itself, no shift per lane.
 __device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
@@ -137,7 +146,7 @@ struct Cell64 {
     // AABB of the cell and the squares of its sides (uniform, in vector
     // registers), and the vertex at each side
     float blo0, blo1, blo2, bhi0, bhi1, bhi2;
-    float hx2, hy2, hz2, lx2, ly2, lz2, rmax2;
+    float hx2, hy2, hz2, lx2, ly2, lz2, mx2, my2, mz2, rmax2, slack;
     uint32_t ext[6];
     uint64_t ext_mask, cut_mask;
     // queue: entry q in lane q (keys as ordered integers, infinite in the
@@ -216,15 +225,15 @@ struct Cell64 {
         in_vgpr(bhi0); in_vgpr(bhi1); in_vgpr(bhi2);
         hx2 = bhi0 * bhi0; hy2 = bhi1 * bhi1; hz2 = bhi2 * bhi2;
         lx2 = blo0 * blo0; ly2 = blo1 * blo1; lz2 = blo2 * blo2;
-        rmax2 = fmaxf(hx2, lx2) + fmaxf(hy2, ly2) + fmaxf(hz2, lz2);
+        mx2 = fmaxf(hx2, lx2); my2 = fmaxf(hy2, ly2); mz2 = fmaxf(hz2, lz2);
+        rmax2 = mx2 + my2 + mz2;
         ext_mask = 0;
 #pragma unroll
         for (int k = 0; k < 6; ++k) ext_mask |= 1ull << ext[k];
     }
     // A clip removes some vertices and adds new ones on edges it cuts, inside
     // the old cell: only the sides whose vertex it removed are reduced again.
-    __device__ void bounds_after_clip() {
-        if ((cut_mask & ext_mask) == 0) return;
+    __device__ void bounds_after_clip(uint64_t cut_mask) {
         const bool al = in_mask(alive);
         auto low = [&](int k, float y, float& b) {
             if (!((cut_mask >> ext[k]) & 1ull)) return;
@@ -278,19 +287,27 @@ struct Cell64 {
     // L of the current leaf: each edge from a kept to a removed vertex gets a
     // new vertex, and the new vertices find their neighbours around the new
     // facet through the table of their old planes.
-    __device__ int cut(uint64_t R, int L, float cax, float cay, float caz, float cb, float ax, float ay, float az,
-                       float b, int32_t hcode) {
-        if (np >= 64) {
-            gc();
-            if (np >= 64) return kOverflow;
-        }
-        const uint64_t kept = alive & ~R, f = ~alive | R;
-        const uint64_t m0 = ballot(((R >> byte_of(va, 0)) & 1ull) != 0) & kept;
-        const uint64_t m1 = ballot(((R >> byte_of(va, 1)) & 1ull) != 0) & kept;
-        const uint64_t m2 = ballot(((R >> byte_of(va, 2)) & 1ull) != 0) & kept;
-        const uint32_t m = (uint32_t)(popc(m0) + popc(m1) + popc(m2));
-        if (m == 0) return kRestart;  // vertices cut off, but no edge crosses the plane
-        if (m > (uint32_t)popc(f)) return kOverflow;
+    // cross() finds the edges, cut() does the work (returns false if the links
+    // are not one cycle: the cell is then built again from the start).
+    struct Cross {
+        uint64_t kept, f;     // vertices kept, free places
+        uint64_t m0, m1, m2;  // vertices whose first, second, third edge is crossed
+        uint32_t m;           // crossing edges
+    };
+    __device__ Cross cross(uint64_t R) const {
+        Cross c;
+        c.kept = alive & ~R;
+        c.f = ~alive | R;
+        c.m0 = ballot(((R >> byte_of(va, 0)) & 1ull) != 0) & c.kept;
+        c.m1 = ballot(((R >> byte_of(va, 1)) & 1ull) != 0) & c.kept;
+        c.m2 = ballot(((R >> byte_of(va, 2)) & 1ull) != 0) & c.kept;
+        c.m = (uint32_t)(popc(c.m0) + popc(c.m1) + popc(c.m2));
+        return c;
+    }
+    __device__ bool cut(const Cross& c, int L, float cax, float cay, float caz, float cb, float ax, float ay, float az,
+                        float b, int32_t hcode) {
+        const uint64_t kept = c.kept, f = c.f, m0 = c.m0, m1 = c.m1, m2 = c.m2;
+        const uint32_t m = c.m;
         // crossing edges ranked by vertex, then edge; the new vertex of rank k
         // takes the free slot of rank k
         auto count_below = [](uint64_t q, uint32_t base) {
@@ -305,45 +322,49 @@ struct Cell64 {
             serial = 1;
         }
         const uint32_t tag = serial << 12, me = tag | ln;
-        if (in_mask(nw)) M.c.sor[fr] = ln;
         // records (vertex, t[(e+2)%3], t[(e+1)%3]): permute selectors 0 = lane
         // number, 4..6 = bytes of vt, 0x0C = zero
         if (in_mask(m0)) M.c.edge[j0] = __builtin_amdgcn_perm(vt, ln, 0x0C050600u);
         if (in_mask(m1)) M.c.edge[j1] = __builtin_amdgcn_perm(vt, ln, 0x0C060400u);
         if (in_mask(m2)) M.c.edge[j2] = __builtin_amdgcn_perm(vt, ln, 0x0C040500u);
         sync();
-        uint32_t rec = 0, x = 0, y = 0;
+        // values of the lanes of nw, any in the others
+        uint32_t rec = __builtin_nondeterministic_value(ln), x = __builtin_nondeterministic_value(ln),
+                 y = __builtin_nondeterministic_value(ln), n1 = __builtin_nondeterministic_value(ln),
+                 n2 = __builtin_nondeterministic_value(ln), own1 = __builtin_nondeterministic_value(ln),
+                 own2 = __builtin_nondeterministic_value(ln);
         if (in_mask(nw)) {
             rec = M.c.edge[fr];
             x = byte_of(rec, 1);
             y = byte_of(rec, 2);
             M.c.tab[x].x = me;
             M.c.tab[y].y = me;
-        }
-        sync();
-        uint32_t n1 = 0, n2 = 0;
-        bool bad = false;
-        if (in_mask(nw)) {
+            M.c.sor[fr] = ln;
+            sync();
             const uint2 u = M.c.tab[x], w = M.c.tab[y];
+            own1 = u.x;
+            own2 = w.y;
             n1 = w.x ^ tag;  // the vertex itself where the tag is this clip's
             n2 = u.y ^ tag;
-            bad = u.x != me || w.y != me || max(n1, n2) > 63u;
-            // The links next (n1) and previous (n2) are then inverse
-            // permutations without fixed points, and have to be one cycle: up
-            // to five vertices they are unless two of them point at each other.
-            bad |= m >= 4u && n1 == n2;
         }
-        // m >= 6 with two vertices pointing at each other is no cycle either
-        if (ballot(bad)) return kRestart;
+        // The links next (n1) and previous (n2) are inverse permutations
+        // without fixed points where every entry is as written, and have to be
+        // one cycle: up to five vertices they are unless two of them point at
+        // each other (no cycle for six or more either).
+        const uint64_t bad = (ballot(own1 != me) | ballot(own2 != me) | ballot(max(n1, n2) > 63u) |
+                              (m >= 4u ? ballot(n1 == n2) : 0ull)) & nw;
+        bool whole = bad == 0;
         if (m >= 6u) {  // follow the links
             const uint32_t start = (uint32_t)lowest(nw);
             uint32_t v = start, steps = 0;
             do {
-                v = rdl(n1, (int)v);
+                v = rdl(n1, (int)v & 63);
                 ++steps;
             } while (v != start && steps <= m);
-            if (steps != m) return kRestart;
+            whole = whole && steps == m;
         }
+        // (a cell whose links are wrong is built again from the start: what
+        // follows does no harm to it and needs no branch)
         // kept vertices point at their new neighbours
         {
             const uint32_t s0 = M.c.sor[j0], s1 = M.c.sor[j1], s2 = M.c.sor[j2];
@@ -382,7 +403,7 @@ struct Cell64 {
         }
         np = (int)h + 1;
         sync();
-        return kChanged;
+        return whole;
     }
 
     // Drops planes no vertex uses (supplementary Sec. A, "Garbage
@@ -450,6 +471,7 @@ struct Cell64 {
             err = 0.f;
         }
         // per axis: the far-corner square of each side the box reaches
+        // (both sides: the larger one)
         const float tx = pmax(bhx >= 0.f ? hx2 : 0.f, blx < 0.f ? lx2 : 0.f);
         const float ty = pmax(bhy >= 0.f ? hy2 : 0.f, bly < 0.f ? ly2 : 0.f);
         const float tz = pmax(bhz >= 0.f ? hz2 : 0.f, blz < 0.f ? lz2 : 0.f);
@@ -465,7 +487,8 @@ struct Cell64 {
         if (qn < 64) {
             qe = wrl(e, qn, qe);
             qk = wrl(k, qn, qk);
-        } else {
+        }
+        if (qn >= 64) {
             if (ln == 0) {
                 M.c.qxe[qn - 64] = e;
                 M.c.qxk[qn - 64] = k;
@@ -479,46 +502,48 @@ struct Cell64 {
     __device__ void pop(uint32_t* e, int* k) {
         int bk = qk;
         int bs = 0;
-        for (int s = 1; s * 64 < qn; ++s) {
-            const int idx = s * 64 + (int)ln;
-            if (idx < qn) {
+        if (qn > 64) {
+            for (int s = 1; s * 64 < qn; ++s) {
+                const int idx = s * 64 + (int)ln;
                 const int kk = M.c.qxk[idx - 64];
-                if (kk < bk) {
-                    bk = kk;
-                    bs = s;
-                }
+                const bool less = idx < qn && kk < bk;
+                bk = less ? kk : bk;
+                bs = less ? s : bs;
             }
         }
         const int m = imin_wave(bk);
         uint64_t msk = ballot(bk == m);
-        if (qn < 64) msk &= (1ull << qn) - 1ull;
+        msk &= qn < 64 ? (1ull << qn) - 1ull : ~0ull;
         const int L = msk ? lowest(msk) : 0;
-        const int last = qn - 1;
         *k = m;
-        if (qn <= 64) {
-            *e = rdl(qe, L);
-            const uint32_t le = rdl(qe, last);
-            const int lk = rdl(qk, last);
-            qe = wrl(le, L, qe);
-            qk = wrl(lk, L, qk);
-            qk = wrl(kInfBits, last, qk);
-        } else {
+        // the last entry goes to lane L, its own lane is marked free; entries
+        // in LDS: lane L is rewritten (with what it holds when the popped one
+        // is in LDS itself)
+        int last = qn - 1;
+        *e = rdl(qe, L);
+        uint32_t le = rdl(qe, last & 63);
+        int lk = rdl(qk, last & 63), freed = kInfBits;
+        if (qn > 64) {
             const int S = rdl(bs, L);
-            const uint32_t le = uni(M.c.qxe[last - 64]);
-            const int lk = (int)uni((uint32_t)M.c.qxk[last - 64]);
-            if (S == 0) {
-                *e = rdl(qe, L);
-                qe = wrl(le, L, qe);
-                qk = wrl(lk, L, qk);
-            } else {
-                *e = uni(M.c.qxe[(S - 1) * 64 + L]);
+            le = uni(M.c.qxe[last - 64]);
+            lk = (int)uni((uint32_t)M.c.qxk[last - 64]);
+            if (S != 0) {
+                const uint32_t ee = uni(M.c.qxe[(S - 1) * 64 + L]);
                 if (ln == 0) {
                     M.c.qxe[(S - 1) * 64 + L] = le;
                     M.c.qxk[(S - 1) * 64 + L] = lk;
                 }
                 sync();
+                le = *e;
+                lk = rdl(qk, L);
+                *e = ee;
             }
+            last = L;
+            freed = lk;
         }
+        qe = wrl(le, L, qe);
+        qk = wrl(lk, L, qk);
+        qk = wrl(freed, last, qk);
         --qn;
     }
 
@@ -531,45 +556,77 @@ struct Cell64 {
         const float a2 = fmaf(ax, ax, fmaf(ay, ay, az * az));
         const float dw = kW ? pw - q.w : 0.f;
         const float b = 0.5f * (a2 + dw);
-        const bool cand = ln < nsite && j != self && q.w != -INFINITY && a2 > 0.f;
+        const uint64_t cand = ballot(ln < nsite) & ballot(j != self) & ballot(q.w != -INFINITY) & ballot(a2 > 0.f);
         const int key = key_bits(b * __builtin_amdgcn_rsqf(a2));  // orders candidates only
+        // Candidates whose plane misses the cell's AABB need no clip: the
+        // largest a.y over the box stays below b by more than the rounding of
+        // a vertex's side test.  Its terms sum to at most (a2 + rmax2) / 2 and
+        // |b| <= (a2 + |dw|) / 2, so 3 u (a2 + rmax2 / 2 + |dw| / 2) covers that
+        // test; ten times as much covers this one too, and splits into a part
+        // of the candidate and one of the box: 7 vector operations instead of
+        // 27 after every clip (a candidate kept in vain only costs its test).
+        const uint64_t sx = ballot(ax >= 0.f), sy = ballot(ay >= 0.f), sz = ballot(az >= 0.f);
+        const float least = b - 16.f * kU * (2.f * a2 + fabsf(dw));
         auto keep = [&]() -> bool {
-            // the plane misses the cell's AABB: max over the box of a.y <= b
-            const float cx = ax >= 0.f ? bhi0 : blo0, cy = ay >= 0.f ? bhi1 : blo1, cz = az >= 0.f ? bhi2 : blo2;
-            const float mm = fmaf(ax, cx, fmaf(ay, cy, az * cz));
-            const float slack = 8.f * kU * (fabsf(ax * cx) + fabsf(ay * cy) + fabsf(az * cz) + a2 + fabsf(dw));
-            return mm > b - slack;
+            const float cx = pick(in_mask(sx), bhi0, blo0), cy = pick(in_mask(sy), bhi1, blo1),
+                        cz = pick(in_mask(sz), bhi2, blo2);
+            return fmaf(ax, cx, fmaf(ay, cy, fmaf(az, cz, 16.f * kU * rmax2))) > least;
         };
-        uint64_t mask = ballot(keep()) & ballot(cand);
-        while (mask) {
-            int L = lowest(mask);
-            if (mask & (mask - 1ull)) {
-                const int kk = in_mask(mask) ? key : kInfBits;
-                const int mn = imin_wave(kk);
-                const uint64_t mm = ballot(kk == mn) & mask;
-                L = mm ? lowest(mm) : L;
+        uint64_t mask = ballot(keep()) & cand;
+        // Nearest plane first, equal ones by lane: each candidate counts those
+        // before it (3 vector operations a candidate), and the next one is
+        // found by one comparison (the least key left by a reduction over the
+        // wave took 12 for each).
+        uint32_t rank = 0;
+        if (mask & (mask - 1ull))
+            for (uint64_t u = mask; u;) {
+                const int l = lowest(u);
+                u = without(u, l);
+                rank += rdl(key, l) < key ? 1u : 0u;
             }
-            mask &= ~(1ull << L);
+        uint64_t next = 0;  // candidates of the least rank left
+        // How the last clip went.  Nothing leaves the loop but the end of its
+        // candidates, and no condition in it has two sides: around divergent
+        // code every such way is compiled to copies of the whole cell.
+        bool room = true, whole = true, gone = false;
+        uint32_t edges = 0;
+        uint64_t left = 0;  // the candidates not done
+        for (uint32_t at = 0; mask;) {
+            next &= mask;
+            for (; next == 0; ++at) next = ballot(rank == at) & mask;
+            const int L = lowest(next);
+            mask = without(mask, L);
             const float hx = rdl(ax, L), hy = rdl(ay, L), hz = rdl(az, L), hb = rdl(b, L);
             const float sv = fmaf(hx, y0, fmaf(hy, y1, fmaf(hz, y2, -hb)));
             const uint64_t R = ballot(sv > 0.f) & alive;
-            if (R == 0) continue;
-            if (R == alive) return kEmptied;
-            const int r = cut(R, L, ax, ay, az, b, hx, hy, hz, hb, (int32_t)j);
-            if (r != kChanged) {
-                if (r == kOverflow) {  // the cell is as before this candidate
-                    ov_ok = true;
-                    ov_leaf = ref;
-                    ov_mask = mask | (1ull << L);
-                    ov_phase = phase;
+            if (R != 0) {
+                if (np >= 64) gc();
+                const Cross c = cross(R);
+                // no edge crosses the plane, no place for the vertices or the plane
+                room = c.m - 1u < (uint32_t)popc(c.f) && np < 64;
+                left = mask | (1ull << L);
+                edges = c.m;
+                gone = R == alive;
+                mask = room ? mask : 0ull;
+                if (room) {
+                    whole = cut(c, L, ax, ay, az, b, hx, hy, hz, hb, (int32_t)j);
+                    if ((R & ext_mask) != 0) {
+                        bounds_after_clip(R);
+                        mask &= ballot(keep());
+                    }
+                    mask = whole ? mask : 0ull;
                 }
-                return r;
             }
-            cut_mask = R;
-            bounds_after_clip();
-            mask &= ballot(keep());
         }
-        return kNone;
+        if (!whole) return kRestart;
+        if (room) return kNone;
+        if (gone) return kEmptied;
+        if (edges == 0 && np < 64) return kRestart;  // vertices cut off, but no edge crosses the plane
+        ov_ok = true;  // the cell is as before this candidate
+        ov_leaf = ref;
+        ov_mask = left;
+        ov_phase = phase;
+        return kOverflow;
     }
 
     __device__ void load_child(uint32_t node, int s, NodeChild* c) const {
@@ -610,77 +667,88 @@ struct Cell64 {
         // every node is visited at most once in a valid tree; the bound only
         // guarantees termination if the tree were ever malformed
         int budget = (int)(4 * A.n + 1024);
-        for (uint32_t phase = 0;; phase = 1) {
-            const int r = leaf(cur, ns > 0 ? phase : 1u);
-            if (r != kNone) return r;
-            if (phase == 0) {
-                if (ns == 0) return kNone;  // the root is a leaf
+        // (one way out of each loop and conditions of one side, as in leaf())
+        int res = kNone;
+        bool more = true;  // something may still cut the cell
+        for (uint32_t phase = 0; more; phase = 1) {
+            res = leaf(cur, ns > 0 ? phase : 1u);
+            more = res == kNone && ns > 0;  // without siblings the root is a leaf
+            NodeChild c;
+            float key, delta;
+            bool cull;
+            if (more && phase == 0) {
                 // the siblings of the path, nearest last
-                NodeChild c;
                 load_child(path >> 1, (int)(path & 1), &c);
-                float key, delta;
-                bool cull;
                 node_test(c, &key, &cull, &delta);
                 const int kb = key_bits(fminf(key, INFINITY));
-                uint64_t live = ballot(!cull && (int)ln < ns);
+                uint64_t live = ballot(!cull) & ballot((int)ln < ns);
                 while (live) {
                     const int L = 63 - __builtin_clzll(live);
-                    live &= ~(1ull << L);
-                    if (!ball_lane(c, L)) continue;
-                    if (qn >= kQueue0) return kOverflow;
-                    push(rdl(path, L), rdl(kb, L));
+                    live = without(live, L);
+                    if (ball_lane(c, L)) {
+                        more = qn < kQueue0;
+                        live = more ? live : 0ull;
+                        if (more) push(rdl(path, L), rdl(kb, L));
+                    }
                 }
+                res = more ? (int)kNone : (int)kOverflow;
             }
             // the next leaf: pop, then descend into the nearer children
-            bool have = false;
-            while (!have) {
-                if (qn == 0) return kNone;
-                if (--budget < 0) return kOverflow;
-                uint32_t e;
-                int k;
-                pop(&e, &k);
-                if (key_value(k) > uni(__builtin_amdgcn_sqrtf(rmax2) * (1.f + 16.f * kU)))
-                    return kNone;  // every key left is at least this one: nothing can cut the cell
-                NodeChild c;
-                load_child(e >> 1, (int)(e & 1), &c);
-                float key, delta;
-                bool cull;
-                node_test(c, &key, &cull, &delta);
-                if (uni((uint32_t)cull) != 0 || !ball_all(c)) continue;
-                cur = uni(c.ref);
-                have = true;
-                while (!ref_is_leaf(cur)) {
-                    if (--budget < 0) return kOverflow;
-                    const uint32_t node = cur;
-                    load_child(node, (int)(ln & 1), &c);
-                    node_test(c, &key, &cull, &delta);
-                    const uint64_t cm = ballot(cull);
-                    if ((cm & 3ull) == 3ull) {
-                        have = false;
-                        break;
+            bool seek = more;
+            while (seek) {
+                more = qn != 0;
+                seek = false;
+                if (more) {
+                    uint32_t e;
+                    int k;
+                    pop(&e, &k);
+                    // every key left is at least this one: beyond the cell's radius nothing can cut it
+                    more = ballot(key_value(k) > __builtin_amdgcn_sqrtf(rmax2) * (1.f + 16.f * kU)) == 0;
+                    if (more) {
+                        load_child(e >> 1, (int)(e & 1), &c);
+                        node_test(c, &key, &cull, &delta);
+                        bool hit = ballot(cull) == 0;
+                        if (hit) hit = ball_all(c);
+                        cur = uni(c.ref);
+                        bool down = hit && !ref_is_leaf(cur);
+                        while (down) {
+                            const uint32_t node = cur;
+                            load_child(node, (int)(ln & 1), &c);
+                            node_test(c, &key, &cull, &delta);
+                            const uint64_t cm = ballot(cull);
+                            const float blx = c.lo[0] - px, bly = c.lo[1] - py, blz = c.lo[2] - pz;
+                            const float bhx = c.hi[0] - px, bhy = c.hi[1] - py, bhz = c.hi[2] - pz;
+                            uint64_t h0 = 0, h1 = 0;
+                            if (!(cm & 1ull))
+                                h0 = ballot(ball(of_even(blx), of_even(bly), of_even(blz), of_even(bhx), of_even(bhy),
+                                                 of_even(bhz), kW ? of_even(c.wmax) : 0.f)) & alive;
+                            if (!(cm & 2ull))
+                                h1 = ballot(ball(of_odd(blx), of_odd(bly), of_odd(blz), of_odd(bhx), of_odd(bhy),
+                                                 of_odd(bhz), kW ? of_odd(c.wmax) : 0.f)) & alive;
+                            hit = (h0 | h1) != 0;
+                            if (hit) {
+                                const uint64_t closer = ballot(rdl(delta, 0) <= rdl(delta, 1));  // child 0
+                                const uint64_t first = h0 == 0 ? 0ull : (h1 == 0 ? 1ull : closer);
+                                const int near = first != 0 ? 0 : 1;
+                                if (h0 != 0 && h1 != 0) {
+                                    more = qn < kQueue0;
+                                    if (more) push((node << 1) | (uint32_t)(1 - near), rdl(key_bits(fminf(key, INFINITY)), 1 - near));
+                                }
+                                cur = rdl(c.ref, near);
+                            }
+                            --budget;
+                            more &= budget >= 0;
+                            down = hit && more && !ref_is_leaf(cur);
+                        }
+                        --budget;
+                        more &= budget >= 0;
+                        res = more ? (int)kNone : (int)kOverflow;
+                        seek = more && !hit;
                     }
-                    const float blx = c.lo[0] - px, bly = c.lo[1] - py, blz = c.lo[2] - pz;
-                    const float bhx = c.hi[0] - px, bhy = c.hi[1] - py, bhz = c.hi[2] - pz;
-                    const bool c0 = (cm & 1ull) != 0 ||
-                                    (ballot(ball(of_even(blx), of_even(bly), of_even(blz), of_even(bhx), of_even(bhy),
-                                                 of_even(bhz), kW ? of_even(c.wmax) : 0.f)) & alive) == 0;
-                    const bool c1 = (cm & 2ull) != 0 ||
-                                    (ballot(ball(of_odd(blx), of_odd(bly), of_odd(blz), of_odd(bhx), of_odd(bhy),
-                                                 of_odd(bhz), kW ? of_odd(c.wmax) : 0.f)) & alive) == 0;
-                    if (c0 && c1) {
-                        have = false;
-                        break;
-                    }
-                    const float d0 = rdl(delta, 0), d1 = rdl(delta, 1);
-                    const int near = c1 ? 0 : (c0 ? 1 : (d0 <= d1 ? 0 : 1));
-                    if (!c0 && !c1) {
-                        if (qn >= kQueue0) return kOverflow;
-                        push((node << 1) | (uint32_t)(1 - near), rdl(key_bits(fminf(key, INFINITY)), 1 - near));
-                    }
-                    cur = rdl(c.ref, near);
                 }
             }
         }
+        return res;
     }
 
     // ------------------------------------------------------------ hand-over
@@ -781,7 +849,11 @@ struct Cell64 {
         }
         // facet ranks: ascending output code (box faces, then sites)
         uint32_t rank = 0;
-        for (uint64_t u = used; u; u &= u - 1ull) rank += rdl(out, lowest(u)) < out ? 1u : 0u;
+        for (uint64_t u = used; u;) {
+            const int l = lowest(u);
+            u = without(u, l);
+            rank += rdl(out, l) < out ? 1u : 0u;
+        }
         const int64_t base = (int64_t)slot * 64;
         if (in_mask(used)) ka->stage.code[base + rank] = out;
         M.f.rank[ln] = rank;
