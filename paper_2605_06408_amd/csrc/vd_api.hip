@@ -335,9 +335,16 @@ VD_API vd_status vd_build(vd_context* c, const float* xyz, const float* w, int64
     a.err = misc;
     a.retry_list = as<uint32_t>(c->lists[0]);
     a.retry_count = misc + 4;
-    // the options the 64-vertex pass of vd_clip64.hip is written for
-    const bool fast64 = o.precision == 1 && !o.perturb && !o.counters && o.culling == 3 && o.traversal == 1 &&
-                        o.warm_start == 0;
+    // The options the 64-vertex pass of vd_clip64.hip is written for.  With
+    // checked signs (mixed precision) it leaves the cells that meet a doubtful
+    // one, about one in fifty, to the general pass, which costs a launch that
+    // lasts as long as one cell takes alone: general pass alone against both,
+    // uniform, clustered with weights and surface sites: 0.45, 0.76 and 1.78
+    // ms against 0.50, 0.92 and 1.88 at 10k sites, 1.15, 2.24 and 4.03 against
+    // 0.92, 2.31 and 3.92 at 40k, 2.47, 6.58 and 7.40 against 1.68, 6.41 and
+    // 6.67 at 100k, 23.5, 28.4 and 46.3 against 14.2, 25.1 and 36.8 at 1M.
+    const bool fast64 = !o.perturb && !o.counters && o.culling == 3 && o.traversal == 1 && o.warm_start == 0 &&
+                        (o.precision == 1 || n >= 65536);
 
     // The clipping passes run back to back with no host synchronisation: the
     // larger passes are launched with persistent grids that read their cell

@@ -1,5 +1,6 @@
-// The 64-vertex pass with the default search options and FP32 predicates:
-// directional plus ball culling, best-first order, no warm start.  It builds
+// The 64-vertex pass with the default search options (directional plus ball
+// culling, best-first order, no warm start) and FP32 predicates, or, in
+// mixed precision, the cells whose signs FP32 can be sure of.  It builds
 // nearly every cell of a diagram, so it is written on its own: the cell
 // builder of vd_clip.hip with everything those options never reach taken
 // out, the same decisions in the same order (the arithmetic behind every
@@ -23,9 +24,12 @@
 // bytes (a permute builds or changes a record in one instruction), node
 // records passed on by lane moves inside the subtraction that uses them, and
 // the squared length of a vertex kept beside it.  Clustered 1M sites, against
-// the general pass: 8200 instead of 12150 vector and 6600 instead of 8800
-// scalar instructions a cell, 15 instead of 37 KB of code, 24.8 -> 14.8 ms;
-// a thousand sites 419 -> about 100 us.
+// the general pass as it was: 7500 instead of 12150 vector and 5600 instead
+// of 8800 scalar instructions a cell, 15 instead of 37 KB of code, 24.8 ->
+// 13.3 ms; a thousand sites 419 -> about 90 us.  Mixed precision, clustered
+// 333k: 8.0 -> 4.6 ms and 0.5 for the cells left to the general pass.  Both
+// the vector and the scalar unit are then near their limit (one instruction
+// in four cycles a SIMD, one a cycle a CU).
 #include "vd_wave.h"
 
 // v_writelane (the compiler has no builtin of that name): v with lane l
@@ -99,6 +103,7 @@ struct ClipMem {
     float4 pl[64];      // planes: a.xyz, b (frame of the site)
     uint2 tab[64];      // .x: new vertex by its first old plane, .y: by its second (serial tag above the index)
     int32_t pcode[64];  // Morton index of the plane's site, or box code -1..-6
+    float psb[64];      // size of the terms b is formed from (error scale; checked signs only)
     uint32_t sor[72];   // free slot of rank
     uint32_t edge[72];  // crossing edges by rank: kept vertex, the two planes, in bytes
     uint32_t qxe[kQueue0 - 64];
@@ -119,16 +124,24 @@ struct FinalMem {
     uint8_t next[256];    // 4 v + k -> the next vertex around facet k of v, with the facet's place there
     uint32_t fv[96];      // facet rings, two 16-bit vertex numbers a word
 };
-union WaveMem64 {
-    ClipMem c;
-    FinalMem f;
+struct WaveMem64 {
+    union {
+        ClipMem c;
+        FinalMem f;
+    };
+    // cells for the retry list, added to it 64 at a time: a lattice in mixed
+    // precision sends all of them there, and one addition to the list's
+    // counter each, 20 ns over the whole device, took more than the cells
+    uint32_t retry[64];
 };
 
 constexpr int kWaves64 = 4;  // waves per block
 
 #pragma clang attribute push(__attribute__((always_inline)), apply_to = function)
 
-template <bool kW>
+// kW: the sites carry weights.  kMixed: signs FP32 cannot be sure of are
+// looked for, and a cell that meets one goes on the retry list.
+template <bool kW, bool kMixed>
 struct Cell64 {
     WaveMem64& M;
     const ClipArgs& A;
@@ -140,15 +153,16 @@ struct Cell64 {
     // the vertex of this lane: position, its squared length, its three planes
     // and the three vertices across its edges (bytes; edge k leaves plane k)
     float y0, y1, y2, r2;
+    float ev;  // error scale of the vertex (checked signs only)
     uint32_t vt, va;
     uint64_t alive;
     int np;
     // AABB of the cell and the squares of its sides (uniform, in vector
     // registers), and the vertex at each side
     float blo0, blo1, blo2, bhi0, bhi1, bhi2;
-    float hx2, hy2, hz2, lx2, ly2, lz2, mx2, my2, mz2, rmax2, slack;
+    float hx2, hy2, hz2, lx2, ly2, lz2, rmax2;
     uint32_t ext[6];
-    uint64_t ext_mask, cut_mask;
+    uint64_t ext_mask;
     // queue: entry q in lane q (keys as ordered integers, infinite in the
     // lanes past the end), from 64 on in LDS
     uint32_t qe;
@@ -189,6 +203,7 @@ struct Cell64 {
             const float lo = ax == 0 ? lo0 : (ax == 1 ? lo1 : lo2), hi = ax == 0 ? hi0 : (ax == 1 ? hi1 : hi2);
             M.c.pl[ln] = make_float4(ax == 0 ? sg : 0.f, ax == 1 ? sg : 0.f, ax == 2 ? sg : 0.f, side ? hi : -lo);
             M.c.pcode[ln] = -(int)(ln + 1);
+            if constexpr (kMixed) M.c.psb[ln] = fabsf(side ? hi : -lo);
         }
         alive = 0xFFull;
         {
@@ -203,6 +218,7 @@ struct Cell64 {
             y1 = sy ? hi1 : lo1;
             y2 = sz ? hi2 : lo2;
             r2 = fmaf(y0, y0, fmaf(y1, y1, y2 * y2));
+            if constexpr (kMixed) ev = fabsf(y0) + fabsf(y1) + fabsf(y2);
         }
         np = 6;
         qn = 0;
@@ -225,8 +241,7 @@ struct Cell64 {
         in_vgpr(bhi0); in_vgpr(bhi1); in_vgpr(bhi2);
         hx2 = bhi0 * bhi0; hy2 = bhi1 * bhi1; hz2 = bhi2 * bhi2;
         lx2 = blo0 * blo0; ly2 = blo1 * blo1; lz2 = blo2 * blo2;
-        mx2 = fmaxf(hx2, lx2); my2 = fmaxf(hy2, ly2); mz2 = fmaxf(hz2, lz2);
-        rmax2 = mx2 + my2 + mz2;
+        rmax2 = fmaxf(hx2, lx2) + fmaxf(hy2, ly2) + fmaxf(hz2, lz2);
         ext_mask = 0;
 #pragma unroll
         for (int k = 0; k < 6; ++k) ext_mask |= 1ull << ext[k];
@@ -304,8 +319,8 @@ struct Cell64 {
         c.m = (uint32_t)(popc(c.m0) + popc(c.m1) + popc(c.m2));
         return c;
     }
-    __device__ bool cut(const Cross& c, int L, float cax, float cay, float caz, float cb, float ax, float ay, float az,
-                        float b, int32_t hcode) {
+    __device__ bool cut(const Cross& c, int L, float cax, float cay, float caz, float cb, float csb, float ax, float ay,
+                        float az, float b, float sbh, int32_t hcode) {
         const uint64_t kept = c.kept, f = c.f, m0 = c.m0, m1 = c.m1, m2 = c.m2;
         const uint32_t m = c.m;
         // crossing edges ranked by vertex, then edge; the new vertex of rank k
@@ -395,11 +410,18 @@ struct Cell64 {
             y1 = fmaf(Q.w, n21, fmaf(b, n01, P.w * n11)) * inv;
             y2 = fmaf(Q.w, n22, fmaf(b, n02, P.w * n12)) * inv;
             r2 = fmaf(y0, y0, fmaf(y1, y1, y2 * y2));
+            if constexpr (kMixed) {
+                const float t0 = fabsf(n00) + fabsf(n01) + fabsf(n02), t1 = fabsf(n10) + fabsf(n11) + fabsf(n12),
+                            t2 = fabsf(n20) + fabsf(n21) + fabsf(n22);
+                const float t = fmaf(t2, M.c.psb[y], fmaf(sbh, t0, M.c.psb[x] * t1));
+                ev = fabsf(y2) + (fabsf(y1) + fmaf(fabsf(inv), t, fabsf(y0)));
+            }
         }
         alive = kept | nw;
         if ((int)ln == L) {
             M.c.pl[h] = make_float4(cax, cay, caz, cb);
             M.c.pcode[h] = hcode;
+            if constexpr (kMixed) M.c.psb[h] = csb;
         }
         np = (int)h + 1;
         sync();
@@ -421,10 +443,12 @@ struct Cell64 {
         const uint32_t dst = mbcnt(u);
         const float4 p = M.c.pl[ln];
         const int32_t c = M.c.pcode[ln];
+        const float sb = kMixed ? M.c.psb[ln] : 0.f;
         sync();
         if (in_mask(u)) {
             M.c.pl[dst] = p;
             M.c.pcode[dst] = c;
+            if constexpr (kMixed) M.c.psb[dst] = sb;
             M.c.tab[ln].x = dst;
         }
         sync();
@@ -572,6 +596,8 @@ struct Cell64 {
                         cz = pick(in_mask(sz), bhi2, blo2);
             return fmaf(ax, cx, fmaf(ay, cy, fmaf(az, cz, 16.f * kU * rmax2))) > least;
         };
+        // for the doubtful-sign test
+        const float sbl = 0.5f * (a2 + fabsf(dw)), an1 = fabsf(ax) + fabsf(ay) + fabsf(az);
         uint64_t mask = ballot(keep()) & cand;
         // Nearest plane first, equal ones by lane: each candidate counts those
         // before it (3 vector operations a candidate), and the next one is
@@ -598,7 +624,15 @@ struct Cell64 {
             mask = without(mask, L);
             const float hx = rdl(ax, L), hy = rdl(ay, L), hz = rdl(az, L), hb = rdl(b, L);
             const float sv = fmaf(hx, y0, fmaf(hy, y1, fmaf(hz, y2, -hb)));
-            const uint64_t R = ballot(sv > 0.f) & alive;
+            uint64_t R = ballot(sv > 0.f) & alive;
+            float sbh = 0.f;
+            if constexpr (kMixed) {
+                sbh = rdl(sbl, L);
+                const float beta = 64.f * kU * fmaf(ev, rdl(an1, L), sbh);
+                whole = (ballot(fabsf(sv) <= beta) & alive) == 0;
+                mask = whole ? mask : 0ull;
+                R = whole ? R : 0ull;
+            }
             if (R != 0) {
                 if (np >= 64) gc();
                 const Cross c = cross(R);
@@ -609,7 +643,7 @@ struct Cell64 {
                 gone = R == alive;
                 mask = room ? mask : 0ull;
                 if (room) {
-                    whole = cut(c, L, ax, ay, az, b, hx, hy, hz, hb, (int32_t)j);
+                    whole = cut(c, L, ax, ay, az, b, sbl, hx, hy, hz, hb, sbh, (int32_t)j);
                     if ((R & ext_mask) != 0) {
                         bounds_after_clip(R);
                         mask &= ballot(keep());
@@ -767,13 +801,13 @@ struct Cell64 {
                 H.psite[ln] = site;
                 // size of the terms of b (read by builds with checked signs only)
                 const float a2 = fmaf(p.x, p.x, fmaf(p.y, p.y, p.z * p.z));
-                H.psb[ln] = c >= 0 ? 0.5f * (a2 + (kW ? fabsf(pw - site.w) : 0.f)) : fabsf(p.w);
+                H.psb[ln] = kMixed ? M.c.psb[ln] : c >= 0 ? 0.5f * (a2 + (kW ? fabsf(pw - site.w) : 0.f)) : fabsf(p.w);
                 H.pcode[ln] = c;
             }
             H.y0[ln] = y0;
             H.y1[ln] = y1;
             H.y2[ln] = y2;
-            H.ev[ln] = 0.f;  // written and read by builds with checked signs only
+            H.ev[ln] = kMixed ? ev : 0.f;  // read by builds with checked signs only
             H.vt[ln] = wide(vt);
             H.va[ln] = wide(va);
             H.qe[ln] = qe;
@@ -791,7 +825,7 @@ struct Cell64 {
             H.vhi = 64u;
             H.qn = (uint32_t)qn;
             H.flags = 0u;
-            H.robust = 0u;
+            H.robust = kMixed ? 1u : 0u;
             H.leaf = ov_leaf;
             H.mask = ov_mask;
             H.phase = ov_phase;
@@ -1019,11 +1053,23 @@ struct Cell64 {
     }
 };
 
-template <bool kW>
+__device__ void add_retries(WaveMem64& M, int count) {
+    KArgs* ka = cold_args();
+    const uint32_t ln = lane_id();
+    wave_sync<true>();
+    uint32_t at = 0;
+    if (ln == 0) at = atomicAdd(ka->retry_count, (uint32_t)count);
+    at = uni(at);
+    if ((int)ln < count) ka->retry_list[at + ln] = M.retry[ln];
+    wave_sync<true>();
+}
+
+template <bool kW, bool kMixed>
 __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
     if (*cold_args()->err != 0u) return;  // rejected input
-    Cell64<kW> C(M, A);
+    Cell64<kW, kMixed> C(M, A);
     unsigned long long st_empty = 0;
+    int waiting = 0;  // cells in M.retry
     Work<kWaves64> work((uint32_t)A.n);
     for (;;) {
         const uint32_t k = work.next(uni((uint32_t)threadIdx.x >> 6));
@@ -1038,8 +1084,11 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
             C.write_empty(orig);
             ++st_empty;
         } else if (res == kRestart) {
-            KArgs* kr = cold_args();
-            if (C.ln == 0) kr->retry_list[atomicAdd(kr->retry_count, 1u)] = k | (C.deep ? 0u : kRetryChecked);
+            if (C.ln == 0) M.retry[waiting] = k | (C.deep || kMixed ? 0u : kRetryChecked);
+            if (++waiting == 64) {
+                add_retries(M, waiting);
+                waiting = 0;
+            }
         } else if (res == kOverflow) {
             KArgs* kn = cold_args();
             uint32_t pos = 0;
@@ -1051,35 +1100,38 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
             if (pos < kn->hand_out_cap) C.save(static_cast<HandoffT<64, kQueue0>*>(kn->hand_out)[pos]);
         }
     }
+    if (waiting > 0) add_retries(M, waiting);
     if (C.ln == 0 && st_empty) atomicAdd(&cold_args()->stats[kStatEmpty], st_empty);
 }
 
 #pragma clang attribute pop
 
 // 72 registers for 7 waves per SIMD: the loops fit, finishing a cell spills a
-// few values.  A build of clustered 1M sites: 20.7 ms at 4 waves, 18.8 at 5,
-// 17.8 at 6, 17.2 at 7 and at 8 (64 registers, 44 spills).
-template <bool kW>
-__global__ __launch_bounds__(64 * kWaves64, 7) void k_clip64(ClipArgs A) {
+// few values.  A build of clustered 1M sites, as first written: 20.7 ms at 4
+// waves, 18.8 at 5, 17.8 at 6, 17.2 at 7 and at 8 (64 registers, 44 spills).
+// With checked signs, two more values a lane, 6 waves.
+template <bool kW, bool kMixed>
+__global__ __launch_bounds__(64 * kWaves64, kMixed ? 6 : 7) void k_clip64(ClipArgs A) {
     __shared__ WaveMem64 mem[kWaves64];
-    run_cells64<kW>(mem[threadIdx.x >> 6], A);
+    run_cells64<kW, kMixed>(mem[threadIdx.x >> 6], A);
+}
+
+template <bool kW, bool kMixed>
+hipError_t launch(const ClipArgs& a, int num_cu, hipStream_t s) {
+    int per_cu = 0;
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip64<kW, kMixed>, 64 * kWaves64, 0);
+    if (e != hipSuccess || per_cu < 1) per_cu = 4;
+    int64_t blocks = (a.n + kWaves64 - 1) / kWaves64;
+    if (blocks > (int64_t)per_cu * num_cu) blocks = (int64_t)per_cu * num_cu;
+    hipLaunchKernelGGL((k_clip64<kW, kMixed>), dim3((unsigned)blocks), dim3(64 * kWaves64), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_clip64(const ClipArgs& a, int num_cu, hipStream_t s) {
-    int per_cu = 0;
-    hipError_t e = a.weighted
-                       ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip64<true>, 64 * kWaves64, 0)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip64<false>, 64 * kWaves64, 0);
-    if (e != hipSuccess || per_cu < 1) per_cu = 4;
-    int64_t blocks = (a.n + kWaves64 - 1) / kWaves64;
-    if (blocks > (int64_t)per_cu * num_cu) blocks = (int64_t)per_cu * num_cu;
-    if (a.weighted)
-        hipLaunchKernelGGL(k_clip64<true>, dim3((unsigned)blocks), dim3(64 * kWaves64), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_clip64<false>, dim3((unsigned)blocks), dim3(64 * kWaves64), 0, s, a);
-    return hipGetLastError();
+    if (a.precision == 2) return a.weighted ? launch<true, true>(a, num_cu, s) : launch<false, true>(a, num_cu, s);
+    return a.weighted ? launch<true, false>(a, num_cu, s) : launch<false, false>(a, num_cu, s);
 }
 
 }  // namespace vd
