@@ -190,9 +190,9 @@ struct P64 {
 // perturbation (its own instantiation: the checked exact evaluation would
 // otherwise cost the default kernels registers).  kW: the sites carry
 // weights; kOpt: the search options (culling, traversal order, warm start)
-// are read at run time.  The 64- and 128-vertex passes of a build with the
-// default options run instantiations with those options fixed, and for an
-// unweighted build without the weight terms of the bounds and ball tests
+// are read at run time.  The passes of a build with the default options
+// run instantiations with those options fixed, the register passes of an
+// unweighted build also without the weight terms of the bounds and ball tests
 // (every weight is zero there): the same results bit for bit, 4% less time
 // for the fixed options (their checks and the scalar registers they held)
 // and 2.5% for the weight terms.  Every wave of a group
@@ -2683,22 +2683,22 @@ __global__ __launch_bounds__(64 * WAVES, VPL == 1 ? 4 : 2) void k_clip(ClipArgs 
 
 // 1024-vertex tier: the kGroupLds waves of a block build one cell, its
 // arrays in LDS (one block per CU).
-template <bool kCount, bool kSoS = false>
+template <bool kCount, bool kSoS, bool kOpt>
 __global__ __launch_bounds__(64 * kGroupLds, 1) void k_clip_lds(ClipArgs A) {
     __shared__ WaveMem<16> mem;
     __shared__ HotMem<16> hot;
     __shared__ uint32_t gx[2 * kGroupLds * 8];
-    run_cells<16, true, kCount, kGroupLds, kSoS>(mem, hot, A, gx);
+    run_cells<16, true, kCount, kGroupLds, kSoS, true, kOpt>(mem, hot, A, gx);
 }
 
 // 16384-vertex tier: the kGroupArena waves of a block build one cell, its
 // arrays in arena[blockIdx.x].
 constexpr int kArenaVPL = kTierCap[3] / 64;
-template <bool kCount, bool kSoS = false>
+template <bool kCount, bool kSoS, bool kOpt>
 __global__ __launch_bounds__(64 * kGroupArena) void k_clip_arena(ClipArgs A, WaveMem<kArenaVPL>* arena) {
     __shared__ HotMem<kArenaVPL> hot;
     __shared__ uint32_t gx[2 * kGroupArena * 8];
-    run_cells<kArenaVPL, false, kCount, kGroupArena, kSoS>(arena[blockIdx.x], hot, A, gx);
+    run_cells<kArenaVPL, false, kCount, kGroupArena, kSoS, true, kOpt>(arena[blockIdx.x], hot, A, gx);
 }
 
 static_assert(kTierCap[0] == 64 && kTierCap[1] == 128 && kTierCap[2] == 1024,
@@ -2733,7 +2733,7 @@ int clip_grid_workers(int tier, int num_cu) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip<2, kWaves2, false>, 64 * kWaves2, 0);
         per_cu *= kWaves2;
     } else if (tier == 2) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip_lds<false>, 64 * kGroupLds, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_clip_lds<false, false, true>, 64 * kGroupLds, 0);
         if (e == hipSuccess && per_cu > 0) return per_cu * num_cu;
         return num_cu;
     } else {
@@ -2745,32 +2745,40 @@ int clip_grid_workers(int tier, int num_cu) {
 
 template <bool kCount, bool kSoS>
 void launch_tier(const ClipArgs& a, int workers, void* arena, hipStream_t s) {
-    // the register passes have instantiations with the default search options fixed
+    // Instantiations with the default search options fixed, in the register
+    // passes also without weights (see Cell); in the large passes the code
+    // falls from 94 to 61 KB and from 124 to 78 (1024 vertices 6.6 -> 6.3 ms on
+    // 1M power sites).  Not in the register passes of perturbed builds: a
+    // lattice of 27k took 1.56 ms instead of 1.52.
     const bool def = a.culling == 3 && a.traversal == 1 && a.warm_start == 0;
+    auto* const ar = static_cast<WaveMem<kArenaVPL>*>(arena);
     switch (a.tier) {
-        case 0:
-            if (kSoS || !def)
-                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, kSoS>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
-            else if (a.weighted)
-                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, true, false>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
-            else
-                hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, false, false>), dim3((workers + kWaves1 - 1) / kWaves1), dim3(64 * kWaves1), 0, s, a);
+        case 0: {
+            const dim3 g((workers + kWaves1 - 1) / kWaves1), t(64 * kWaves1);
+            if (kSoS || !def) hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, kSoS>), g, t, 0, s, a);
+            else if (a.weighted) hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, true, false>), g, t, 0, s, a);
+            else hipLaunchKernelGGL((k_clip<1, kWaves1, kCount, false, false, false>), g, t, 0, s, a);
             break;
-        case 1:
-            if (kSoS || !def)
-                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, kSoS>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
-            else if (a.weighted)
-                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, true, false>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
-            else
-                hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, false, false>), dim3((workers + kWaves2 - 1) / kWaves2), dim3(64 * kWaves2), 0, s, a);
+        }
+        case 1: {
+            const dim3 g((workers + kWaves2 - 1) / kWaves2), t(64 * kWaves2);
+            if (kSoS || !def) hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, kSoS>), g, t, 0, s, a);
+            else if (a.weighted) hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, true, false>), g, t, 0, s, a);
+            else hipLaunchKernelGGL((k_clip<2, kWaves2, kCount, false, false, false>), g, t, 0, s, a);
             break;
-        case 2:
-            hipLaunchKernelGGL((k_clip_lds<kCount, kSoS>), dim3(workers), dim3(64 * kGroupLds), 0, s, a);
+        }
+        case 2: {
+            const dim3 g(workers), t(64 * kGroupLds);
+            if (!def) hipLaunchKernelGGL((k_clip_lds<kCount, kSoS, true>), g, t, 0, s, a);
+            else hipLaunchKernelGGL((k_clip_lds<kCount, kSoS, false>), g, t, 0, s, a);
             break;
-        default:
-            hipLaunchKernelGGL((k_clip_arena<kCount, kSoS>), dim3(workers), dim3(64 * kGroupArena), 0, s, a,
-                               static_cast<WaveMem<kArenaVPL>*>(arena));
+        }
+        default: {
+            const dim3 g(workers), t(64 * kGroupArena);
+            if (!def) hipLaunchKernelGGL((k_clip_arena<kCount, kSoS, true>), g, t, 0, s, a, ar);
+            else hipLaunchKernelGGL((k_clip_arena<kCount, kSoS, false>), g, t, 0, s, a, ar);
             break;
+        }
     }
 }
 
