@@ -183,7 +183,10 @@ def run_leg(name, xyz, w, box, kw, steps, warmup, label, verbose=False):
     # dominant kernel: the 64-vertex pass, priced with its own counters
     k_ms = float(np.mean(clip_ms))
     wk = w_alg(ctr["tier0"])
-    kernel = {"kernel": "k_clip<1, 4, ...> (64-vertex pass)", "kernel_ms": k_ms, "w_alg": wk,
+    # (k_clip64 and, for what it leaves, the general kernel of that pass)
+    default = all(kw.get(o, v) in (v, 0) for o, v in (("culling", 3), ("traversal", 1), ("warm_start", 0))) and \
+        not kw.get("perturb") and (kw.get("precision", 1) == 1 or n >= 65536)
+    kernel = {"kernel": "%s (64-vertex pass)" % ("k_clip64" if default else "k_clip<1, 4, ...>"), "kernel_ms": k_ms, "w_alg": wk,
               "achieved_Tops": wk / (k_ms * 1e-3) / 1e12, "frac": wk / (k_ms * 1e-3) / 1e12 / P_VALU_TOPS}
     # whole step
     W = w_alg(ctr["total"])

@@ -1825,10 +1825,10 @@ _Pragma("unroll")
             if (r == kChanged) {
                 bounds_after_clip();
                 mask &= ballot(keep(true));
-                // what the cut cell no longer meets needs no clip either
-                if constexpr (G > 1 || VPL >= 2) {
-                    if (mask && robust < 2) mask = cutting(mask, ax, ay, az, b, sbl);
-                }
+                // (the candidates left are not tested again: a new vertex can
+                // come out, by its rounding, on the far side of a plane that
+                // passes close to the cell, or in doubt of it, where no vertex
+                // was before, and what is decided of it then has to stay)
             }
         }
         return kNone;

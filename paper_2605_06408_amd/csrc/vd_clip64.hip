@@ -582,19 +582,16 @@ struct Cell64 {
         const float b = 0.5f * (a2 + dw);
         const uint64_t cand = ballot(ln < nsite) & ballot(j != self) & ballot(q.w != -INFINITY) & ballot(a2 > 0.f);
         const int key = key_bits(b * __builtin_amdgcn_rsqf(a2));  // orders candidates only
-        // Candidates whose plane misses the cell's AABB need no clip: the
-        // largest a.y over the box stays below b by more than the rounding of
-        // a vertex's side test.  Its terms sum to at most (a2 + rmax2) / 2 and
-        // |b| <= (a2 + |dw|) / 2, so 3 u (a2 + rmax2 / 2 + |dw| / 2) covers that
-        // test; ten times as much covers this one too, and splits into a part
-        // of the candidate and one of the box: 7 vector operations instead of
-        // 27 after every clip (a candidate kept in vain only costs its test).
+        // the plane misses the cell's AABB: max over the box of a.y <= b (with
+        // the very slack of the general pass: a vertex may lie outside the box
+        // by its rounding, so a candidate more or less could be a clip more)
         const uint64_t sx = ballot(ax >= 0.f), sy = ballot(ay >= 0.f), sz = ballot(az >= 0.f);
-        const float least = b - 16.f * kU * (2.f * a2 + fabsf(dw));
         auto keep = [&]() -> bool {
             const float cx = pick(in_mask(sx), bhi0, blo0), cy = pick(in_mask(sy), bhi1, blo1),
                         cz = pick(in_mask(sz), bhi2, blo2);
-            return fmaf(ax, cx, fmaf(ay, cy, fmaf(az, cz, 16.f * kU * rmax2))) > least;
+            const float mm = fmaf(ax, cx, fmaf(ay, cy, az * cz));
+            const float slack = 8.f * kU * (fabsf(ax * cx) + fabsf(ay * cy) + fabsf(az * cz) + a2 + fabsf(dw));
+            return mm > b - slack;
         };
         // for the doubtful-sign test
         const float sbl = 0.5f * (a2 + fabsf(dw)), an1 = fabsf(ax) + fabsf(ay) + fabsf(az);
