@@ -54,9 +54,10 @@ PEAK_HBM_GBS = 8000.0     # MI355X HBM3E
 # workload, each scaled by what the same counter reads for a plain 256 MiB
 # device copy in the same run.  Valid only while the kernel source is unchanged.
 TRAFFIC_MEASURED = {
-    "sources_sha1": {"paper_2605_06408_amd/csrc/vd_clip.hip": "8b7a529a5af7ea0e90c41faeb3f8d35f56feccdd",
-                     "paper_2605_06408_amd/csrc/vd_internal.h": "77d985737103a5e17fcf0f4b9b37769ea8224b30"},
-    "workload": "clustered_1m", "fetch_kib": 54281.5, "write_kib": 1088839.78125, "fetch_scale": 2.0,
+    "sources_sha1": {"paper_2605_06408_amd/csrc/vd_clip64.hip": "c634f9103c3c10c792bd9e3c7e070a61b357637a",
+                     "paper_2605_06408_amd/csrc/vd_wave.h": "ac131df0b58a94ed0ee41e359f23f2d971565ba1",
+                     "paper_2605_06408_amd/csrc/vd_internal.h": "570b642f00a26908eacd2b55d8c5c5620fcf83be"},
+    "workload": "clustered_1m", "fetch_kib": 175635.0625, "write_kib": 1414655.34375, "fetch_scale": 2.0,
     "write_scale": 1.0,
 }
 

@@ -1104,9 +1104,9 @@ struct Cell {
     // its tables in the arena in the 16384-vertex tier, and held every mask in
     // vector registers since nothing told the compiler that what waves
     // exchange is uniform.  Time of the passes, with the slots in registers
-    // and the candidates tested two at a time: 1024 vertices 9.9 -> 6.6 ms
-    // (351 cells of 1M power cells), 16384 vertices 9.0 -> 4.6 ms (one cell of
-    // 1452 vertices).
+    // and the candidates tested two at a time: 1024 vertices 9.9 -> 7 ms (351
+    // cells of 1M power cells), 16384 vertices 9.0 -> 4.6 ms (one cell of 1452
+    // vertices).
     __device__ int apply_group(Wave<uint64_t>& R, bool any, bool all, float ax, float ay, float az, float b, float sbh,
                                int32_t hcode, bool* consistent) {
         *consistent = true;

@@ -24,12 +24,12 @@
 // bytes (a permute builds or changes a record in one instruction), node
 // records passed on by lane moves inside the subtraction that uses them, and
 // the squared length of a vertex kept beside it.  Clustered 1M sites, against
-// the general pass as it was: 7500 instead of 12150 vector and 5600 instead
+// the general pass as it was: 7600 instead of 12150 vector and 5600 instead
 // of 8800 scalar instructions a cell, 15 instead of 37 KB of code, 24.8 ->
-// 13.3 ms; a thousand sites 419 -> about 90 us.  Mixed precision, clustered
-// 333k: 8.0 -> 4.6 ms and 0.5 for the cells left to the general pass.  Both
-// the vector and the scalar unit are then near their limit (one instruction
-// in four cycles a SIMD, one a cycle a CU).
+// 12.5 ms; a thousand sites 419 -> about 90 us.  Mixed precision, clustered
+// 333k: 8.0 -> 4.6 ms and 0.5 for the cells left to the general pass.  The
+// vector unit is then full (99% of one instruction in four cycles a SIMD) and
+// the scalar unit at 73% of one a cycle a CU.
 #include "vd_wave.h"
 
 // v_writelane (the compiler has no builtin of that name): v with lane l
