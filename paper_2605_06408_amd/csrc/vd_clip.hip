@@ -178,11 +178,6 @@ struct WaveMem : ArenaState<VPL>, QueueExt<VPL>, TableMem<VPL> {
     int32_t key[CAP];      // finalize and gc: output codes, used flags
 };
 
-// A plane in FP64, recomputed from the input coordinates.
-struct P64 {
-    double a0, a1, a2, b;
-};
-
 // kLds: the per-cell arrays are in LDS (else in global memory).  kCount:
 // count work units and cycles (a separate instantiation, so the timed
 // kernels carry no counting code).  G: waves building the cell together
@@ -604,8 +599,7 @@ struct Cell {
             float dz = fmaxf(fmaxf(lz - z_, z_ - hz), 0.f);
             float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
             float r2 = fmaf(x_, x_, fmaf(y_, y_, z_ * z_));
-            float lhs = d2 - wm, rhs = r2 - pwv();
-            hit |= ballot(lhs - rhs <= 16.f * kU * (d2 + r2 + fabsf(wm) + fabsf(pwv()))) & al_;
+            hit |= ballot(ball_test<kW>(d2, r2, wm, pwv())) & al_;
         });
         return g_or<1>(hit != 0 ? 1u : 0u) != 0;
     }
@@ -622,17 +616,17 @@ struct Cell {
         const float h1x = rdl(bhx, 1), h1y = rdl(bhy, 1), h1z = rdl(bhz, 1), w1 = kW ? rdl(c.wmax, 1) : 0.f;
         uint64_t a0 = 0, a1 = 0;
         VD_EACH_SLOT({
-            const float r2 = fmaf(x_, x_, fmaf(y_, y_, z_ * z_)), rhs = r2 - pwv(), tol = r2 + fabsf(pwv());
+            const float r2 = fmaf(x_, x_, fmaf(y_, y_, z_ * z_));
             float dx = fmaxf(fmaxf(l0x - x_, x_ - h0x), 0.f);
             float dy = fmaxf(fmaxf(l0y - y_, y_ - h0y), 0.f);
             float dz = fmaxf(fmaxf(l0z - z_, z_ - h0z), 0.f);
             float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            a0 |= ballot((d2 - w0) - rhs <= 16.f * kU * (d2 + tol + fabsf(w0))) & al_;
+            a0 |= ballot(ball_test<kW>(d2, r2, w0, pwv())) & al_;
             dx = fmaxf(fmaxf(l1x - x_, x_ - h1x), 0.f);
             dy = fmaxf(fmaxf(l1y - y_, y_ - h1y), 0.f);
             dz = fmaxf(fmaxf(l1z - z_, z_ - h1z), 0.f);
             d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            a1 |= ballot((d2 - w1) - rhs <= 16.f * kU * (d2 + tol + fabsf(w1))) & al_;
+            a1 |= ballot(ball_test<kW>(d2, r2, w1, pwv())) & al_;
         });
         const uint32_t r = g_or<2>((a0 != 0 ? 1u : 0u) | (a1 != 0 ? 2u : 0u));
         *hit0 = (r & 1u) != 0;
@@ -669,25 +663,14 @@ struct Cell {
         return r;
     }
 
-    // Intersection of three FP64 planes: numerator n and determinant (y = n / det).
-    __device__ static void cramer64(const P64& A0, const P64& B0, const P64& C0, double* n, double* det) {
-        double bc0 = B0.a1 * C0.a2 - B0.a2 * C0.a1, bc1 = B0.a2 * C0.a0 - B0.a0 * C0.a2,
-               bc2 = B0.a0 * C0.a1 - B0.a1 * C0.a0;
-        double ca0 = C0.a1 * A0.a2 - C0.a2 * A0.a1, ca1 = C0.a2 * A0.a0 - C0.a0 * A0.a2,
-               ca2 = C0.a0 * A0.a1 - C0.a1 * A0.a0;
-        double ab0 = A0.a1 * B0.a2 - A0.a2 * B0.a1, ab1 = A0.a2 * B0.a0 - A0.a0 * B0.a2,
-               ab2 = A0.a0 * B0.a1 - A0.a1 * B0.a0;
-        *det = A0.a0 * bc0 + A0.a1 * bc1 + A0.a2 * bc2;
-        n[0] = A0.b * bc0 + B0.b * ca0 + C0.b * ab0;
-        n[1] = A0.b * bc1 + B0.b * ca1 + C0.b * ab1;
-        n[2] = A0.b * bc2 + B0.b * ca2 + C0.b * ab2;
-    }
-
     // Side of the vertex with planes t w.r.t. plane h, recomputed in FP64 from
     // the input coordinates.  Returns +1 outside, -1 inside, 0 undecided.
     __device__ int side64(W t, const P64& h) const {
-        double n[3], det;
-        cramer64(plane64(T::fld(t, 0)), plane64(T::fld(t, 1)), plane64(T::fld(t, 2)), n, &det);
+        const P64 P = plane64(T::fld(t, 0)), Q = plane64(T::fld(t, 1)), S = plane64(T::fld(t, 2));
+        const Meet64 y(P, Q, S);
+        const double det = y.det;
+        double n[3];
+        y.numerator(P, Q, S, n);
         // s * det = a_h . n - b_h det, evaluated without dividing
         double s = h.a0 * n[0] + h.a1 * n[1] + h.a2 * n[2] - h.b * det;
         if (det < 0) s = -s;
@@ -813,7 +796,7 @@ struct Cell {
             const float sv = fmaf(ax, x_, fmaf(ay, y_, fmaf(az, z_, -b)));
             uint64_t r = ballot(sv > 0.f) & al_, am = 0;
             if (mode != 0) {
-                const float beta = 64.f * kU * (an1 * ev[s_] + sbh);
+                const float beta = doubt(an1, ev[s_], sbh);
                 am = mode == 3 ? al_ : ballot(fabsf(sv) <= beta) & al_;
                 if (mode == 2) r &= ~am;
             }
@@ -882,27 +865,13 @@ struct Cell {
     // Position and error scale of the vertex of planes (h, x, y), by Cramer's rule.
     __device__ void solve(uint32_t x, uint32_t y, float ax, float ay, float az, float b, float sbh, float* q0, float* q1,
                           float* q2, float* e) const {
-        float4 P = M.pl[x], Q = M.pl[y];
-        // n0 = a_x cross a_y, n1 = a_y cross a_h, n2 = a_h cross a_x
-        float n00 = P.y * Q.z - P.z * Q.y, n01 = P.z * Q.x - P.x * Q.z, n02 = P.x * Q.y - P.y * Q.x;
-        float n10 = Q.y * az - Q.z * ay, n11 = Q.z * ax - Q.x * az, n12 = Q.x * ay - Q.y * ax;
-        float n20 = ay * P.z - az * P.y, n21 = az * P.x - ax * P.z, n22 = ax * P.y - ay * P.x;
-        float det = fmaf(ax, n00, fmaf(ay, n01, az * n02));
-        // hardware reciprocal (1 ulp): the FP32 position only decides
-        // signs, within the error scale; outputs are recomputed in FP64
-        float inv = __builtin_amdgcn_rcpf(det);
-        *q0 = (b * n00 + P.w * n10 + Q.w * n20) * inv;
-        *q1 = (b * n01 + P.w * n11 + Q.w * n21) * inv;
-        *q2 = (b * n02 + P.w * n12 + Q.w * n22) * inv;
-        // error scale of the vertex, for the doubtful-sign test (only
-        // read when signs are checked: robust builds)
-        if (robust != 0) {
-            const float sbx = M.psb[x], sby = M.psb[y];
-            float s = (sbh * (fabsf(n00) + fabsf(n01) + fabsf(n02)) +
-                       sbx * (fabsf(n10) + fabsf(n11) + fabsf(n12)) +
-                       sby * (fabsf(n20) + fabsf(n21) + fabsf(n22))) * fabsf(inv);
-            *e = s + fabsf(*q0) + fabsf(*q1) + fabsf(*q2);
-        }
+        const Solve32 v(M.pl[x], M.pl[y], ax, ay, az, b);
+        *q0 = v.y0;
+        *q1 = v.y1;
+        *q2 = v.y2;
+        // error scale, for the doubtful-sign test (only read when signs are
+        // checked: robust builds)
+        if (robust != 0) *e = v.scale(sbh, M.psb[x], M.psb[y]);
     }
 
     // Tries the clip with the given outside masks; on an inconsistent
@@ -1497,34 +1466,11 @@ _Pragma("unroll")
         // hardware square roots (1 ulp), inside the bound's rounding margin
         float d = __builtin_amdgcn_sqrtf(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
         float dw = kW ? pw - c.wmax : 0.f;
-        float lb, err;
-        if (dw > 0.f && culling() == 3) {
-            // every site j in the box has b_j / |a_j| >= f(|a_j|) with
-            // f(t) = t/2 + dw/(2t), and |a_j| lies between the box's nearest
-            // and farthest distances: the bound is f at sqrt(dw) clamped to
-            // that range (the paper's bound keeps only dw < 0 and is d/2 here)
+        const float lbs = least_plane(d, dw, culling() == 3, [&] {
             const float fx = pmax(fabsf(blx), fabsf(bhx)), fy = pmax(fabsf(bly), fabsf(bhy)),
                         fz = pmax(fabsf(blz), fabsf(bhz));
-            const float dfar = __builtin_amdgcn_sqrtf(fmaf(fx, fx, fmaf(fy, fy, fz * fz)));
-            const float dc = fminf(fmaxf(__builtin_amdgcn_sqrtf(dw), d), dfar);
-            if (dc > 0.f) {
-                lb = 0.5f * dc + 0.5f * dw * __builtin_amdgcn_rcpf(dc);
-                err = lb;
-            } else {
-                lb = 0.5f * d;
-                err = 0.5f * d;
-            }
-        } else if (dw >= 0.f) {
-            lb = 0.5f * d;
-            err = 0.5f * d;
-        } else if (d > 0.f) {
-            const float q = 0.5f * dw * __builtin_amdgcn_rcpf(d);
-            lb = 0.5f * d + q;
-            err = 0.5f * d - q;
-        } else {
-            lb = -INFINITY;
-            err = 0.f;
-        }
+            return __builtin_amdgcn_sqrtf(fmaf(fx, fx, fmaf(fy, fy, fz * fz)));
+        });
         float rb2;
         if (culling() == 2) {
             rb2 = riso2;
@@ -1536,8 +1482,6 @@ _Pragma("unroll")
             rb2 = tx + ty + tz;
         }
         float rb = __builtin_amdgcn_sqrtf(rb2);
-        // lower bound made safe against FP32 rounding of its terms
-        float lbs = lb - 16.f * kU * err;
         *key = lbs;
         *cull = lbs > rb * (1.f + 16.f * kU);
         *delta = lbs - rb;
@@ -1735,8 +1679,8 @@ _Pragma("unroll")
                 const float qn1 = fabsf(q0) + fabsf(q1) + fabsf(q2), qs = rdl(sb, L1);
                 VD_EACH_SLOT({
                     const float e = ev[s_];
-                    o0 |= ballot(fmaf(p0, x_, fmaf(p1, y_, fmaf(p2, z_, -pb))) >= -64.f * kU * (pn * e + ps)) & al_;
-                    o1 |= ballot(fmaf(q0, x_, fmaf(q1, y_, fmaf(q2, z_, -qb))) >= -64.f * kU * (qn1 * e + qs)) & al_;
+                    o0 |= ballot(fmaf(p0, x_, fmaf(p1, y_, fmaf(p2, z_, -pb))) >= -doubt(pn, e, ps)) & al_;
+                    o1 |= ballot(fmaf(q0, x_, fmaf(q1, y_, fmaf(q2, z_, -qb))) >= -doubt(qn1, e, qs)) & al_;
                 });
             }
             cut |= (o0 != 0 ? 1ull << L0 : 0ull) | (o1 != 0 ? 1ull << L1 : 0ull);
@@ -1783,9 +1727,7 @@ _Pragma("unroll")
             if (culling() == 3) {
                 // the plane misses the cell's AABB: max over the box of a.y <= b
                 float cx = ax >= 0.f ? bhi0 : blo0, cy = ay >= 0.f ? bhi1 : blo1, cz = az >= 0.f ? bhi2 : blo2;
-                float mm = fmaf(ax, cx, fmaf(ay, cy, az * cz));
-                float slack = 8.f * kU * (fabsf(ax * cx) + fabsf(ay * cy) + fabsf(az * cz) + a2 + fabsf(dw));
-                return mm > b - slack;
+                return reaches(ax, ay, az, b, cx, cy, cz, a2, dw);
             }
             float r2 = radius2_toward(ax, ay, az);
             float t = b - 4.f * kU * (2.f * a2 + fabsf(dw) + r2);
@@ -2286,10 +2228,12 @@ _Pragma("unroll")
     // ------------------------------------------------------------ output
     // FP64 position of a vertex (relative to the site) from its three planes.
     __device__ void pos64(W t, float fx, float fy, float fz, double* y) const {
-        double n[3], det;
-        cramer64(plane64(T::fld(t, 0)), plane64(T::fld(t, 1)), plane64(T::fld(t, 2)), n, &det);
-        if (det != 0.0) {
-            double inv = 1.0 / det;
+        const P64 P = plane64(T::fld(t, 0)), Q = plane64(T::fld(t, 1)), S = plane64(T::fld(t, 2));
+        const Meet64 m(P, Q, S);
+        if (m.det != 0.0) {
+            double n[3];
+            m.numerator(P, Q, S, n);
+            const double inv = 1.0 / m.det;
             y[0] = n[0] * inv; y[1] = n[1] * inv; y[2] = n[2] * inv;
         } else {
             y[0] = fx; y[1] = fy; y[2] = fz;
@@ -2463,7 +2407,7 @@ _Pragma("unroll")
         if (ballot(bad)) return false;
         // volume and centroid from the tetrahedra (ref, anchor_f, v, next_f(v)),
         // accumulated in FP64 (thin cells cancel badly in FP32)
-        double vol6 = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
+        Fan64 sum;
         for (uint32_t v = ln; v < nv; v += 64) {
             const double Px = M.vpx[v], Py = M.vpy[v], Pz = M.vpz[v];
             W tri = M.vtri[v], adj = M.vadj[v];
@@ -2474,19 +2418,10 @@ _Pragma("unroll")
                 if (an == v || nx == an) continue;
                 const double Qx = M.vpx[an], Qy = M.vpy[an], Qz = M.vpz[an];
                 const double Nx = M.vpx[nx], Ny = M.vpy[nx], Nz = M.vpz[nx];
-                // det(anchor, v, next) relative to the reference vertex
-                double cx = Py * Nz - Pz * Ny, cy = Pz * Nx - Px * Nz, cz = Px * Ny - Py * Nx;
-                double det = Qx * cx + Qy * cy + Qz * cz;
-                vol6 += det;
-                mx += det * (Qx + Px + Nx);
-                my += det * (Qy + Py + Ny);
-                mz += det * (Qz + Pz + Nz);
+                sum.add(Qx, Qy, Qz, Px, Py, Pz, Nx, Ny, Nz);
             }
         }
-        vol6 = wsum64(vol6);
-        mx = wsum64(mx);
-        my = wsum64(my);
-        mz = wsum64(mz);
+        const double vol6 = wsum64(sum.vol6), mx = wsum64(sum.mx), my = wsum64(sum.my), mz = wsum64(sum.mz);
         uint32_t nbox = 0;
         for (int q = ln; q < F; q += 64) nbox += M.key[q] < 0 ? 1u : 0u;
         nbox = wsum_u(nbox);
@@ -2498,9 +2433,9 @@ _Pragma("unroll")
             ka->cnt_n[orig] = (uint32_t)F - nbox;
             ka->vol[orig] = (float)(vol6 / 6.0);
             double inv = vol6 != 0.0 ? 0.25 / vol6 : 0.0;
-            ka->cen[3 * orig] = (float)(p64[0] + ref[0] + mx * inv);
-            ka->cen[3 * orig + 1] = (float)(p64[1] + ref[1] + my * inv);
-            ka->cen[3 * orig + 2] = (float)(p64[2] + ref[2] + mz * inv);
+            ka->cen[3 * orig] = centroid_of(px, ref[0], mx, inv);
+            ka->cen[3 * orig + 1] = centroid_of(py, ref[1], my, inv);
+            ka->cen[3 * orig + 2] = centroid_of(pz, ref[2], mz, inv);
             ka->flags[orig] = (uint8_t)flags;
             ka->loc[self] = make_loc((uint32_t)A.tier, slot);
         }

@@ -4,8 +4,8 @@
 // nearly every cell of a diagram, so it is written on its own: the cell
 // builder of vd_clip.hip with everything those options never reach taken
 // out, the same decisions in the same order (the arithmetic behind every
-// decision is that of vd_clip.hip to the last bit, so both give the same
-// cells, vertex order included).
+// decision is that of vd_wave.h in both, so both give the same cells, vertex
+// order included).
 //
 // A cell this pass cannot finish goes elsewhere: one that outgrows 64
 // vertices is handed on with its state (HandoffT) to the 128-vertex pass;
@@ -96,9 +96,6 @@ __device__ __forceinline__ double rdl64(double v, int l) {
 // the first 64.  While it is finished (the planes' codes are read first, the
 // queue is empty): FP64 planes, then vertex positions in their place, and
 // the facet tables.
-struct PlaneD {
-    double a0, a1, a2, b;
-};
 struct ClipMem {
     float4 pl[64];      // planes: a.xyz, b (frame of the site)
     uint2 tab[64];      // .x: new vertex by its first old plane, .y: by its second (serial tag above the index)
@@ -111,7 +108,7 @@ struct ClipMem {
 };
 struct FinalMem {
     union {
-        PlaneD pd[64];
+        P64 pd[64];
         struct {
             double x[64], y[64], z[64];  // by vertex number, relative to vertex 0
         } v;
@@ -277,12 +274,7 @@ struct Cell64 {
         const float dy = fmaxf(fmaxf(ly - y1, y1 - hy), 0.f);
         const float dz = fmaxf(fmaxf(lz - y2, y2 - hz), 0.f);
         const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        if constexpr (kW) {
-            const float rhs = r2 - pw, tol = r2 + fabsf(pw);
-            return (d2 - wm) - rhs <= 16.f * kU * (d2 + tol + fabsf(wm));
-        } else {
-            return d2 - r2 <= 16.f * kU * (d2 + r2);
-        }
+        return ball_test<kW>(d2, r2, wm, pwv());
     }
     // of the box held by lane l
     __device__ bool ball_lane(const NodeChild& c, int l) const {
@@ -396,26 +388,12 @@ struct Cell64 {
             vt = (rec & 0xFFFF00u) | h;
             va = (rec & 0xFFu) | (n1 << 8) | (n2 << 16);
             const float4 P = M.c.pl[x], Q = M.c.pl[y];
-            // a_x cross a_y, a_y cross a_h, a_h cross a_x (fused in the order
-            // the general pass is compiled to: the signs have to agree)
-            const float n00 = fmaf(P.y, Q.z, -(P.z * Q.y)), n01 = fmaf(P.z, Q.x, -(P.x * Q.z)),
-                        n02 = fmaf(P.x, Q.y, -(P.y * Q.x));
-            const float n10 = fmaf(Q.y, az, -(Q.z * ay)), n11 = fmaf(Q.z, ax, -(Q.x * az)),
-                        n12 = fmaf(Q.x, ay, -(Q.y * ax));
-            const float n20 = fmaf(ay, P.z, -(az * P.y)), n21 = fmaf(az, P.x, -(ax * P.z)),
-                        n22 = fmaf(ax, P.y, -(ay * P.x));
-            const float det = fmaf(ax, n00, fmaf(ay, n01, az * n02));
-            const float inv = __builtin_amdgcn_rcpf(det);
-            y0 = fmaf(Q.w, n20, fmaf(b, n00, P.w * n10)) * inv;
-            y1 = fmaf(Q.w, n21, fmaf(b, n01, P.w * n11)) * inv;
-            y2 = fmaf(Q.w, n22, fmaf(b, n02, P.w * n12)) * inv;
+            const Solve32 s(P, Q, ax, ay, az, b);
+            y0 = s.y0;
+            y1 = s.y1;
+            y2 = s.y2;
             r2 = fmaf(y0, y0, fmaf(y1, y1, y2 * y2));
-            if constexpr (kMixed) {
-                const float t0 = fabsf(n00) + fabsf(n01) + fabsf(n02), t1 = fabsf(n10) + fabsf(n11) + fabsf(n12),
-                            t2 = fabsf(n20) + fabsf(n21) + fabsf(n22);
-                const float t = fmaf(t2, M.c.psb[y], fmaf(sbh, t0, M.c.psb[x] * t1));
-                ev = fabsf(y2) + (fabsf(y1) + fmaf(fabsf(inv), t, fabsf(y0)));
-            }
+            if constexpr (kMixed) ev = s.scale(sbh, M.c.psb[x], M.c.psb[y]);
         }
         alive = kept | nw;
         if ((int)ln == L) {
@@ -469,39 +447,17 @@ struct Cell64 {
         // hardware square roots (1 ulp), inside the bound's rounding margin
         float d = __builtin_amdgcn_sqrtf(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
         float dw = kW ? pw - c.wmax : 0.f;
-        float lb, err;
-        if (dw > 0.f) {
-            // least value of t/2 + dw/(2t) over the distances t from p_i to the box
+        const float lbs = least_plane(d, dw, true, [&] {
             const float fx = pmax(fabsf(blx), fabsf(bhx)), fy = pmax(fabsf(bly), fabsf(bhy)),
                         fz = pmax(fabsf(blz), fabsf(bhz));
-            const float dfar = __builtin_amdgcn_sqrtf(fmaf(fx, fx, fmaf(fy, fy, fz * fz)));
-            const float dc = fminf(fmaxf(__builtin_amdgcn_sqrtf(dw), d), dfar);
-            if (dc > 0.f) {
-                lb = 0.5f * dc + 0.5f * dw * __builtin_amdgcn_rcpf(dc);
-                err = lb;
-            } else {
-                lb = 0.5f * d;
-                err = 0.5f * d;
-            }
-        } else if (dw >= 0.f) {
-            lb = 0.5f * d;
-            err = 0.5f * d;
-        } else if (d > 0.f) {
-            const float q = 0.5f * dw * __builtin_amdgcn_rcpf(d);
-            lb = 0.5f * d + q;
-            err = 0.5f * d - q;
-        } else {
-            lb = -INFINITY;
-            err = 0.f;
-        }
+            return __builtin_amdgcn_sqrtf(fmaf(fx, fx, fmaf(fy, fy, fz * fz)));
+        });
         // per axis: the far-corner square of each side the box reaches
         // (both sides: the larger one)
         const float tx = pmax(bhx >= 0.f ? hx2 : 0.f, blx < 0.f ? lx2 : 0.f);
         const float ty = pmax(bhy >= 0.f ? hy2 : 0.f, bly < 0.f ? ly2 : 0.f);
         const float tz = pmax(bhz >= 0.f ? hz2 : 0.f, blz < 0.f ? lz2 : 0.f);
         float rb = __builtin_amdgcn_sqrtf(tx + ty + tz);
-        // lower bound made safe against FP32 rounding of its terms
-        float lbs = lb - 16.f * kU * err;
         *key = lbs;
         *cull = lbs > rb * (1.f + 16.f * kU);
         *delta = lbs - rb;
@@ -589,9 +545,7 @@ struct Cell64 {
         auto keep = [&]() -> bool {
             const float cx = pick(in_mask(sx), bhi0, blo0), cy = pick(in_mask(sy), bhi1, blo1),
                         cz = pick(in_mask(sz), bhi2, blo2);
-            const float mm = fmaf(ax, cx, fmaf(ay, cy, az * cz));
-            const float slack = 8.f * kU * (fabsf(ax * cx) + fabsf(ay * cy) + fabsf(az * cz) + a2 + fabsf(dw));
-            return mm > b - slack;
+            return reaches(ax, ay, az, b, cx, cy, cz, a2, dw);
         };
         // for the doubtful-sign test
         const float sbl = 0.5f * (a2 + fabsf(dw)), an1 = fabsf(ax) + fabsf(ay) + fabsf(az);
@@ -625,7 +579,7 @@ struct Cell64 {
             float sbh = 0.f;
             if constexpr (kMixed) {
                 sbh = rdl(sbl, L);
-                const float beta = 64.f * kU * fmaf(ev, rdl(an1, L), sbh);
+                const float beta = doubt(rdl(an1, L), ev, sbh);
                 whole = (ballot(fabsf(sv) <= beta) & alive) == 0;
                 mask = whole ? mask : 0ull;
                 R = whole ? R : 0ull;
@@ -859,7 +813,7 @@ struct Cell64 {
         // FP64 planes from the input coordinates
         const double qx = px, qy = py, qz = pz;
         if (in_mask(used)) {
-            PlaneD d;
+            P64 d;
             if (code < 0) {
                 const int ax = (-code - 1) >> 1;
                 const bool side = ((-code - 1) & 1) != 0;
@@ -900,19 +854,15 @@ struct Cell64 {
         }
         double Y0 = 0.0, Y1 = 0.0, Y2 = 0.0;
         if (al) {
-            const PlaneD P = M.f.pd[byte_of(vt, 0)], Q = M.f.pd[byte_of(vt, 1)], S = M.f.pd[byte_of(vt, 2)];
-            const double bc0 = Q.a1 * S.a2 - Q.a2 * S.a1, bc1 = Q.a2 * S.a0 - Q.a0 * S.a2,
-                         bc2 = Q.a0 * S.a1 - Q.a1 * S.a0;
-            const double ca0 = S.a1 * P.a2 - S.a2 * P.a1, ca1 = S.a2 * P.a0 - S.a0 * P.a2,
-                         ca2 = S.a0 * P.a1 - S.a1 * P.a0;
-            const double ab0 = P.a1 * Q.a2 - P.a2 * Q.a1, ab1 = P.a2 * Q.a0 - P.a0 * Q.a2,
-                         ab2 = P.a0 * Q.a1 - P.a1 * Q.a0;
-            const double det = P.a0 * bc0 + P.a1 * bc1 + P.a2 * bc2;
-            if (det != 0.0) {
-                const double inv = 1.0 / det;
-                Y0 = (P.b * bc0 + Q.b * ca0 + S.b * ab0) * inv;
-                Y1 = (P.b * bc1 + Q.b * ca1 + S.b * ab1) * inv;
-                Y2 = (P.b * bc2 + Q.b * ca2 + S.b * ab2) * inv;
+            const P64 P = M.f.pd[byte_of(vt, 0)], Q = M.f.pd[byte_of(vt, 1)], S = M.f.pd[byte_of(vt, 2)];
+            const Meet64 y(P, Q, S);
+            if (y.det != 0.0) {
+                double n[3];
+                y.numerator(P, Q, S, n);
+                const double inv = 1.0 / y.det;
+                Y0 = n[0] * inv;
+                Y1 = n[1] * inv;
+                Y2 = n[2] * inv;
             } else {
                 Y0 = y0;
                 Y1 = y1;
@@ -997,7 +947,7 @@ struct Cell64 {
         }
         // volume and centroid from the tetrahedra (ref, anchor_f, v, next_f(v)),
         // in FP64 (thin cells cancel badly in FP32)
-        double vol6 = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
+        Fan64 sum;
         if (al) {
             uint32_t f = tri, nx3 = adj >> 8 | (adj << 16);  // the facet and the next vertex around it in the low bytes
 #pragma unroll 1
@@ -1006,18 +956,10 @@ struct Cell64 {
                 if (an == v || nx == an) continue;
                 const double Qx = M.f.v.x[an], Qy = M.f.v.y[an], Qz = M.f.v.z[an];
                 const double Nx = M.f.v.x[nx], Ny = M.f.v.y[nx], Nz = M.f.v.z[nx];
-                const double cx = X1 * Nz - X2 * Ny, cy = X2 * Nx - X0 * Nz, cz = X0 * Ny - X1 * Nx;
-                const double det = Qx * cx + Qy * cy + Qz * cz;
-                vol6 += det;
-                mx += det * (Qx + X0 + Nx);
-                my += det * (Qy + X1 + Ny);
-                mz += det * (Qz + X2 + Nz);
+                sum.add(Qx, Qy, Qz, X0, X1, X2, Nx, Ny, Nz);
             }
         }
-        vol6 = wsum64(vol6);
-        mx = wsum64(mx);
-        my = wsum64(my);
-        mz = wsum64(mz);
+        const double vol6 = wsum64(sum.vol6), mx = wsum64(sum.mx), my = wsum64(sum.my), mz = wsum64(sum.mz);
         const uint32_t nbox = (uint32_t)popc(ballot(code < 0) & used);
         if (ln == 0) {
             ka->cnt_v[orig] = (uint32_t)nv;
@@ -1025,9 +967,9 @@ struct Cell64 {
             ka->cnt_n[orig] = (uint32_t)F - nbox;
             ka->vol[orig] = (float)(vol6 / 6.0);
             const double inv = vol6 != 0.0 ? 0.25 / vol6 : 0.0;
-            ka->cen[3 * orig] = (float)((double)sx + R0 + mx * inv);
-            ka->cen[3 * orig + 1] = (float)((double)sy + R1 + my * inv);
-            ka->cen[3 * orig + 2] = (float)((double)sz0 + R2 + mz * inv);
+            ka->cen[3 * orig] = centroid_of(sx, R0, mx, inv);
+            ka->cen[3 * orig + 1] = centroid_of(sy, R1, my, inv);
+            ka->cen[3 * orig + 2] = centroid_of(sz0, R2, mz, inv);
             ka->flags[orig] = 0;
             ka->loc[self] = make_loc(0u, slot);
         }

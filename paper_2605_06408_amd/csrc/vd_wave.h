@@ -227,6 +227,141 @@ struct Work {
     }
 };
 
+// ---------------------------------------------------------------- arithmetic
+// What decides signs, orders candidates and makes the outputs, for every
+// clipping pass.  The passes have to agree to the last bit (a cell may be
+// begun in one and finished in another, and which of the two 64-vertex kernels
+// builds a cell must not show).  No rounding of what decides is left to the
+// compiler: in the FP32 functions products and sums are fused where fma is
+// written and nowhere else.  The FP64 ones make outputs only, or signs that
+// are held against a bound far above their rounding.
+
+// Intersection of the planes h (a, b), P and Q by Cramer's rule, in FP32.
+struct Solve32 {
+    float y0, y1, y2, inv;
+    float t0, t1, t2;  // absolute sums of the minors, for the error scale
+    __device__ __forceinline__ Solve32(float4 P, float4 Q, float ax, float ay, float az, float b) {
+#pragma clang fp contract(off)
+        // a_P cross a_Q, a_Q cross a_h, a_h cross a_P
+        const float n00 = fmaf(P.y, Q.z, -(P.z * Q.y)), n01 = fmaf(P.z, Q.x, -(P.x * Q.z)),
+                    n02 = fmaf(P.x, Q.y, -(P.y * Q.x));
+        const float n10 = fmaf(Q.y, az, -(Q.z * ay)), n11 = fmaf(Q.z, ax, -(Q.x * az)),
+                    n12 = fmaf(Q.x, ay, -(Q.y * ax));
+        const float n20 = fmaf(ay, P.z, -(az * P.y)), n21 = fmaf(az, P.x, -(ax * P.z)),
+                    n22 = fmaf(ax, P.y, -(ay * P.x));
+        const float det = fmaf(ax, n00, fmaf(ay, n01, az * n02));
+        // hardware reciprocal (1 ulp): the FP32 position only decides signs,
+        // within the error scale; outputs are recomputed in FP64
+        inv = __builtin_amdgcn_rcpf(det);
+        y0 = fmaf(Q.w, n20, fmaf(b, n00, P.w * n10)) * inv;
+        y1 = fmaf(Q.w, n21, fmaf(b, n01, P.w * n11)) * inv;
+        y2 = fmaf(Q.w, n22, fmaf(b, n02, P.w * n12)) * inv;
+        t0 = fabsf(n00) + fabsf(n01) + fabsf(n02);
+        t1 = fabsf(n10) + fabsf(n11) + fabsf(n12);
+        t2 = fabsf(n20) + fabsf(n21) + fabsf(n22);
+    }
+    // Error scale of the vertex; sbh, sbp, sbq: sizes of the terms of b.
+    __device__ __forceinline__ float scale(float sbh, float sbp, float sbq) const {
+#pragma clang fp contract(off)
+        const float t = fmaf(t2, sbq, fmaf(sbh, t0, sbp * t1));
+        return fabsf(y2) + (fabsf(y1) + fmaf(fabsf(inv), t, fabsf(y0)));
+    }
+};
+// A side test of size below this is doubtful: an1 the absolute sum of the
+// plane's normal, sb the size of the terms of its b, e the vertex's error scale.
+__device__ __forceinline__ float doubt(float an1, float e, float sb) {
+#pragma clang fp contract(off)
+    return 64.f * kU * fmaf(an1, e, sb);
+}
+// Some point of the cell's AABB may be beyond the plane; c its corner farthest
+// along a, a2 = |a|^2, dw the difference of the weights.
+__device__ __forceinline__ bool reaches(float ax, float ay, float az, float b, float cx, float cy, float cz, float a2,
+                                        float dw) {
+#pragma clang fp contract(off)
+    const float mm = fmaf(ax, cx, fmaf(ay, cy, az * cz));
+    const float terms = fabsf(ax * cx) + fabsf(ay * cy) + fabsf(az * cz) + a2 + fabsf(dw);
+    return mm > fmaf(-8.f * kU, terms, b);
+}
+// A vertex at squared distance d2 from a box (r2 from the site) might be cut
+// by a site of it: d2 - wm < r2 - pw, with a margin for rounding.
+template <bool kW>
+__device__ __forceinline__ bool ball_test(float d2, float r2, float wm, float pw) {
+#pragma clang fp contract(off)
+    if constexpr (kW) return (d2 - wm) - (r2 - pw) <= 16.f * kU * (d2 + (r2 + fabsf(pw)) + fabsf(wm));
+    else return d2 - r2 <= 16.f * kU * (d2 + r2);
+}
+// Least plane distance of any site in a box at distance d (the farthest point
+// at dfar, read where dw > 0 and the tighter bound is asked for), dw = w_i less
+// the largest weight in it; made safe against the rounding of its terms.
+template <typename Far>
+__device__ __forceinline__ float least_plane(float d, float dw, bool tight, Far dfar) {
+#pragma clang fp contract(off)
+    float lb, err;
+    if (dw > 0.f && tight) {
+        // every site j in the box has b_j / |a_j| >= f(|a_j|) with
+        // f(t) = t/2 + dw/(2t), and |a_j| lies between the box's nearest
+        // and farthest distances: the bound is f at sqrt(dw) clamped to
+        // that range (the paper's bound keeps only dw < 0 and is d/2 here)
+        const float dc = fminf(fmaxf(__builtin_amdgcn_sqrtf(dw), d), dfar());
+        if (dc > 0.f) {
+            lb = fmaf(0.5f, dc, 0.5f * dw * __builtin_amdgcn_rcpf(dc));
+            err = lb;
+        } else {
+            lb = 0.5f * d;
+            err = 0.5f * d;
+        }
+    } else if (dw >= 0.f) {
+        lb = 0.5f * d;
+        err = 0.5f * d;
+    } else if (d > 0.f) {
+        const float q = 0.5f * dw * __builtin_amdgcn_rcpf(d);
+        lb = fmaf(0.5f, d, q);
+        err = fmaf(0.5f, d, -q);
+    } else {
+        lb = -INFINITY;
+        err = 0.f;
+    }
+    return fmaf(-16.f * kU, err, lb);
+}
+
+// A plane in FP64.
+struct P64 {
+    double a0, a1, a2, b;
+};
+// Intersection of three FP64 planes: y = n / det.
+struct Meet64 {
+    double bc0, bc1, bc2, ca0, ca1, ca2, ab0, ab1, ab2, det;
+    __device__ __forceinline__ Meet64(const P64& A, const P64& B, const P64& C) {
+        bc0 = B.a1 * C.a2 - B.a2 * C.a1; bc1 = B.a2 * C.a0 - B.a0 * C.a2; bc2 = B.a0 * C.a1 - B.a1 * C.a0;
+        ca0 = C.a1 * A.a2 - C.a2 * A.a1; ca1 = C.a2 * A.a0 - C.a0 * A.a2; ca2 = C.a0 * A.a1 - C.a1 * A.a0;
+        ab0 = A.a1 * B.a2 - A.a2 * B.a1; ab1 = A.a2 * B.a0 - A.a0 * B.a2; ab2 = A.a0 * B.a1 - A.a1 * B.a0;
+        det = fma(A.a2, bc2, fma(A.a0, bc0, A.a1 * bc1));
+    }
+    __device__ __forceinline__ void numerator(const P64& A, const P64& B, const P64& C, double* n) const {
+        n[0] = fma(C.b, ab0, fma(B.b, ca0, A.b * bc0));
+        n[1] = fma(C.b, ab1, fma(B.b, ca1, A.b * bc1));
+        n[2] = fma(C.b, ab2, fma(B.b, ca2, A.b * bc2));
+    }
+};
+// Sums over the tetrahedra (reference, Q, P, N): six times the volume and 24
+// times the moments, relative to the reference.
+struct Fan64 {
+    double vol6 = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
+    __device__ __forceinline__ void add(double Qx, double Qy, double Qz, double Px, double Py, double Pz, double Nx,
+                                        double Ny, double Nz) {
+        const double cx = Py * Nz - Pz * Ny, cy = Pz * Nx - Px * Nz, cz = Px * Ny - Py * Nx;
+        const double det = fma(Qz, cz, fma(Qx, cx, Qy * cy));
+        vol6 += det;
+        mx = fma(det, Qx + Px + Nx, mx);
+        my = fma(det, Qy + Py + Ny, my);
+        mz = fma(det, Qz + Pz + Nz, mz);
+    }
+};
+// One coordinate of the centroid; inv = 1 / (4 vol6).
+__device__ __forceinline__ float centroid_of(float p, double ref, double m, double inv) {
+    return (float)fma(m, inv, (double)p + ref);
+}
+
 // queue capacity of the pass of vertex capacity cap
 constexpr int queue_cap(int cap) { return cap < kQueue0 ? kQueue0 : cap; }
 
