@@ -10,8 +10,9 @@
 // A cell this pass cannot finish goes elsewhere: one that outgrows 64
 // vertices is handed on with its state (HandoffT) to the 128-vertex pass;
 // one whose FP32 signs turn out inconsistent, or whose path to the root has
-// more than 64 siblings, goes on the retry list, which the general 64-vertex
-// kernel builds from the start, with FP64 signs where needed.
+// more than 64 siblings, or in mixed precision one that meets a doubtful sign,
+// goes on the retry list, which the general 64-vertex kernel builds from the
+// start, with FP64 signs where needed.
 //
 // What bounds it: instruction issue, not memory.  One wave owns one cell
 // (vertex v in lane v).  With many cells the vector unit issues in four of
@@ -121,15 +122,9 @@ struct FinalMem {
     uint8_t next[256];    // 4 v + k -> the next vertex around facet k of v, with the facet's place there
     uint32_t fv[96];      // facet rings, two 16-bit vertex numbers a word
 };
-struct WaveMem64 {
-    union {
-        ClipMem c;
-        FinalMem f;
-    };
-    // cells for the retry list, added to it 64 at a time: a lattice in mixed
-    // precision sends all of them there, and one addition to the list's
-    // counter each, 20 ns over the whole device, took more than the cells
-    uint32_t retry[64];
+union WaveMem64 {
+    ClipMem c;
+    FinalMem f;
 };
 
 constexpr int kWaves64 = 4;  // waves per block
@@ -137,7 +132,8 @@ constexpr int kWaves64 = 4;  // waves per block
 #pragma clang attribute push(__attribute__((always_inline)), apply_to = function)
 
 // kW: the sites carry weights.  kMixed: signs FP32 cannot be sure of are
-// looked for, and a cell that meets one goes on the retry list.
+// looked for, and a cell that meets one goes on the retry list (it is marked,
+// and k_retries lists the marked ones).
 template <bool kW, bool kMixed>
 struct Cell64 {
     WaveMem64& M;
@@ -959,6 +955,19 @@ struct Cell64 {
                 sum.add(Qx, Qy, Qz, X0, X1, X2, Nx, Ny, Nz);
             }
         }
+        if constexpr (kMixed) {
+            // summed by vertex number, as the general pass does: which of the
+            // two builds a cell must not show (see run_cells64)
+            const int to = 4 * (int)(al ? v : (uint32_t)nv + mbcnt(~alive));
+            auto turn = [&](double& x) {
+                x = __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(x)),
+                                     __builtin_amdgcn_ds_permute(to, __double2loint(x)));
+            };
+            turn(sum.vol6);
+            turn(sum.mx);
+            turn(sum.my);
+            turn(sum.mz);
+        }
         const double vol6 = wsum64(sum.vol6), mx = wsum64(sum.mx), my = wsum64(sum.my), mz = wsum64(sum.mz);
         const uint32_t nbox = (uint32_t)popc(ballot(code < 0) & used);
         if (ln == 0) {
@@ -992,23 +1001,12 @@ struct Cell64 {
     }
 };
 
-__device__ void add_retries(WaveMem64& M, int count) {
-    KArgs* ka = cold_args();
-    const uint32_t ln = lane_id();
-    wave_sync<true>();
-    uint32_t at = 0;
-    if (ln == 0) at = atomicAdd(ka->retry_count, (uint32_t)count);
-    at = uni(at);
-    if ((int)ln < count) ka->retry_list[at + ln] = M.retry[ln];
-    wave_sync<true>();
-}
-
 template <bool kW, bool kMixed>
 __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
     if (*cold_args()->err != 0u) return;  // rejected input
     Cell64<kW, kMixed> C(M, A);
     unsigned long long st_empty = 0;
-    int waiting = 0;  // cells in M.retry
+    uint32_t missed = 0;  // cells in a row with a doubtful sign
     Work<kWaves64> work((uint32_t)A.n);
     for (;;) {
         const uint32_t k = work.next(uni((uint32_t)threadIdx.x >> 6));
@@ -1019,14 +1017,29 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
             res = C.traverse();
             if (res == kNone && !C.finalize(k, orig)) res = kRestart;
         }
+        if constexpr (kMixed) missed = res == kRestart ? missed : 0u;
         if (res == kEmptied) {
             C.write_empty(orig);
             ++st_empty;
         } else if (res == kRestart) {
-            if (C.ln == 0) M.retry[waiting] = k | (C.deep || kMixed ? 0u : kRetryChecked);
-            if (++waiting == 64) {
-                add_retries(M, waiting);
-                waiting = 0;
+            KArgs* kn = cold_args();
+            if (C.ln == 0) {
+                if constexpr (kMixed) kn->loc[k] = kLocRetry;  // listed by k_retries
+                else kn->retry_list[atomicAdd(kn->retry_count, 1u)] = k | (C.deep ? 0u : kRetryChecked);
+            }
+            // Checked signs: after six such cells in a row the next 8 of the
+            // wave's range go there untried, after one more the next 16, up to
+            // 64 (a claim for each would cost 20 ns over the whole device).  A
+            // set full of ties then costs the general pass and little else: a
+            // lattice of 262k sites 5.3 ms with every cell tried, 4.8 so, 4.5
+            // by the general pass alone; of 1M 20.3, 17.7 and 17.3.  Where one
+            // cell in ten has a doubtful sign one in a million begins this.
+            if constexpr (kMixed) {
+                if (++missed >= 6u) {
+                    uint32_t got = 0;
+                    const uint32_t first = work.more(8u << min(missed - 6u, 3u), &got);
+                    if (C.ln < got) kn->loc[first + C.ln] = kLocRetry;
+                }
             }
         } else if (res == kOverflow) {
             KArgs* kn = cold_args();
@@ -1034,12 +1047,12 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
             if (C.ln == 0) {
                 pos = atomicAdd(kn->next_count, 1u);
                 kn->next_list[pos] = k;
+                if constexpr (kMixed) kn->loc[k] = make_loc(1u, 0u);  // not kLocRetry, as it may stand there
             }
             pos = uni(pos);
             if (pos < kn->hand_out_cap) C.save(static_cast<HandoffT<64, kQueue0>*>(kn->hand_out)[pos]);
         }
     }
-    if (waiting > 0) add_retries(M, waiting);
     if (C.ln == 0 && st_empty) atomicAdd(&cold_args()->stats[kStatEmpty], st_empty);
 }
 
@@ -1055,6 +1068,34 @@ __global__ __launch_bounds__(64 * kWaves64, kMixed ? 6 : 7) void k_clip64(ClipAr
     run_cells64<kW, kMixed>(mem[threadIdx.x >> 6], A);
 }
 
+// Cells marked kLocRetry, listed in (nearly) Morton order: a block lists those
+// of kListCells cells in order.  The general pass gives each XCD a range of the
+// list, and in the order in which waves finish its caches were of less use (1M
+// sites of a lattice: 20.3 instead of 19.6 ms).
+constexpr int kListItems = 16, kListCells = 256 * kListItems;
+__global__ __launch_bounds__(256) void k_retries(const uint32_t* __restrict__ loc, int64_t n,
+                                                 const uint32_t* __restrict__ err, uint32_t* __restrict__ list,
+                                                 uint32_t* __restrict__ count) {
+    if (*err != 0u) return;
+    __shared__ uint32_t sums[4], base;
+    const int ln = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t first = (int64_t)blockIdx.x * kListCells + (int64_t)threadIdx.x * kListItems;
+    uint32_t m = 0;
+    for (int i = 0; i < kListItems; ++i)
+        if (first + i < n && loc[first + i] == kLocRetry) m |= 1u << i;
+    const uint32_t own = (uint32_t)__popc(m), upto = wscan_u(own);
+    if (ln == 63) sums[wv] = upto;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t total = sums[0] + sums[1] + sums[2] + sums[3];
+        base = total ? atomicAdd(count, total) : 0u;
+    }
+    __syncthreads();
+    uint32_t at = base + upto - own;
+    for (int k = 0; k < wv; ++k) at += sums[k];
+    for (; m; m &= m - 1u) list[at++] = (uint32_t)(first + __builtin_ctz(m));
+}
+
 template <bool kW, bool kMixed>
 hipError_t launch(const ClipArgs& a, int num_cu, hipStream_t s) {
     int per_cu = 0;
@@ -1063,6 +1104,9 @@ hipError_t launch(const ClipArgs& a, int num_cu, hipStream_t s) {
     int64_t blocks = (a.n + kWaves64 - 1) / kWaves64;
     if (blocks > (int64_t)per_cu * num_cu) blocks = (int64_t)per_cu * num_cu;
     hipLaunchKernelGGL((k_clip64<kW, kMixed>), dim3((unsigned)blocks), dim3(64 * kWaves64), 0, s, a);
+    if (kMixed)
+        hipLaunchKernelGGL(k_retries, dim3((unsigned)((a.n + kListCells - 1) / kListCells)), dim3(256), 0, s, a.loc, a.n,
+                           a.err, a.retry_list, a.retry_count);
     return hipGetLastError();
 }
 

@@ -70,6 +70,9 @@ struct Stage {
 
 // Location of a cell's staged record: tier in bits 30..31, slot below.
 __host__ __device__ inline uint32_t make_loc(uint32_t tier, uint32_t slot) { return (tier << 30) | slot; }
+// In its place while the 64-vertex passes run: the cell is left to the general
+// one (no slot has this number).
+constexpr uint32_t kLocRetry = 0xFFFFFFFFu;
 
 // Per-cell flag bits (mirror vd.h)
 constexpr uint32_t kFlagEmpty = 1u, kFlagFP64 = 2u, kFlagLarge = 4u, kFlagUncertain = 8u, kFlagFailed = 16u,
@@ -156,8 +159,8 @@ struct ClipArgs {
     const void* hand_in;
     uint32_t hand_in_cap;
     // cells the 64-vertex pass of vd_clip64.hip leaves to the general one:
-    // it writes the list (retry 0), the general pass builds it, each cell in
-    // its own slot (retry 1)
+    // listed behind it (retry 0), built by the general pass, each cell in its
+    // own slot (retry 1)
     uint32_t* retry_list;
     uint32_t* retry_count;
     int retry;
@@ -307,7 +310,8 @@ hipError_t launch_scan3(const Scan3Args& a, hipStream_t s);
 int clip_grid_workers(int tier, int num_cu);
 size_t arena_bytes_per_worker();
 hipError_t launch_clip(const ClipArgs& a, int workers, void* arena, hipStream_t s);
-// The 64-vertex pass of FP32 builds with the default search options.
+// The 64-vertex pass of builds with the default search options, in FP32 or
+// (a.precision 2) for the cells whose signs FP32 can be sure of.
 hipError_t launch_clip64(const ClipArgs& a, int num_cu, hipStream_t s);
 hipError_t launch_write(const WriteArgs& a, hipStream_t s);
 

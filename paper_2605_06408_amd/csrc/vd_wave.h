@@ -184,6 +184,18 @@ struct Work {
     __device__ __forceinline__ uint32_t workers(uint32_t q) const {
         return (gridDim.x + kWorkRanges - 1 - q) / kWorkRanges * kPerBlock;
     }
+    // Up to `want` cells on from the place of this worker's range: the first,
+    // and how many (none when the range is used up).
+    __device__ __forceinline__ uint32_t more(uint32_t want, uint32_t* got) {
+        const uint32_t range = blockIdx.x % kWorkRanges, given = workers(range), all = cells(range);
+        *got = 0;
+        if (stage != 1 || given >= all) return 0;
+        uint32_t c = 0;
+        if (lane_id() == 0) c = atomicAdd(&cold_args()->work_counter[range * kCounterStride], want);
+        c = uni(c) + given;
+        if (c < all) *got = min(want, all - c);
+        return start(range) + c;
+    }
     // The next cell, or kNoCell; called by one whole wave, the worker-th of
     // its workgroup.  The counter of range q is at work_counter[q * kCounterStride].
     __device__ __forceinline__ uint32_t next(uint32_t worker) {
