@@ -89,7 +89,7 @@ typedef struct vd_options {
 
 /* Phases reported by vd_get_timings (milliseconds, HIP events on `stream`). */
 #define VD_PHASE_LBVH 0       /* packing, Morton codes, radix sort, tree, bounds */
-#define VD_PHASE_CLIP 1       /* traversal + clipping, 64-vertex tier (one kernel) */
+#define VD_PHASE_CLIP 1       /* traversal + clipping, 64-vertex tier */
 #define VD_PHASE_CLIP_LARGE 2 /* traversal + clipping, 128-, 1024- and 16384-vertex tiers */
 #define VD_PHASE_SCAN 3       /* prefix sums of the per-cell counts */
 #define VD_PHASE_BUILD 4      /* the whole vd_build, first to last device operation */

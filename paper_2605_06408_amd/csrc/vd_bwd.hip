@@ -50,8 +50,10 @@
 namespace vd {
 namespace {
 
-// Vertices of a cell of the block class kept in LDS (105 KB, with vertex
-// gradients 130 KB); a larger one solves its vertices where a ring meets them.
+// Vertices of a cell of the block class kept in LDS (104 KB declared, with
+// vertex gradients 130 KB; the compiler puts arrays of the threads into what
+// is left, 156 and 136 KB in all); a larger one solves its vertices where a
+// ring meets them.
 constexpr int kBwdBlockCap = 2048;
 constexpr int kBwdBlockCapVert = 1536;
 
@@ -278,6 +280,8 @@ __global__ __launch_bounds__(256, (kTier < 2 ? 3 : 1)) void k_bwd_cells(BwdArgs 
     __shared__ Mem mem[kGroups];
     __shared__ double red[GS > 64 ? 4 * 256 : 1];
     __shared__ uint32_t redu[4];
+    static_assert(sizeof(mem) + sizeof(red) + sizeof(redu) <= 160 * 1024 / (kTier < 2 ? 3 : 1),
+                  "the groups of a block must fit the LDS of a CU, three blocks of the smaller classes");
     const int ln = threadIdx.x % GS, grp = threadIdx.x / GS;
     Mem& M = mem[grp];
     // every group of a wave takes the same number of turns (the sums over

@@ -1653,11 +1653,14 @@ _Pragma("unroll")
 
     // The candidates of `mask` (plane of lane L: a, b, size sb) that have
     // some vertex of the cell outside, or, when doubtful signs are
-    // re-evaluated, within rounding of it.  A plane that misses the cell
-    // misses every cell it is later clipped to, so the others need no clip:
-    // one pass over the vertices for the whole leaf (and for a wave group one
-    // exchange) instead of a selection and a clip each.  The test is the FP32
-    // side test of classify.
+    // re-evaluated, within rounding of it.  The others are left out: one pass
+    // over the vertices for the whole leaf (and for a wave group one exchange)
+    // instead of a selection and a clip each.  The test is the FP32 side test
+    // of classify.  Exactly, a plane that misses the cell misses every cell it
+    // is later clipped to; in FP32 a vertex made by a later clip of this leaf
+    // can come out beyond such a plane by its rounding, so this rule decides
+    // some cells' signs at that level (those of the passes above 64 vertices:
+    // the results of a build depend on it there, and it is the same in all).
     __device__ uint64_t cutting(uint64_t mask, float ax, float ay, float az, float b, float sb) {
         if constexpr (kCount) count(kCtrClassify, nalive() * (uint64_t)popc(mask));
         uint64_t cut = 0;  // candidates that put a vertex of this wave outside
@@ -2604,17 +2607,16 @@ __device__ void run_cells(WaveMem<VPL>& M, HotMem<VPL>& H, const ClipArgs& A, ui
 // Register tiers: per-cell arrays in LDS, WAVES independent waves per
 // block.  Register budgets: the 64-vertex pass is held to 128 registers for
 // 4 waves per SIMD (a few spills cost less than the lost occupancy: the pass
-// issues VALU work back to back), the 128-vertex pass to 256 for 2 (its
-// cells are fewer and longer: at 3 waves per SIMD the spills of its two
-// slots made each cell slower than the occupancy gained).
+// issues VALU work back to back), the 128-vertex pass to 256 for 2.  (It was
+// slower at 3 when it kept its cell in scratch memory; since it does not, 3
+// waves in 168 registers have been measured faster where it has many cells, 390
+// -> 383 ms on 20M surface sites, but are not in use: not tested enough.)
 template <int VPL, int WAVES, bool kCount, bool kSoS = false, bool kW = true, bool kOpt = true>
 __global__ __launch_bounds__(64 * WAVES, VPL == 1 ? 4 : 2) void k_clip(ClipArgs A) {
     __shared__ WaveMem<VPL> mem[WAVES];
     HotMem<VPL> none;
     run_cells<VPL, true, kCount, 1, kSoS, kW, kOpt>(mem[threadIdx.x >> 6], none, A, nullptr);
 }
-
-// Waves per cell in the 1024-vertex (LDS) and 16384-vertex (arena) tiers.
 
 // 1024-vertex tier: the kGroupLds waves of a block build one cell, its
 // arrays in LDS (one block per CU).
@@ -2637,7 +2639,7 @@ __global__ __launch_bounds__(64 * kGroupArena) void k_clip_arena(ClipArgs A, Wav
 }
 
 static_assert(kTierCap[0] == 64 && kTierCap[1] == 128 && kTierCap[2] == 1024,
-              "the LDS tiers are instantiated for 64, 256 and 1024 vertices");
+              "the passes with a cell in registers or LDS are instantiated for 64, 128 and 1024 vertices");
 static_assert(sizeof(WaveMem<16>) + sizeof(HotMem<16>) + 2 * kGroupLds * 8 * sizeof(uint32_t) <= 160 * 1024,
               "the 1024-vertex tier must fit the LDS of one CU");
 static_assert(sizeof(HotMem<kArenaVPL>) + 2 * kGroupArena * 8 * sizeof(uint32_t) <= 160 * 1024,

@@ -75,18 +75,6 @@ __device__ __forceinline__ float of_odd(float v) { return pair_move<0xF5>(v); } 
 __device__ __forceinline__ int imin_wave(int v) {
     return wave_reduce_i(v, [](int a, int b) { return min(a, b); });
 }
-// Inclusive sum over the lanes up to this one (lane moves within rows, then
-// the row totals passed on; lanes without a source add zero).
-__device__ __forceinline__ uint32_t scan_wave(uint32_t v) {
-    int x = (int)v;
-    x += dpp<0x111, 0xF>(0, x);  // row_shr:1
-    x += dpp<0x112, 0xF>(0, x);
-    x += dpp<0x114, 0xF>(0, x);
-    x += dpp<0x118, 0xF>(0, x);
-    x += dpp<0x142, 0xA>(0, x);  // row_bcast:15 into rows 1 and 3
-    x += dpp<0x143, 0xC>(0, x);  // row_bcast:31 into rows 2 and 3
-    return (uint32_t)x;
-}
 __device__ __forceinline__ double rdl64(double v, int l) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                             __builtin_amdgcn_readlane(__double2loint(v), l));
@@ -911,7 +899,7 @@ struct Cell64 {
         bool bad = false;
         {
             const uint32_t sz = M.f.size[ln], start = M.f.anchor[ln];
-            uint32_t at = scan_wave(sz) - sz;
+            uint32_t at = wscan_u(sz) - sz;
             if ((int)ln < F) {
                 ka->stage.fsize[base + ln] = (uint16_t)sz;
                 if (sz < 3u || start >= (uint32_t)nv) {
@@ -1058,10 +1046,11 @@ __device__ void run_cells64(WaveMem64& M, const ClipArgs& A) {
 
 #pragma clang attribute pop
 
-// 72 registers for 7 waves per SIMD: the loops fit, finishing a cell spills a
-// few values.  A build of clustered 1M sites, as first written: 20.7 ms at 4
-// waves, 18.8 at 5, 17.8 at 6, 17.2 at 7 and at 8 (64 registers, 44 spills).
-// With checked signs, two more values a lane, 6 waves.
+// 72 registers for 7 waves per SIMD: 21 values (22 with weights) go to scratch
+// memory, none in a loop of a cell (60 bytes a lane and cell).  A build of
+// clustered 1M sites, as first written: 20.7 ms at 4 waves, 18.8 at 5, 17.8 at
+// 6, 17.2 at 7 and at 8 (64 registers, 44 spills).  With checked signs, two
+// more values a lane, 6 waves (80 registers, 10 spills, 3 with weights).
 template <bool kW, bool kMixed>
 __global__ __launch_bounds__(64 * kWaves64, kMixed ? 6 : 7) void k_clip64(ClipArgs A) {
     __shared__ WaveMem64 mem[kWaves64];

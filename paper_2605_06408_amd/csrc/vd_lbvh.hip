@@ -123,7 +123,8 @@ hipError_t launch_morton(const float4* pts, int64_t n, const float* bbox, uint64
 // Above, one kernel makes the codes and the histograms of all eight digits at
 // once (the keys are in registers), then each pass is one kernel in which a
 // tile of keys finds its digits' places among the earlier tiles by looking
-// back over what they have published (decoupled look-back): a word per tile
+// back over what they have published (decoupled look-back, Merrill and Garland
+// 2016): a word per tile
 // and digit, 2 bits of state above the count.  A tile takes its number from a
 // counter, so every earlier tile is running or done, and publishes its own
 // counts before it waits: the wait ends.  Against a histogram, a three-kernel

@@ -101,12 +101,6 @@ __device__ __forceinline__ float wmin(float v) {
 __device__ __forceinline__ float wmax(float v) {
     return unford(wave_reduce_i(ford(v), [](int a, int b) { return max(a, b); }));
 }
-__device__ __forceinline__ uint64_t wor64(uint64_t v) {
-    auto op = [](int a, int b) { return a | b; };
-    const uint32_t lo = (uint32_t)wave_reduce_i((int)(uint32_t)v, op);
-    const uint32_t hi = (uint32_t)wave_reduce_i((int)(uint32_t)(v >> 32), op);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
 __device__ __forceinline__ uint32_t wsum_u(uint32_t v) {
     return (uint32_t)wave_reduce_i((int)v, [](int a, int b) { return (int)((uint32_t)a + (uint32_t)b); });
 }
@@ -141,9 +135,8 @@ __device__ __forceinline__ double wsum64(double v) {
 
 
 // Orders this wave's accesses to its per-cell arrays, so that what one lane
-// wrote before is seen by every lane after: LDS (one wave, no workgroup
-// barrier needed) or, for the arena tier, global memory (one wave per
-// workgroup).
+// wrote before is seen by every lane after: in LDS, or for the arena tier in
+// global memory.  Other waves need a barrier as well.
 template <bool kLds>
 __device__ __forceinline__ void wave_sync() {
     if constexpr (kLds) {
