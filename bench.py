@@ -54,10 +54,10 @@ PEAK_HBM_GBS = 8000.0     # MI355X HBM3E
 # workload, each scaled by what the same counter reads for a plain 256 MiB
 # device copy in the same run.  Valid only while the kernel source is unchanged.
 TRAFFIC_MEASURED = {
-    "sources_sha1": {"paper_2605_06408_amd/csrc/vd_clip64.hip": "c634f9103c3c10c792bd9e3c7e070a61b357637a",
-                     "paper_2605_06408_amd/csrc/vd_wave.h": "ac131df0b58a94ed0ee41e359f23f2d971565ba1",
-                     "paper_2605_06408_amd/csrc/vd_internal.h": "570b642f00a26908eacd2b55d8c5c5620fcf83be"},
-    "workload": "clustered_1m", "fetch_kib": 175635.0625, "write_kib": 1414655.34375, "fetch_scale": 2.0,
+    "sources_sha1": {"paper_2605_06408_amd/csrc/vd_clip64.hip": "d0da95eabfbc4553bdbc6ec0c793e28083db19c0",
+                     "paper_2605_06408_amd/csrc/vd_wave.h": "7e9481ba8f48d2ebb230c8377eda2cba7b73542c",
+                     "paper_2605_06408_amd/csrc/vd_internal.h": "77043e06fc2979f323395e4a39c5558cdcfe5d1a"},
+    "workload": "clustered_1m", "fetch_kib": 166202.125, "write_kib": 1487640.75, "fetch_scale": 2.0,
     "write_scale": 1.0,
 }
 
