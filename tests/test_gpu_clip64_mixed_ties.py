@@ -56,3 +56,26 @@ def test_route_does_not_show(kind, n):
             if a.dtype == torch.float32:  # bits, so that a NaN equals itself
                 a, b = a.view(torch.int32), b.view(torch.int32)
             assert torch.equal(a, b), k
+
+
+def test_passes_run_again():
+    """More cells beyond 128 vertices than a fresh context has room for (1024):
+    the passes run a second time, over the marks and lists of the first.  1600
+    sites, each inside a sphere of 70 others, on a lattice of spheres."""
+    import torch
+    import paper_2605_06408_amd as vd
+    rng = np.random.default_rng(8)
+    g = np.stack(np.meshgrid(np.arange(16), np.arange(10), np.arange(10), indexing="ij"), -1).reshape(-1, 1, 3) + 0.5
+    u = rng.normal(size=(len(g), 70, 3))
+    u *= 0.2 / np.linalg.norm(u, axis=2, keepdims=True)
+    xyz = np.concatenate([g, g + u], 1).reshape(-1, 3)
+    xyz = torch.from_numpy(xyz[rng.permutation(len(xyz))].astype(np.float32)).cuda()
+    box = [0.0, 0, 0, 16, 10, 10]
+    fresh = vd.Context(0).build(xyz, None, box, precision=2)
+    assert int((torch.diff(fresh.vert_off) > 128).sum()) > 1024
+    ctx = vd.Context(0)
+    general = ctx.build(xyz, None, box, precision=2, counters=True)
+    again = ctx.build(xyz, None, box, precision=2)
+    for k in vd.OUTPUT_FIELDS:
+        assert torch.equal(getattr(fresh, k), getattr(general, k)), k
+        assert torch.equal(getattr(again, k), getattr(general, k)), k
